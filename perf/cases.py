@@ -229,3 +229,115 @@ def tolerance(case):
     if case["path"] == "receive":
         return "exact"
     return {"rel": 2e-7, "max": 1e-6, "differ": 4e-6}
+
+
+# ---- the same results in 64 bits ------------------------------------------------------------------
+
+def _constant(bits, dist):
+    """The minimiser a of ACIQ's expected error at this bitwidth: Laplace a e^a = 3 4^q, Gaussian phi(a) - a Q(a) = a / (6 4^q)."""
+    def excess(a):
+        if dist == qp.QP_GAUSS:
+            return math.exp(-0.5 * a * a) / math.sqrt(2 * math.pi) - a * 0.5 * math.erfc(a / math.sqrt(2)) - a / (6.0 * 4.0 ** bits)
+        return math.log(3.0 * 4.0 ** bits) - math.log(a) - a
+    lo, hi = 1e-3, 100.0
+    for _ in range(200):
+        mid = 0.5 * (lo + hi)
+        lo, hi = (mid, hi) if excess(mid) > 0 else (lo, mid)
+    return 0.5 * (lo + hi)
+
+
+def _grid(center, alpha, bits, clip):
+    """[lo, hi, scale, 1/scale] as the record holds them, in 32 bits."""
+    def f32(v):
+        return torch.tensor(v, dtype=torch.float64).to(torch.float32).item()
+    lo, hi = f32(f32(center) - f32(alpha)), f32(f32(center) + f32(alpha))
+    if clip:
+        lo, hi = max(lo, clip[0]), min(hi, clip[1])
+    if not hi > lo:
+        return [lo, hi, 0.0, 0.0]
+    levels = 2.0 ** bits - 1
+    return [lo, hi, f32((hi - lo) / levels), f32(levels / (hi - lo))]
+
+
+def _expanded(x, grid, bits):
+    """What the receiver holds: codes by the 32-bit rule, lo + code scale in 64 bits rounded once."""
+    lo, hi, scale, inv = grid
+    code = ((x.clamp(lo, hi) - torch.tensor(lo, device=DEVICE)) * torch.tensor(inv, device=DEVICE)).round_().clamp_(0, 2 ** bits - 1)
+    return code.double().mul_(scale).add_(lo).float()
+
+
+def _sender(x, bits, flags, dist):
+    x = x.float()
+    n, d = x.numel(), x.double()
+    mean, mn, mx = d.mean().item(), x.min(), x.max()
+    nbins = 2048
+    bins = ((x - mn) * (nbins / (mx - mn).double()).float()).clamp_(0, nbins - 1).to(torch.int64)
+    hist = torch.bincount(bins, minlength=nbins).double()
+    width = (mx.double() - mn.double()).item() / nbins
+    peak = int(hist.max().item())
+    stats = {"mean": mean, "mad": (d - mean).abs_().mean().item(), "abs_mean": d.abs().mean().item(),
+             "var": (d - mean).square_().mean().item(), "min": mn.item(), "max": mx.item(), "peak": peak,
+             "peak_density": peak / (n * width)}
+    stats["b_r"] = 1.0 / (2.0 * stats["peak_density"])
+    if dist == qp.QP_DIST_AUTO:
+        z = mn.double() + (torch.arange(nbins, device=DEVICE, dtype=torch.float64) + 0.5) * width - mean
+        dens, b, var = hist / (n * width), stats["mad"], stats["var"]
+        fit_l = (dens - (-z.abs() / b).exp() / (2 * b)).square().sum().item()
+        fit_g = (dens - (-z * z / (2 * var)).exp() / math.sqrt(2 * math.pi * var)).square().sum().item()
+        dist = qp.QP_GAUSS if fit_g < fit_l else qp.QP_LAPLACE
+    if dist == qp.QP_GAUSS:
+        s_e, s_r = math.sqrt(stats["var"]), 1.0 / (math.sqrt(2 * math.pi) * stats["peak_density"])
+    else:
+        s_e, s_r = stats["mad"], stats["b_r"]
+    t, c = 100, _constant(bits, dist)
+    step = (s_r - s_e) / t
+    clip = (stats["min"], stats["max"]) if flags & qp.QP_SEARCH_CLIP_TO_DATA else None
+    scores = [math.nan] * (t + 1)
+
+    def score(js):
+        for j in js:
+            if scores[j] != scores[j]:
+                scores[j] = (d - _expanded(x, _grid(mean, c * (s_e + j * step), bits, clip), bits).double()).square_().sum().item()
+        return min(js, key=lambda j: (scores[j], j))
+
+    if flags & qp.QP_SEARCH_LOW_BITS_ONLY and bits > 4:
+        win = 0
+    elif flags & qp.QP_SEARCH_COARSE_TO_FINE:
+        first = score(list(range(0, t + 1, 10)))
+        win = score(list(range(max(0, first - 9), min(t, first + 9) + 1)))
+    else:
+        win = score(list(range(t + 1)))
+    alpha = c * (s_e + win * step)
+    result = [s_e, s_r, s_e + win * step, alpha, scores[0] / n, scores[win] / n]
+    return stats, scores, result, _grid(mean, alpha, bits, clip), x
+
+
+def exact(case, seed):
+    s = prepare(case, seed)
+    bits = case["bits"]
+
+    def f64(v):
+        return torch.tensor(v, dtype=torch.float64)
+    if case["path"] == "receive":
+        n = case["n"]
+        words = torch.cat([s["packed"].view(torch.int32), torch.zeros(1, dtype=torch.int32, device=DEVICE)])
+        y = torch.empty(n, dtype=torch.float64, device=DEVICE)
+        for at in range(0, n, 1 << 24):
+            bit = torch.arange(at, min(n, at + (1 << 24)), device=DEVICE, dtype=torch.int64) * bits
+            word = bit >> 5
+            both = (words[word].long() & 0xffffffff) | ((words[word + 1].long() & 0x7fffffff) << 32)
+            y[at:at + bit.numel()] = ((both >> (bit & 31)) & (2 ** bits - 1)).double() * s["q"].scale + s["q"].lo
+        return y
+    if case["path"] == "stream":
+        grids, ys = [], []
+        for x in s["x"]:
+            *_, grid, x32 = _sender(x, bits, case["flags"], case["dist"])
+            grids.append(f64(grid))
+            ys.append(_expanded(x32, grid, bits).double())
+        return {"packed": [None] * len(grids), "grid": grids, "y": ys}
+    stats, scores, result, grid, x32 = _sender(s["x"], bits, case["flags"], case["dist"])
+    if case["path"] == "send":
+        return {"packed": None, "grid": f64(grid), "moments": f64([stats[k] for k in ("mean", "mad", "abs_mean", "var", "min", "max")]),
+                "density": f64([stats["peak_density"], stats["b_r"]]), "result": f64(result), "winner": None, "scores": f64(scores)}
+    return {"mean": stats["mean"], "mad": stats["mad"], "var": stats["var"], "b_r": stats["b_r"], "peak": None, "alpha": result[3],
+            "winner": None, "mse": result[5], "mse_aciq": result[4], "packed": None, "y": _expanded(x32, grid, bits).double()}
