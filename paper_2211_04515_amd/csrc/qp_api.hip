@@ -319,13 +319,14 @@ qp_status qp_dsaciq_hist_search(uint32_t bits, const qp_search_cfg_t *cfg, void 
 }
 
 static qp_status pack_common(const void *x_dev, uint64_t n, qp_dtype dtype, uint32_t bits, const qp_qparams_t *hq,
-                             const qp_qparams_t *dq, void *packed_dev, size_t packed_bytes, void *stream)
+                             const qp_qparams_t *dq, void *packed_dev, size_t packed_bytes, void *stream,
+                             qp_qparams_t *dq_out = nullptr)
 {
     if (!x_dev || !packed_dev || n == 0 || n > kMaxN || !dtype_ok(dtype) || !bits_ok(bits) || !aligned16(x_dev) ||
         !aligned16(packed_dev))
         return QP_EINVAL;
     if (packed_bytes < qp_packed_bytes(n, bits)) return QP_ENOSPC;
-    return hip_status(launch_quant_pack(x_dev, n, dtype, bits, hq, dq, packed_dev, static_cast<hipStream_t>(stream)));
+    return hip_status(launch_quant_pack(x_dev, n, dtype, bits, hq, dq, packed_dev, dq_out, static_cast<hipStream_t>(stream)));
 }
 
 qp_status qp_quant_pack(const void *x_dev, uint64_t n, qp_dtype dtype, const qp_qparams_t *qparams, void *packed_dev,
@@ -400,13 +401,7 @@ qp_status qp_compress_async(const void *x_dev, uint64_t n, qp_dtype dtype, uint3
     st = search_common(x_dev, n, dtype, nullptr, bits, cfg, ws_dev, ws_bytes, stream, final_record ? 0u : nbins, table);
     if (st != QP_OK) return st;
     const qp_qparams_t *qdev = reinterpret_cast<const qp_qparams_t *>(static_cast<char *>(ws_dev) + kOffQParams);
-    st = qp_quant_pack_dev(x_dev, n, dtype, bits, qdev, packed_dev, packed_bytes, stream);
-    if (st != QP_OK) return st;
-    if (qparams_out_dev &&
-        hipMemcpyAsync(qparams_out_dev, qdev, sizeof(qp_qparams_t), hipMemcpyDeviceToDevice,
-                       static_cast<hipStream_t>(stream)) != hipSuccess)
-        return QP_EHIP;
-    return QP_OK;
+    return pack_common(x_dev, n, dtype, bits, nullptr, qdev, packed_dev, packed_bytes, stream, qparams_out_dev);
 }
 
 qp_status qp_compress_many_async(const qp_job_t *jobs, uint32_t count, const qp_search_cfg_t *cfg, const qp_lane_t *lanes,

@@ -731,8 +731,9 @@ ModelArgs model_args(const SearchPlan &plan, const qp_stats_t *stats_host_or_nul
 hipError_t launch_model_fit(void *ws, hipStream_t s);
 uint32_t search_blocks(uint64_t n);
 hipError_t launch_hist_search(uint32_t bits, uint32_t t_steps, double F, void *ws, hipStream_t s);
+// dev_qp_out (or null): where the record of dev_qp is copied to.
 hipError_t launch_quant_pack(const void *x, uint64_t n, int dtype, uint32_t bits, const qp_qparams_t *host_qp,
-                             const qp_qparams_t *dev_qp, void *packed, hipStream_t s);
+                             const qp_qparams_t *dev_qp, void *packed, qp_qparams_t *dev_qp_out, hipStream_t s);
 // The search with one candidate per lane over LDS-staged tiles, for tensors of at most
 // kTileSearchMaxN elements and at most 256 candidates (same arguments as launch_search).
 bool tile_search_eligible(uint64_t n, const SearchPlan &plan);
