@@ -105,9 +105,10 @@ template <int DT> __global__ __launch_bounds__(kStThreads) void k_search_tile(Ti
         if (e0 + kStSub < e_end) load_sub(e0 + kStSub);   // next sub-tile in flight while this one is scored
         const uint32_t nv = (uint32_t)min((uint64_t)kStSub, e_end - e0);
         const uint32_t nv4 = nv / 4u;
-        const uint32_t per = (nv4 + S - 1u) / S;
+        // slice k takes the groups k, k + S, ...: every slice the same number `trips`, the first few one more
+        const uint32_t trips = nv4 / S;
+        const float4 *mine = reinterpret_cast<const float4 *>(sh_x) + slice;
         if (active) {
-            const uint32_t g0 = min(slice * per, nv4), g1 = min(g0 + per, nv4);
             auto run = [&](auto short_tag) {
                 constexpr bool SHORT = decltype(short_tag)::value;
                 auto one = [&](float xv, double &acc) {
@@ -125,27 +126,34 @@ template <int DT> __global__ __launch_bounds__(kStThreads) void k_search_tile(Ti
                     const double de = (double)err;
                     acc = fma(de, de, acc);   // de*de is exact in fp64
                 };
-                // two groups of four per step, each with its own running sum: both LDS reads are issued
-                // before the arithmetic, and the two fp64 accumulation chains interleave
-                uint32_t g = g0;
-                for (; g + 2 <= g1; g += 2) {
-                    const float4 xa = reinterpret_cast<const float4 *>(sh_x)[g];
-                    const float4 xb = reinterpret_cast<const float4 *>(sh_x)[g + 1];
-                    one(xa.x, acc0);
-                    one(xb.x, acc1);
-                    one(xa.y, acc0);
-                    one(xb.y, acc1);
-                    one(xa.z, acc0);
-                    one(xb.z, acc1);
-                    one(xa.w, acc0);
-                    one(xb.w, acc1);
+                // Eight groups of four per step (of the short sequence), two running sums: the LDS reads are issued before
+                // the arithmetic, which only two to four waves per SIMD are there to hide, and the fp64 chains interleave.
+                // The trip count is the same for all lanes, so the loop is scalar work (with a range of groups per
+                // slice it was 6 of 70 vector instructions).  Sender path of 1 M fp32 elements, per step 2 (ranges) / 2 / 4 /
+                // 8 groups: 44.0 / 44.3 / 42.2 / 41.8 us.
+                constexpr uint32_t U = SHORT ? 8u : 1u;
+                uint32_t i = 0;
+#pragma unroll 1
+                for (; i + U <= trips; i += U) {
+                    float4 v[U];
+#pragma unroll
+                    for (uint32_t u = 0; u < U; ++u) v[u] = mine[(i + u) * S];
+#pragma unroll
+                    for (uint32_t u = 0; u < U; ++u) {
+                        double &acc = u % 2u ? acc1 : acc0;
+                        one(v[u].x, acc);
+                        one(v[u].y, acc);
+                        one(v[u].z, acc);
+                        one(v[u].w, acc);
+                    }
                 }
-                if (g < g1) {
-                    const float4 xa = reinterpret_cast<const float4 *>(sh_x)[g];
-                    one(xa.x, acc0);
-                    one(xa.y, acc0);
-                    one(xa.z, acc0);
-                    one(xa.w, acc0);
+#pragma unroll 1
+                for (; i * S + slice < nv4; ++i) {
+                    const float4 v = mine[i * S];
+                    one(v.x, acc0);
+                    one(v.y, acc1);
+                    one(v.z, acc0);
+                    one(v.w, acc1);
                 }
                 if (slice == 0)   // the tensor's ragged end (fewer than 4 elements)
                     for (uint32_t e = 4u * nv4; e < nv; ++e) one(sh_x[e], acc0);
@@ -215,10 +223,10 @@ bool tile_search_eligible(uint64_t n, const SearchPlan &plan)
 static uint64_t tile_share(uint64_t n)
 {
     // Shares of whole 128-element groups, at least 512 elements.  The grid is a whole number of blocks per
-    // compute unit (no unit gets one more than another): one, or two from about two sub-tiles per unit on,
-    // whose staging and scoring then overlap (2 M elements: 62 -> 57 us; coarse-to-fine on 9.7 M: 103 -> 90 us).
-    const uint64_t per_cu = (n + (uint64_t)kStMaxBlocks * kStSub / 2) / ((uint64_t)kStMaxBlocks * kStSub);   // rounded
-    const uint64_t blocks = (uint64_t)kStMaxBlocks * (per_cu >= 2 ? 2 : 1);
+    // compute unit (no unit gets one more than another): one while its share is one sub-tile, else two, whose staging
+    // and scoring then overlap (sender path, one / two blocks: 1 M elements 42.2 / 42.7 us, 1.23 M 48.8 / 47.5 us; 2 M
+    // search 62 / 57 us; coarse-to-fine on 9.7 M 103 / 90 us).
+    const uint64_t blocks = (uint64_t)kStMaxBlocks * (n > (uint64_t)kStMaxBlocks * kStSub ? 2 : 1);
     uint64_t share = (n + blocks - 1) / blocks;
     share = (share + 127) / 128 * 128;
     return share < 512 ? 512 : share;
