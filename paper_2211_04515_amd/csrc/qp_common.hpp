@@ -719,7 +719,8 @@ hipError_t launch_search(const void *x, uint64_t n, int dtype, const SearchPlan 
 // Large bf16 tensors: the table of value counts (zeroed and built in one pass over the tensor) and the
 // statistics record and histogram computed from it.
 bool uses_value_table(uint64_t n, int dtype);
-hipError_t launch_value_table(const void *x, uint64_t n, void *ws, hipStream_t s);
+// (nbins != 0: launch_stats_from_table will follow; the histogram is cleared)
+hipError_t launch_value_table(const void *x, uint64_t n, uint32_t nbins, void *ws, hipStream_t s);
 hipError_t launch_stats_from_table(uint64_t n, uint32_t nbins, void *ws, hipStream_t s);
 // The directed search over the value table (which must be built): one launch, no set-up kernel.
 hipError_t launch_table_search(uint64_t n, const SearchPlan &plan, const qp_stats_t *stats_host_or_null, void *ws, hipStream_t s);

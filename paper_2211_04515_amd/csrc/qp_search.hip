@@ -615,7 +615,7 @@ hipError_t launch_search(const void *x, uint64_t n, int dtype, const SearchPlan 
     if (uses_value_table(n, dtype)) {
         if (plan.stride > 1u || finalize_nbins) return hipErrorInvalidValue;   // refused / the table path finalizes itself
         if (!value_table_ready) {
-            const hipError_t e = launch_value_table(x, n, ws, s);
+            const hipError_t e = launch_value_table(x, n, 0u, ws, s);
             if (e != hipSuccess) return e;
         }
         return launch_table_search(n, plan, st, ws, s);

@@ -15,11 +15,18 @@ namespace qp {
 
 bool uses_value_table(uint64_t n, int dtype) { return dtype == QP_BF16 && n >= kValueTableMinN; }
 
-// Also clears the search's ticket: the search over the table has no set-up launch that could.
-__global__ __launch_bounds__(1024) void k_value_table_zero(uint32_t *__restrict__ counts, Ctl *__restrict__ ctl)
+// Also clears the tickets (the search over the table has no set-up launch that could) and, for statistics, the
+// histogram (nbins != 0).
+__global__ __launch_bounds__(1024) void k_value_table_zero(uint32_t *__restrict__ counts, uint32_t *__restrict__ hist,
+                                                           uint32_t nbins, Ctl *__restrict__ ctl)
 {
-    reinterpret_cast<uint4 *>(counts)[blockIdx.x * 1024u + threadIdx.x] = make_uint4(0u, 0u, 0u, 0u);
-    if (blockIdx.x == 0 && threadIdx.x == 0) ctl->ticket_search = 0u;
+    const uint32_t i = blockIdx.x * 1024u + threadIdx.x;
+    reinterpret_cast<uint4 *>(counts)[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (i < nbins) hist[i] = 0u;
+    if (i == 0) {
+        ctl->ticket_search = 0u;
+        ctl->ticket_stats = 0u;
+    }
 }
 
 // A block counts one sign (32768 patterns, 128 KB of LDS, plain u32 counters) of one chunk of the
@@ -75,10 +82,13 @@ __device__ __forceinline__ void value_hist_loop(const uint16_t *__restrict__ x, 
     }
 }
 
+// Every block also leaves the first pass's partial (sums, range, NaN/Inf) of what it counted: it has the counts in LDS
+// and looks at each of them anyway.
 __global__ __launch_bounds__(kVhThreads) void k_value_hist_bf16(const uint16_t *__restrict__ x, uint64_t n,
-                                                                uint32_t *__restrict__ counts)
+                                                                uint32_t *__restrict__ counts, Part1 *__restrict__ part)
 {
     __shared__ uint32_t sh[32768];
+    __shared__ Part1 sh1[kVhThreads / kWave];
     const uint32_t tid = threadIdx.x;
     const uint32_t sign = (blockIdx.x >> 3) & 1u;
     const uint32_t chunk = ((blockIdx.x >> 4) << 3) | (blockIdx.x & 7u);
@@ -90,73 +100,15 @@ __global__ __launch_bounds__(kVhThreads) void k_value_hist_bf16(const uint16_t *
     if (sign) value_hist_loop<1>(x, n, chunk, nchunks, sh);
     else value_hist_loop<0>(x, n, chunk, nchunks, sh);
     __syncthreads();
-    for (uint32_t i = tid; i < 32768u; i += kVhThreads) {
-        const uint32_t c = sh[i];
-        if (c) atomicAdd(&counts[(sign << 15) | i], c);
-    }
-}
-
-hipError_t launch_value_table(const void *x, uint64_t n, void *ws, hipStream_t s)
-{
-    uint32_t *counts = reinterpret_cast<uint32_t *>(static_cast<char *>(ws) + kOffValueCounts);
-    hipLaunchKernelGGL(k_value_table_zero, dim3(kNumValues16 / 4096u), dim3(1024), 0, s, counts,
-                       reinterpret_cast<Ctl *>(static_cast<char *>(ws) + kOffCtl));
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const uint64_t tile = (uint64_t)kVhThreads * kVhUnroll;               // 16-byte vectors per block step
-    uint64_t chunks = ((n / 8) + tile - 1) / tile;
-    chunks = (chunks + 7) / 8 * 8;                                        // whole groups of 8 (one per XCD)
-    if (chunks > 128) chunks = 128;                                       // two blocks (signs) per chunk: one block per compute unit
-    hipLaunchKernelGGL(k_value_hist_bf16, dim3((uint32_t)(2 * chunks)), dim3(kVhThreads), 0, s,
-                       static_cast<const uint16_t *>(x), n, counts);
-    return hipGetLastError();
-}
-
-// ---- statistics from the table ---------------------------------------------------------------
-// One block.  Pass A over the table: sum c v, sum c |v|, min, max, count of NaN/Inf patterns;
-// pass B: sum c |v - mu|, sum c (v - mu)^2 and the histogram (bin of the value, weight c), with
-// exactly the per-value arithmetic of the streaming kernels (fp32 bin index, fp64 moments).
-// c v is exact in fp64 (c < 2^32, v has 8 significant bits); sums are taken in a fixed order.
-constexpr int kTsThreads = 1024;
-__global__ __launch_bounds__(kTsThreads) void k_stats_from_table(const uint32_t *__restrict__ counts, uint64_t n,
-                                                                 uint32_t nbins, uint32_t *__restrict__ hist,
-                                                                 qp_stats_t *__restrict__ out)
-{
-    // the histogram in 8 (more than 2048 bins: 4) interleaved copies, copy = lane mod 8: neighbouring
-    // lanes hold neighbouring values, which mostly fall into the same bin
-    __shared__ uint32_t sh_hist[4 * kMaxBins];
-    __shared__ Part1 sh1[kTsThreads / kWave];
-    __shared__ Part2 sh2[kTsThreads / kWave];
-    __shared__ uint32_t sh_pk[kTsThreads / kWave];
-    __shared__ Part1 tot1;
-    const uint32_t tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-    constexpr uint32_t per = kNumValues16 / kTsThreads;   // 64 table entries per lane
-    const uint32_t rep_shift = nbins <= kMaxBins / 2 ? 3u : 2u;
-    const uint32_t copy = tid & ((1u << rep_shift) - 1u);
-    for (uint32_t b = tid; b < (nbins << rep_shift); b += kTsThreads) sh_hist[b] = 0u;
-
-    // ---- pass A ----
-    // a lane's 64 entries are four consecutive ones in each of 16 strides: 16 independent 16-byte loads,
-    // all in flight at once (one block reads the whole 256 KB table, so latency is what counts)
-    uint32_t cnt[per];
-#pragma unroll
-    for (uint32_t k = 0; k < per / 4; ++k) {
-        const uint4 c4 = reinterpret_cast<const uint4 *>(counts)[k * kTsThreads + tid];
-        cnt[4 * k] = c4.x;
-        cnt[4 * k + 1] = c4.y;
-        cnt[4 * k + 2] = c4.z;
-        cnt[4 * k + 3] = c4.w;
-    }
     double s = 0.0, sa = 0.0;
     float mn = INFINITY, mx = -INFINITY;
     uint32_t bad = 0u;
-#pragma unroll
-    for (uint32_t k = 0; k < per; ++k) {
-        const uint32_t p = ((k / 4) * kTsThreads + tid) * 4 + (k % 4);
-        const uint32_t c = cnt[k];
+    for (uint32_t i = tid; i < 32768u; i += kVhThreads) {
+        const uint32_t c = sh[i], pattern = (sign << 15) | i;
         if (c) {
-            const float v = __uint_as_float(p << 16);
-            const double d = (double)v, w = (double)c;
+            atomicAdd(&counts[pattern], c);
+            const float v = __uint_as_float(pattern << 16);
+            const double d = (double)v, w = (double)c;   // w d is exact: c < 2^32, v has 8 significant bits
             s = fma(w, d, s);
             sa = fma(w, fabs(d), sa);
             mn = fminf(mn, v);
@@ -169,81 +121,138 @@ __global__ __launch_bounds__(kTsThreads) void k_stats_from_table(const uint32_t 
     mn = wave_min(mn);
     mx = wave_max(mx);
     bad = wave_sum_u32(bad);
-    if (lane == 0) sh1[wave] = Part1{s, sa, mn, mx, bad, 0u};
+    if (tid % kWave == 0) sh1[tid / kWave] = Part1{s, sa, mn, mx, bad, 0u};
     __syncthreads();
     if (tid == 0) {
         Part1 t = sh1[0];
-        for (int k = 1; k < kTsThreads / kWave; ++k) {
+        for (int k = 1; k < kVhThreads / kWave; ++k) {
             t.sum += sh1[k].sum;
             t.sum_abs += sh1[k].sum_abs;
             t.mn = fminf(t.mn, sh1[k].mn);
             t.mx = fmaxf(t.mx, sh1[k].mx);
             t.bad += sh1[k].bad;
         }
-        tot1 = t;
-    }
-    __syncthreads();
-
-    // ---- pass B ----
-    const double mean = tot1.sum / (double)n;
-    const float lo = tot1.mn;
-    const float range = tot1.mx - lo;
-    const float w_inv = (float)((double)(float)nbins / (double)range);
-    const float top = (float)(nbins - 1u);
-    double dev = 0.0, sq = 0.0;
-    // a lane's four consecutive values usually share a bin: their counts are added up first
-    uint32_t run_idx = 0u, run_cnt = 0u;
-#pragma unroll
-    for (uint32_t k = 0; k < per; ++k) {
-        const uint32_t c = cnt[k];
-        if (c) {
-            const float v = __uint_as_float((((k / 4) * kTsThreads + tid) * 4 + (k % 4)) << 16);
-            const double d = (double)v - mean, w = (double)c;
-            dev = fma(w, fabs(d), dev);
-            sq = fma(w * d, d, sq);
-            const float tt = (v - lo) * w_inv;
-            const uint32_t idx = (uint32_t)__builtin_amdgcn_fmed3f(tt, 0.0f, top);   // NaN -> 0
-            if (idx != run_idx && run_cnt) {
-                atomicAdd(&sh_hist[(run_idx << rep_shift) + copy], run_cnt);
-                run_cnt = 0u;
-            }
-            run_idx = idx;
-            run_cnt += c;
-        }
-    }
-    if (run_cnt) atomicAdd(&sh_hist[(run_idx << rep_shift) + copy], run_cnt);
-    dev = wave_sum(dev);
-    sq = wave_sum(sq);
-    if (lane == 0) sh2[wave] = Part2{dev, sq};
-    __syncthreads();   // also: the histogram is complete
-    uint32_t peak = 0u;
-    for (uint32_t b = tid; b < nbins; b += kTsThreads) {
-        uint32_t c = 0u;
-        for (uint32_t r = 0; r < (1u << rep_shift); ++r) c += sh_hist[(b << rep_shift) + r];
-        hist[b] = c;
-        peak = max(peak, c);
-    }
-    peak = wave_max_u32(peak);
-    if (lane == 0) sh_pk[wave] = peak;
-    __syncthreads();
-    if (tid == 0) {
-        Part2 t2 = sh2[0];
-        uint32_t pk = sh_pk[0];
-        for (int k = 1; k < kTsThreads / kWave; ++k) {
-            t2.dev += sh2[k].dev;
-            t2.sq += sh2[k].sq;
-            pk = max(pk, sh_pk[k]);
-        }
-        *out = stats_record(tot1, t2, pk, nbins, n);
+        part[blockIdx.x] = t;
     }
 }
 
+// blocks of k_value_hist_bf16, i.e. partials that it leaves
+static uint32_t value_hist_blocks(uint64_t n)
+{
+    const uint64_t tile = (uint64_t)kVhThreads * kVhUnroll;               // 16-byte vectors per block step
+    uint64_t chunks = ((n / 8) + tile - 1) / tile;
+    chunks = (chunks + 7) / 8 * 8;                                        // whole groups of 8 (one per XCD)
+    if (chunks > 128) chunks = 128;                                       // two blocks (signs) per chunk: one block per compute unit
+    return (uint32_t)(2 * chunks);
+}
+static_assert(256u <= kMaxStat1Blocks && 256u <= (uint32_t)kFinThreads, "a partial per block");
+
+hipError_t launch_value_table(const void *x, uint64_t n, uint32_t nbins, void *ws, hipStream_t s)
+{
+    char *w = static_cast<char *>(ws);
+    uint32_t *counts = reinterpret_cast<uint32_t *>(w + kOffValueCounts);
+    hipLaunchKernelGGL(k_value_table_zero, dim3(kNumValues16 / 4096u), dim3(1024), 0, s, counts,
+                       reinterpret_cast<uint32_t *>(w + kOffHist), nbins, reinterpret_cast<Ctl *>(w + kOffCtl));
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_value_hist_bf16, dim3(value_hist_blocks(n)), dim3(kVhThreads), 0, s, static_cast<const uint16_t *>(x), n, counts,
+                       reinterpret_cast<Part1 *>(w + kOffPart1));
+    return hipGetLastError();
+}
+
+// ---- statistics from the table ---------------------------------------------------------------
+// The second pass over the table, a thousand patterns per block: sum c |v - mu|, sum c (v - mu)^2 and the histogram (bin of
+// the value, weight c), with exactly the per-value arithmetic of the streaming kernel (fp32 bin index, fp64 moments).  Every
+// block adds the first pass's partials itself; the block that draws the last ticket makes the record, as in the streaming
+// pass 2.  One block over the whole table, both passes, took 11.5 us: 64 entries per lane one after the other; spread over
+// 64 blocks it is latency.
+constexpr uint32_t kTsBlocks = 64, kTsPer = kNumValues16 / kTsBlocks / kFinThreads;   // entries of a lane: 2
+__global__ __launch_bounds__(kFinThreads) void k_stats_from_table(const uint32_t *__restrict__ counts, uint64_t n,
+                                                                  const Part1 *__restrict__ part1, uint32_t nb1,
+                                                                  Part2 *__restrict__ part2, uint32_t nbins,
+                                                                  uint32_t *__restrict__ hist, Ctl *__restrict__ ctl,
+                                                                  qp_stats_t *__restrict__ out)
+{
+    __shared__ uint32_t sh_hist[kMaxBins];
+    __shared__ Part1 sh1[kFinThreads / kWave];
+    __shared__ Part2 sh2[kFinThreads / kWave];
+    __shared__ uint32_t sh_last;
+    const uint32_t tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+    const uint32_t first = (blockIdx.x * kFinThreads + tid) * kTsPer;   // the lane's first pattern
+    static_assert(kTsPer == 2 && kTsBlocks <= kMaxStat2Blocks, "two entries a lane");
+    const uint2 two = reinterpret_cast<const uint2 *>(counts)[first / 2];
+    const uint32_t cnt[kTsPer] = {two.x, two.y};
+    const Part1 tot = reduce_part1_block<kFinThreads>(part1, nb1, sh1);
+    const double mean = tot.sum / (double)n;
+    const float lo = tot.mn;
+    const float range = tot.mx - lo;
+    const float w_inv = (float)((double)(float)nbins / (double)range);
+    const float top = (float)(nbins - 1u);
+    auto bin = [&](uint32_t pattern) {
+        const float tt = (__uint_as_float(pattern << 16) - lo) * w_inv;
+        return (uint32_t)__builtin_amdgcn_fmed3f(tt, 0.0f, top);   // NaN -> 0
+    };
+    // the block's patterns are a run of values: its bins lie between those of its ends (but for NaN patterns)
+    const uint32_t p0 = blockIdx.x * kFinThreads * kTsPer, ba = bin(p0), bb = bin(p0 + kFinThreads * kTsPer - 1u);
+    const uint32_t b0 = min(ba, bb), b1 = max(ba, bb);
+    for (uint32_t b = b0 + tid; b <= b1; b += kFinThreads) sh_hist[b] = 0u;
+    __syncthreads();
+    double dev = 0.0, sq = 0.0;
+#pragma unroll
+    for (uint32_t k = 0; k < kTsPer; ++k) {
+        const uint32_t c = cnt[k], idx = bin(first + k);
+        if (c) {
+            const double d = (double)__uint_as_float((first + k) << 16) - mean, w = (double)c;
+            dev = fma(w, fabs(d), dev);
+            sq = fma(w * d, d, sq);
+        }
+        // small values share a bin, whole waves of them: one increment then
+        const uint32_t idx0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)idx);
+        const bool one = wave_max_u32(idx != idx0 ? 1u : 0u) == 0u;
+        const uint32_t all = one ? wave_sum_u32(c) : 0u;
+        const uint32_t add = one ? (lane == 0 ? all : 0u) : c;
+        if (add) {
+            if (idx >= b0 && idx <= b1) atomicAdd(&sh_hist[idx], add);
+            else atomicAdd(&hist[idx], add);
+        }
+    }
+    dev = wave_sum(dev);
+    sq = wave_sum(sq);
+    if (lane == 0) sh2[wave] = Part2{dev, sq};
+    __syncthreads();   // also: the block's part of the histogram is complete
+    for (uint32_t b = b0 + tid; b <= b1; b += kFinThreads) {
+        const uint32_t c = sh_hist[b];
+        if (c) atomicAdd(&hist[b], c);
+    }
+    if (tid == 0) {
+        Part2 p = sh2[0];
+        for (int k = 1; k < kFinThreads / kWave; ++k) {
+            p.dev += sh2[k].dev;
+            p.sq += sh2[k].sq;
+        }
+        st_dev(&part2[blockIdx.x].dev, p.dev);
+        st_dev(&part2[blockIdx.x].sq, p.sq);
+    }
+    wait_stores();     // this lane's histogram atomics and partial have arrived ...
+    __syncthreads();   // ... and so have those of every lane of the block
+    if (tid == 0) {
+        const uint32_t prev = __hip_atomic_fetch_add(&ctl->ticket_stats, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        sh_last = (prev == gridDim.x - 1u) ? 1u : 0u;
+    }
+    __syncthreads();
+    if (!sh_last) return;
+    finalize_stats_block<true>(part1, nb1, part2, gridDim.x, hist, nbins, n, out);
+    if (tid == 0) ctl->ticket_stats = 0u;
+}
+
+// after launch_value_table with the same nbins
 hipError_t launch_stats_from_table(uint64_t n, uint32_t nbins, void *ws, hipStream_t s)
 {
     char *w = static_cast<char *>(ws);
-    hipLaunchKernelGGL(k_stats_from_table, dim3(1), dim3(kTsThreads), 0, s,
-                       reinterpret_cast<const uint32_t *>(w + kOffValueCounts), n, nbins,
-                       reinterpret_cast<uint32_t *>(w + kOffHist), reinterpret_cast<qp_stats_t *>(w + kOffStats));
+    hipLaunchKernelGGL(k_stats_from_table, dim3(kTsBlocks), dim3(kFinThreads), 0, s,
+                       reinterpret_cast<const uint32_t *>(w + kOffValueCounts), n, reinterpret_cast<const Part1 *>(w + kOffPart1),
+                       value_hist_blocks(n), reinterpret_cast<Part2 *>(w + kOffPart2), nbins, reinterpret_cast<uint32_t *>(w + kOffHist),
+                       reinterpret_cast<Ctl *>(w + kOffCtl), reinterpret_cast<qp_stats_t *>(w + kOffStats));
     return hipGetLastError();
 }
 
