@@ -395,7 +395,7 @@ qp_status qp_compress_async(const void *x_dev, uint64_t n, qp_dtype dtype, uint3
     // through its value table instead, which the statistics build and finalize and the search then reuses.
     // (With the model chosen on the device the record is needed before the search starts: the statistics finalize it.)
     const bool table = uses_value_table(n, dtype);
-    const bool final_record = table || (cfg && cfg->dist == QP_DIST_AUTO);
+    const bool final_record = searches_value_table(n, dtype, make_plan(bits, cfg)) || table || (cfg && cfg->dist == QP_DIST_AUTO);
     st = hip_status(launch_stats(x_dev, n, dtype, nbins, ws_dev, static_cast<hipStream_t>(stream), final_record));
     if (st != QP_OK) return st;
     st = search_common(x_dev, n, dtype, nullptr, bits, cfg, ws_dev, ws_bytes, stream, final_record ? 0u : nbins, table);

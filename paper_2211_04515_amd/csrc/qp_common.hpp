@@ -23,6 +23,12 @@ constexpr uint32_t kNumValues16 = 65536;   // bit patterns of a bfloat16
 #define QP_VALUE_TABLE_MIN_N (1ull << 20)
 #endif
 constexpr uint64_t kValueTableMinN = QP_VALUE_TABLE_MIN_N;
+// Below that, a full sweep of a bf16 tensor still goes through a table of its own once it has this many element-candidate
+// pairs (0.6 M elements with 101 candidates): the one-candidate-per-lane search grows with the pairs, counting hardly.
+// Sender path with 101 candidates, without / with the table: 0.35 M elements 32.0 / 34.2 us, 0.52 M 32.9 / 32.5, 0.7 M
+// 37.5 / 34.1, 1 M 42.3 / 33.7.  The statistics stay with their two streaming passes there (without a search those are the
+// faster: 1 M elements 19.5 / 24.2 us), so that they do not depend on what follows.
+constexpr uint64_t kValueTableMinPairs = 60000000ull;
 // Tensors at least this large take the forms of quantize+pack (3 and 6 bit) and unpack+dequantize that pay on
 // large tensors only (measured break-even between 9.7 M and 77 M elements).
 #ifndef QP_LARGE_FORMS_MIN_N
@@ -719,6 +725,8 @@ hipError_t launch_search(const void *x, uint64_t n, int dtype, const SearchPlan 
 // Large bf16 tensors: the table of value counts (zeroed and built in one pass over the tensor) and the
 // statistics record and histogram computed from it.
 bool uses_value_table(uint64_t n, int dtype);
+// Whether the search of such a tensor runs on its value table.
+bool searches_value_table(uint64_t n, int dtype, const SearchPlan &plan);
 // (nbins != 0: launch_stats_from_table will follow; the histogram is cleared)
 hipError_t launch_value_table(const void *x, uint64_t n, uint32_t nbins, void *ws, hipStream_t s);
 hipError_t launch_stats_from_table(uint64_t n, uint32_t nbins, void *ws, hipStream_t s);

@@ -612,7 +612,7 @@ hipError_t launch_search(const void *x, uint64_t n, int dtype, const SearchPlan 
     }
     // A bf16 tensor has at most 65536 distinct values: above a modest size it is cheaper to count them once
     // (one pass over the tensor) and run the candidates over the value table.
-    if (uses_value_table(n, dtype)) {
+    if (searches_value_table(n, dtype, plan)) {
         if (plan.stride > 1u || finalize_nbins) return hipErrorInvalidValue;   // refused / the table path finalizes itself
         if (!value_table_ready) {
             const hipError_t e = launch_value_table(x, n, 0u, ws, s);

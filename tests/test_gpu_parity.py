@@ -952,6 +952,38 @@ def test_sender_and_receiver_on_random_sizes(qp):
         assert np.array_equal(y.cpu().numpy(), orc.dequantize(orc.quantize(as_f32(x), oq), oq)), case
 
 
+# one block per compute unit and two (2^20 elements), the last and first slices with a group more; bf16 sweeps on the tile
+# search and on a table of their own (6e7 pairs: 594,060 elements with 101 candidates, fewer with more), and the whole
+# counting kernel's smallest chunk counts with partials of their own
+@pytest.mark.parametrize("kind,n,t", [("fp32", (1 << 20) - 1, 100), ("fp32", (1 << 20) + 1, 100), ("fp32", 4 * 5 * 205 + 3, 100),
+                                      ("fp32", 70_001, 10), ("bf16", 594_059, 100), ("bf16", 594_060, 100),
+                                      ("bf16", 480_001, 127), ("bf16", 1_048_576, 100), ("bf16", 1_048_575, 7)])
+def test_search_routes_and_tile_remainders(qp, kind, n, t):
+    """Scores and winner against the oracle on either side of the search's size rules, the fused path equal to the calls one
+    by one, and the winner's record copied to a pointer of any alignment."""
+    x = si.make_config("C2" if kind == "fp32" else "C5", n=n)
+    xf, xd = as_f32(x), to_dev(x)
+    cfg = qp.qp_default_search_cfg()
+    cfg.t_steps = t
+    ws, ws2 = qp.alloc_workspace(n, cfg), qp.alloc_workspace(n, cfg)
+    st = qp.qp_stats(xd, ws)
+    res, q = qp.qp_dsaciq_search(xd, st, 3, ws, cfg=cfg)
+    off = qp.qp_ws_offset(qp.QP_WS_SCORES)
+    scores = ws[off:off + 8 * (t + 1)].cpu().numpy().view(np.float64)
+    for j in (0, t // 2, t):
+        oqj = orc.make_qparams(st.mean, orc.laplace_F(3) * (st.mad + j * ((st.b_r - st.mad) / t)), 3, n)
+        assert scores[j] == pytest.approx(pairwise_sq_error(xf, oqj), rel=REL_SCORE_PAIRWISE)
+    assert res.j_star == int(np.argmin(scores)) and res.mse_star == pytest.approx(scores.min() / n, rel=1e-15)
+    packed, p2 = qp.alloc_packed(n, 3), qp.alloc_packed(n, 3)
+    rec = torch.zeros(48, dtype=torch.uint8, device="cuda")
+    qp.qp_compress_async(xd, 3, ws2, packed, rec.data_ptr() + 5, cfg=cfg)
+    qp.qp_quant_pack(xd, q, p2)
+    assert torch.equal(packed, p2)
+    raw = rec.cpu().numpy().tobytes()
+    assert raw[5:37] == bytes(q) and raw[:5] == bytes(5) and raw[37:] == bytes(11)
+    assert bytes(qp.read_ws(ws2, qp.QP_WS_RESULT, qp.qp_search_result_t)) == bytes(res)
+
+
 def test_sender_path_other_grids(qp):
     x = si.make_config("C2", n=200_003)
     xd = to_dev(x)
