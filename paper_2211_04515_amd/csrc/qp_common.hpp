@@ -17,8 +17,8 @@ constexpr uint32_t kMaxStat1Blocks = 512;  // most blocks of statistics pass 1 (
 constexpr uint32_t kMaxStat2Blocks = 256;  // most blocks of pass 2 (512 lanes each): one per CU measured best
 constexpr uint32_t kMaxSearchBlocks = 1024;
 constexpr uint32_t kNumValues16 = 65536;   // bit patterns of a bfloat16
-// bf16 tensors at least this large go through their value table (counting the values and working on
-// 65536 of them costs about 30 us; the per-element kernels pass that at about a million elements)
+// bf16 tensors at least this large go through their value table in the statistics too (counting the values and working on
+// 65536 of them costs about 25 us with the search; one image's worth of statistics alone is cheaper in two passes)
 #ifndef QP_VALUE_TABLE_MIN_N
 #define QP_VALUE_TABLE_MIN_N (1ull << 20)
 #endif
