@@ -280,8 +280,10 @@ qp_status qp_unpack_dequant_dev(const void *packed_dev, size_t packed_bytes, uin
 
 /* ---- whole sender side without a host round trip ------------------------------
  * stats -> directed search -> quantize + pack, all on `stream`, nothing copied to the
- * host.  If qparams_out_dev is not NULL the winner's record is also copied there
- * (device to device) so that it can travel with the payload.  The statistics, the
+ * host.  If qparams_out_dev is not NULL the winner's record also goes there, so that it can
+ * travel with the payload: the pack kernel stores it if that is memory of the stream's device,
+ * apart from x_dev, packed_dev and the workspace's record, and otherwise a copy command behind
+ * the kernel does (any alignment; a few microseconds more).  The statistics, the
  * search result and the scores are left in the workspace regions as by the separate
  * calls; nothing is reported about NaN / Inf elements here (QP_WS_STATS holds their
  * count; such elements are packed as code 0).

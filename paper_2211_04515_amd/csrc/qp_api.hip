@@ -365,6 +365,35 @@ qp_status qp_unpack_dequant_dev(const void *packed_dev, size_t packed_bytes, uin
     return unpack_common(packed_dev, packed_bytes, bits, nullptr, qparams_dev, y_dev, n, stream);
 }
 
+static bool overlap(const void *a, uint64_t a_bytes, const void *b, uint64_t b_bytes)
+{
+    const uintptr_t p = reinterpret_cast<uintptr_t>(a), q = reinterpret_cast<uintptr_t>(b);
+    return p < q + b_bytes && q < p + a_bytes;
+}
+
+// Whether the pack kernel may write the record to `out` itself.  Its other blocks run at the same time, so `out` must be
+// apart from all that they read and write; and a kernel's store, unlike a copy command, needs memory of the stream's own
+// device, all 32 bytes of it.  Everything else (pinned, pageable or managed host memory, another device's, an address that the
+// runtime does not know) is left to a copy command behind the kernel, which handles or refuses it.
+static bool kernel_may_store(qp_qparams_t *out, const void *x_dev, uint64_t x_bytes, const void *packed_dev, uint64_t packed_bytes,
+                             const qp_qparams_t *record, hipStream_t s)
+{
+    if (overlap(out, sizeof *out, x_dev, x_bytes) || overlap(out, sizeof *out, packed_dev, packed_bytes) ||
+        overlap(out, sizeof *out, record, sizeof *record))
+        return false;
+    int dev = -1;
+    hipPointerAttribute_t attr{};
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipStreamGetDevice(s, &dev) != hipSuccess || hipPointerGetAttributes(&attr, out) != hipSuccess ||
+        hipMemGetAddressRange(&base, &size, reinterpret_cast<hipDeviceptr_t>(out)) != hipSuccess) {
+        (void)hipGetLastError();   // the question is not an error of the caller's
+        return false;
+    }
+    const uint64_t at = reinterpret_cast<uintptr_t>(out) - reinterpret_cast<uintptr_t>(base);
+    return attr.type == hipMemoryTypeDevice && attr.device == dev && at <= size && size - at >= sizeof *out;
+}
+
 // Everything qp_compress_async refuses, before anything is launched.
 static qp_status check_compress(const void *x_dev, uint64_t n, qp_dtype dtype, uint32_t bits, const qp_search_cfg_t *cfg,
                                 void *ws_dev, size_t ws_bytes, void *packed_dev, size_t packed_bytes)
@@ -400,7 +429,12 @@ qp_status qp_compress_async(const void *x_dev, uint64_t n, qp_dtype dtype, uint3
     st = search_common(x_dev, n, dtype, nullptr, bits, cfg, ws_dev, ws_bytes, stream, final_record ? 0u : nbins, table);
     if (st != QP_OK) return st;
     const qp_qparams_t *qdev = reinterpret_cast<const qp_qparams_t *>(static_cast<char *>(ws_dev) + kOffQParams);
-    return pack_common(x_dev, n, dtype, bits, nullptr, qdev, packed_dev, packed_bytes, stream, qparams_out_dev);
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    const bool store = qparams_out_dev && kernel_may_store(qparams_out_dev, x_dev, n * (dtype == QP_BF16 ? 2u : 4u), packed_dev,
+                                                           qp_packed_bytes(n, bits), qdev, s);
+    st = pack_common(x_dev, n, dtype, bits, nullptr, qdev, packed_dev, packed_bytes, stream, store ? qparams_out_dev : nullptr);
+    if (st != QP_OK || !qparams_out_dev || store) return st;
+    return hip_status(hipMemcpyAsync(qparams_out_dev, qdev, sizeof(qp_qparams_t), hipMemcpyDeviceToDevice, s));
 }
 
 qp_status qp_compress_many_async(const qp_job_t *jobs, uint32_t count, const qp_search_cfg_t *cfg, const qp_lane_t *lanes,

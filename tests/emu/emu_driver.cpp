@@ -3,6 +3,8 @@
 //   emu_driver <in.bin> <n> <dtype 0|1> <bits> <t_steps> <dist> <flags> <stride> <nbins> <cus> <outdir> [cands_per_round]
 #include <hip/hip_runtime.h>
 
+#include <sys/mman.h>
+
 #include <string>
 #include <vector>
 
@@ -20,9 +22,18 @@ static void dump(const std::string &dir, const char *name, const void *p, size_t
 static bool g_shared = false;             // blocks run as processes: "device memory" must be shared between them
 static void *alloc_exact(size_t bytes)   // 16-byte aligned; the sanitizer sees any overrun past `bytes` (rounded to 16)
 {
-    if (g_shared) return emu::shared_alloc(bytes);   // ends at an inaccessible page instead
-    void *p = aligned_alloc(16, (bytes + 15) / 16 * 16);
+    void *p = g_shared ? emu::shared_alloc(bytes)   // ends at an inaccessible page instead
+                       : aligned_alloc(16, (bytes + 15) / 16 * 16);
     if (!p) exit(3);
+    emu::know(p, bytes, hipMemoryTypeDevice, 0, false);
+    return p;
+}
+// Memory that no kernel of this device reaches: the host's, or another device's without peer access.
+static void *alloc_unreachable(size_t bytes, hipMemoryType type, int device)
+{
+    void *p = mmap(nullptr, (bytes + 4095) / 4096 * 4096, PROT_READ | PROT_WRITE, MAP_SHARED | MAP_ANONYMOUS, -1, 0);
+    if (p == MAP_FAILED) exit(3);
+    emu::know(p, bytes, type, device, true);
     return p;
 }
 static void release(void *p)
@@ -75,13 +86,29 @@ int main(int argc, char **argv)
     if (rc_search == QP_OK) {
         rc_pack = qp_quant_pack(x, n, dtype, &q, packed, pkb, nullptr);
         rc_unpack = qp_unpack_dequant(packed, pkb, &q, y, n, nullptr);
-        qp_qparams_t &qout = *(qp_qparams_t *)alloc_exact(sizeof(qp_qparams_t));
-        rc_compress = qp_compress_async(x, n, dtype, bits, &cfg, ws2, wsb, packed2, pkb, &qout, nullptr);
+        // where the fused path's record goes: memory of its own, the last bytes of the input or of the payload, where the
+        // search leaves it anyway, memory that kernels do not reach, or an allocation too short for it
+        const char *env = getenv("EMU_RECORD");
+        const std::string where = env ? env : "own";
+        qp_qparams_t qread;
+        char *qout;   // (any alignment)
+        if (where == "in_x") qout = (char *)x + (n * esz - sizeof q);
+        else if (where == "in_packed") qout = (char *)packed2 + (pkb - sizeof q);
+        else if (where == "on_itself") qout = (char *)ws2 + qp_ws_offset(QP_WS_QPARAMS);
+        else if (where == "host") qout = (char *)alloc_unreachable(sizeof q, hipMemoryTypeHost, 0);
+        else if (where == "peer") qout = (char *)alloc_unreachable(sizeof q, hipMemoryTypeDevice, 1);
+        else if (where == "short") qout = (char *)alloc_exact(sizeof q - 8);
+        else qout = (char *)alloc_exact(sizeof q);
+        rc_compress = qp_compress_async(x, n, dtype, bits, &cfg, ws2, wsb, packed2, pkb, (qp_qparams_t *)qout, nullptr);
         if (rc_compress == QP_OK) {
+            const emu::Allocation *m = emu::find(qout);
+            if (m->unreachable) mprotect(m->base, 4096, PROT_READ);
+            memcpy(&qread, qout, sizeof q);
+            if (where == "in_packed") memcpy(qout, (char *)packed + (pkb - sizeof q), sizeof q);   // the codes it replaced
             const char *a = (const char *)ws, *b = (const char *)ws2;
             same = memcmp(a + qp_ws_offset(QP_WS_STATS), b + qp_ws_offset(QP_WS_STATS), sizeof(qp_stats_t)) == 0 &&
                    memcmp(a + qp_ws_offset(QP_WS_QPARAMS), b + qp_ws_offset(QP_WS_QPARAMS), sizeof(qp_qparams_t)) == 0 &&
-                   memcmp(&qout, &q, sizeof q) == 0 && memcmp(packed, packed2, pkb) == 0;
+                   memcmp(&qread, &q, sizeof q) == 0 && memcmp(packed, packed2, pkb) == 0;
         }
     }
     dump(out, "stats.bin", &st, sizeof st);

@@ -73,6 +73,34 @@ void *shared_alloc(size_t bytes)
     return base + body - (bytes + 15) / 16 * 16;
 }
 
+static std::vector<Allocation> g_known;
+
+void know(void *base, size_t bytes, hipMemoryType type, int device, bool unreachable)
+{
+    g_known.push_back(Allocation{(char *)base, bytes, hipPointerAttribute_t{type, device}, unreachable});
+    if (unreachable && mprotect(base, (bytes + 4095) / 4096 * 4096, PROT_NONE) != 0) { perror("mprotect"); exit(3); }
+}
+
+const Allocation *find(const void *p)
+{
+    for (const Allocation &m : g_known)
+        if ((const char *)p >= m.base && (const char *)p < m.base + m.bytes) return &m;
+    return nullptr;
+}
+
+// As the runtime's copies: any two memories, and nothing past the end of an allocation that it knows.
+hipError_t copy(void *d, const void *s, size_t n)
+{
+    const Allocation *to = find(d), *from = find(s);
+    if ((to && (char *)d + n > to->base + to->bytes) || (from && (const char *)s + n > from->base + from->bytes)) return hipErrorInvalidValue;
+    const bool open = to && to->unreachable;
+    const size_t pages = open ? (to->bytes + 4095) / 4096 * 4096 : 0;
+    if (open && mprotect(to->base, pages, PROT_READ | PROT_WRITE) != 0) { perror("mprotect"); exit(3); }
+    memcpy(d, s, n);
+    if (open && mprotect(to->base, pages, PROT_NONE) != 0) { perror("mprotect"); exit(3); }
+    return hipSuccess;
+}
+
 void launch(dim3 grid, dim3 block, const std::function<void()> &fn)
 {
     g_blockDim = block;

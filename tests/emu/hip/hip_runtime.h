@@ -41,6 +41,9 @@ static inline uint2 make_uint2(uint32_t a, uint32_t b) { return uint2{a, b}; }
 
 typedef void *hipStream_t;
 enum hipError_t { hipSuccess = 0, hipErrorInvalidValue = 1 };
+enum hipMemoryType { hipMemoryTypeHost = 1, hipMemoryTypeDevice = 2 };
+struct hipPointerAttribute_t { hipMemoryType type; int device; };
+typedef void *hipDeviceptr_t;
 enum { hipMemcpyDeviceToHost = 2, hipMemcpyDeviceToDevice = 3, hipDeviceAttributeMultiprocessorCount = 63 };
 #ifndef __HIP_MEMORY_SCOPE_AGENT
 #define __HIP_MEMORY_SCOPE_AGENT 4
@@ -60,6 +63,11 @@ extern BlockCtx *g_ctx;
 extern thread_local unsigned t_opcount;
 void launch(dim3 grid, dim3 block, const std::function<void()> &fn);
 void *shared_alloc(size_t bytes);   // "device memory" that the per-block processes of the concurrent mode share
+// What the runtime knows of an allocation.  `unreachable` (whole pages): no kernel may touch it, only copies do.
+struct Allocation { char *base; size_t bytes; hipPointerAttribute_t attr; bool unreachable; };
+void know(void *base, size_t bytes, hipMemoryType type, int device, bool unreachable);
+const Allocation *find(const void *p);
+hipError_t copy(void *d, const void *s, size_t n);
 uint32_t exchange(uint32_t v, int src_lane_or_minus1, int ctrl, int xor_mask);
 }  // namespace emu
 
@@ -73,7 +81,23 @@ uint32_t exchange(uint32_t v, int src_lane_or_minus1, int ctrl, int xor_mask);
 
 static inline hipError_t hipGetLastError() { return hipSuccess; }
 static inline hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
-static inline hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, int, hipStream_t) { memcpy(d, s, n); return hipSuccess; }
+static inline hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, int, hipStream_t) { return emu::copy(d, s, n); }
+static inline hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *p)
+{
+    const emu::Allocation *m = emu::find(p);
+    if (!m) return hipErrorInvalidValue;
+    *a = m->attr;
+    return hipSuccess;
+}
+static inline hipError_t hipMemGetAddressRange(hipDeviceptr_t *base, size_t *size, hipDeviceptr_t p)
+{
+    const emu::Allocation *m = emu::find(p);
+    if (!m) return hipErrorInvalidValue;
+    *base = m->base;
+    *size = m->bytes;
+    return hipSuccess;
+}
+static inline hipError_t hipStreamGetDevice(hipStream_t, int *d) { *d = 0; return hipSuccess; }
 #define HIP_SYMBOL(x) x
 template <typename T> static inline hipError_t hipGetSymbolAddress(void **p, const T &sym) { *p = (void *)&sym; return hipSuccess; }
 static inline hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }

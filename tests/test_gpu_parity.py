@@ -984,6 +984,47 @@ def test_search_routes_and_tile_remainders(qp, kind, n, t):
     assert bytes(qp.read_ws(ws2, qp.QP_WS_RESULT, qp.qp_search_result_t)) == bytes(res)
 
 
+def test_sender_record_in_pinned_memory_or_inside_the_input(qp):
+    """The winner's record reaches a pinned host buffer, and the end of the input's own buffer without disturbing the codes
+    of the elements that it replaces: eager, and replayed from a graph with eager work between the replays."""
+    n = 1_234_567
+    x1, x2 = to_dev(si.make_config("C3", n=n)), to_dev(si.make_config("C2", n=n))
+    ws = qp.alloc_workspace(n)
+    rec = torch.zeros(32, dtype=torch.uint8, device="cuda")
+    want = []
+    for x in (x1, x2):
+        packed = qp.alloc_packed(n, 3)
+        qp.qp_compress_async(x, 3, ws, packed, rec.data_ptr())
+        want.append((packed, rec.clone()))
+    xin, p2 = torch.empty_like(x1), qp.alloc_packed(n, 3)
+    pinned = torch.zeros(32, dtype=torch.uint8, pin_memory=True)
+    tail = xin.view(torch.uint8)[-32:]
+    for where, out in (("pinned", pinned), ("input", tail)):
+        print(f"[case] record in {where}", flush=True)
+
+        def call():
+            qp.qp_compress_async(xin, 3, ws, p2, out.data_ptr())
+
+        def check(k):
+            torch.cuda.synchronize()
+            assert torch.equal(p2, want[k][0]) and torch.equal(out.cpu(), want[k][1].cpu()), (where, k)
+
+        for k, x in enumerate((x1, x2)):
+            xin.copy_(x)
+            call()
+            check(k)
+        s, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(g, stream=s):
+            call()
+        for k in (0, 1, 0):
+            xin.copy_(x1 if k == 0 else x2)
+            p2.zero_()
+            torch.cuda.synchronize()
+            g.replay()
+            check(k)
+
+
 def test_sender_path_other_grids(qp):
     x = si.make_config("C2", n=200_003)
     xd = to_dev(x)

@@ -53,11 +53,14 @@ def drivers():
     return out
 
 
-def start_driver(exe, out_dir, x, bits, t=100, dist=0, flags=0, stride=0, nbins=2048, cus=4, cpr=None, concurrent=0, seed=1):
+def start_driver(exe, out_dir, x, bits, t=100, dist=0, flags=0, stride=0, nbins=2048, cus=4, cpr=None, concurrent=0, seed=1,
+                 record=None):
     os.makedirs(out_dir, exist_ok=True)
     inp = os.path.join(out_dir, "in.bin")
     x.tofile(inp)
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:abort_on_error=0", UBSAN_OPTIONS="print_stacktrace=1")
+    if record:
+        env["EMU_RECORD"] = record
     if concurrent:
         env.update(EMU_CONCURRENT_BLOCKS=str(concurrent), EMU_SEED=str(seed))
     return subprocess.run([exe, inp, str(x.size), "1" if x.dtype == np.uint16 else "0", str(bits), str(t), str(dist),
@@ -158,8 +161,13 @@ STREAM_C2F_CASES = [("streaming_c2f", ("C3", 10_011, 2, dict(stride=10), 100)),
                     ("streaming_c2f", ("C3", 10_011, 4, dict(stride=10, conc=3, seed=3, cpr=4), 100)),
                     ("streaming_c2f", ("C2", 8_193, 3, dict(stride=5, clip=True, conc=2, seed=4), 40)),
                     ("streaming_c2f", ("C3", 6_007, 4, dict(stride=64, conc=4, seed=5), 100))]
+# Where the fused path's record goes.  The pack kernel writes it only where it may: not over what its other blocks still
+# read or write (the input, the payload, the record itself), and not to memory that only a copy of the runtime reaches.
+RECORD_CASES = [("default", ("C3", 9_001, 4, dict(record=r), 3)) for r in ("in_x", "in_packed", "on_itself", "host", "peer")]
+RECORD_CASES += [("default", ("bf16", 9_001, 3, dict(record="in_x", conc=2, seed=s), 3)) for s in (1, 2)]
+RECORD_REFUSED = ("default", ("C3", 3_001, 4, dict(record="short"), 3))
 ALL_CASES = ([("default", c) for c in TILE_CASES] + [("streaming", c) for c in STREAM_CASES] + [("streaming", REFUSED)] + ACIQ_ONLY
-             + CONCURRENT_CASES + STREAM_C2F_CASES)
+             + CONCURRENT_CASES + STREAM_C2F_CASES + RECORD_CASES + [RECORD_REFUSED])
 
 
 def case_id(tag, c):
@@ -179,14 +187,14 @@ def runs(drivers, tmp_path_factory):
         out_dir = os.path.join(base, case_id(tag, item[1]))
         p = start_driver(drivers[tag], out_dir, x, bits, t=t, dist=v.get("dist", 0), flags=flags,
                          stride=v.get("stride", 0) if flags & 2 else 0, cus=4 if tag == "default" else 2, cpr=v.get("cpr"),
-                         concurrent=v.get("conc", 0), seed=v.get("seed", 1))
+                         concurrent=v.get("conc", 0), seed=v.get("seed", 1), record=v.get("record"))
         return case_id(tag, item[1]), (p, out_dir, x)
 
     with ThreadPoolExecutor(max_workers=6) as ex:
         return dict(ex.map(go, ALL_CASES))
 
 
-WHOLE = [a for a in ALL_CASES if a[1] is not REFUSED and a not in ACIQ_ONLY]
+WHOLE = [a for a in ALL_CASES if a[1] is not REFUSED and a not in ACIQ_ONLY and a is not RECORD_REFUSED]
 
 
 @pytest.mark.parametrize("tag,case", WHOLE, ids=[case_id(*a) for a in WHOLE])
@@ -205,6 +213,13 @@ def test_emulation_refuses_what_the_library_refuses(runs):
     p, out_dir, x = runs[case_id("streaming", REFUSED)]
     r = read_outputs(p, out_dir)
     assert r["rc"][0] == 0 and r["rc"][1] == -1
+
+
+def test_a_record_that_does_not_fit_its_allocation_is_an_error(runs):
+    """The runtime's copy refuses it (QP_EHIP): nothing is written past the end."""
+    p, out_dir, x = runs[case_id(*RECORD_REFUSED)]
+    r = read_outputs(p, out_dir)
+    assert r["rc"][:5] == [0, 0, 0, 0, -3]
 
 
 @pytest.mark.parametrize("tag,case", ACIQ_ONLY, ids=[case_id(*a) for a in ACIQ_ONLY])
