@@ -126,12 +126,13 @@ template <int DT> __global__ __launch_bounds__(kStThreads) void k_search_tile(Ti
                     const double de = (double)err;
                     acc = fma(de, de, acc);   // de*de is exact in fp64
                 };
-                // Eight groups of four per step (of the short sequence), two running sums: the LDS reads are issued before
+                // Eight groups of four per step (four of the full sequence), two running sums: the LDS reads are issued before
                 // the arithmetic, which only two to four waves per SIMD are there to hide, and the fp64 chains interleave.
                 // The trip count is the same for all lanes, so the loop is scalar work (with a range of groups per
                 // slice it was 6 of 70 vector instructions).  Sender path of 1 M fp32 elements, per step 2 (ranges) / 2 / 4 /
-                // 8 groups: 44.0 / 44.3 / 42.2 / 41.8 us.
-                constexpr uint32_t U = SHORT ? 8u : 1u;
+                // 8 groups: 44.0 / 44.3 / 42.2 / 41.8 us.  Full sequence (values so small that the grid's reciprocal is
+                // infinite), search of 0.7 M elements, per step 2 (ranges) / 1 / 2 / 4 groups: 30.9 / 35.7 / 31.5 / 30.2 us.
+                constexpr uint32_t U = SHORT ? 8u : 4u;
                 uint32_t i = 0;
 #pragma unroll 1
                 for (; i + U <= trips; i += U) {

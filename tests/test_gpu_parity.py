@@ -354,6 +354,25 @@ def test_search_degenerate_inputs(qp, name):
     assert (q.lo, q.hi, q.scale, q.inv_scale) == (oq.lo, oq.hi, oq.scale, oq.inv_scale)
 
 
+# values so small that the grid's reciprocal is infinite: the tile search's full clamp sequence, several of its steps with a
+# remainder and a ragged end, one step less than a slice needs, and many slices
+@pytest.mark.parametrize("n,t", [(4 * 5 * 205 + 3, 100), (70_001, 100), (70_001, 10), (513, 100), ((1 << 20) + 1, 3)])
+def test_tile_search_full_clamp_sequence(qp, n, t):
+    x = (np.random.default_rng(n + t).laplace(0.0, 1.0, size=n) * 1e-41).astype(np.float32)
+    xd = to_dev(x)
+    cfg = qp.qp_default_search_cfg()
+    cfg.t_steps = t
+    ws = qp.alloc_workspace(n, cfg)
+    st = qp.qp_stats(xd, ws)
+    res, q = qp.qp_dsaciq_search(xd, st, 4, ws, cfg=cfg)
+    assert np.isinf(q.inv_scale)
+    ores, oq, oscores = orc.dsaciq_search(x, oracle_stats_from(st), 4, t)
+    off = qp.qp_ws_offset(qp.QP_WS_SCORES)
+    scores = ws[off:off + 8 * (t + 1)].cpu().numpy().view(np.float64)
+    assert np.allclose(scores, oscores, rtol=REL_SCORE, atol=0.0, equal_nan=True)
+    assert res.j_star == ores.j_star
+
+
 def test_search_is_bit_reproducible(qp):
     x = si.make_config("C2", n=1_000_003)
     xd = to_dev(x)

@@ -121,6 +121,8 @@ def small_input(kind, n):
         return (np.random.default_rng(n).standard_normal(n) * 0.8 + 0.3).astype(np.float32)
     if kind == "gauss_bf16":
         return si.f32_to_bf16_bits((np.random.default_rng(n).standard_normal(n) * 0.8 + 0.3).astype(np.float32))
+    if kind == "subnormal":   # the grid's reciprocal is infinite: the search's full clamp sequence
+        return (np.random.default_rng(n).laplace(0.0, 1.0, size=n) * 1e-41).astype(np.float32)
     return si.make_config(kind, n=n)
 
 
@@ -129,6 +131,7 @@ def small_input(kind, n):
 TILE_CASES = [("C1", 3_011, 2, {}, 100), ("C3", 4_999, 3, {}, 12), ("bf16", 5_345, 4, {}, 12), ("C2", 4_097, 16, {}, 7),
               ("C3", 130, 6, {}, 12), ("C3", 3_001, 4, dict(clip=True), 12), ("C2", 2_191, 2, dict(dist=1, stride=4), 20),
               ("bf16", 2_777, 8, dict(stride=3, clip=True), 12), ("C1", 5, 4, {}, 5), ("C3", 1, 8, {}, 3),
+              ("subnormal", 3_003, 4, {}, 12),
               # the model chosen per tensor by fit (Gaussian data must take the Gaussian model, Laplace-like data the paper's)
               ("gauss", 4_001, 4, dict(dist=2), 12), ("C1", 3_011, 3, dict(dist=2, clip=True), 12), ("gauss", 2_500, 2, dict(dist=2, stride=4), 20)]
 # the same kind of tensors through the kernels large tensors take (thresholds lowered at build time)
