@@ -29,7 +29,7 @@ constexpr int kStThreads = kFinThreads;          // 512: finalize_stats_block fi
 constexpr uint32_t kStVecs = 2;                  // 4-element vectors a lane stages per sub-tile
 constexpr uint32_t kStSub = kStThreads * kStVecs * 4;   // 4096 elements per sub-tile (16 KB of LDS)
 constexpr uint32_t kStMaxCands = 256;            // every candidate gets a lane (or several)
-constexpr uint32_t kStMaxBlocks = 256;              // one block per compute unit: no unit gets two while others idle
+constexpr uint32_t kStUnits = 256;               // compute units: a grid has at most one or two blocks for each
 
 struct TileSearchArgs {
     const void *x;
@@ -221,19 +221,24 @@ bool tile_search_eligible(uint64_t n, const SearchPlan &plan)
     return n <= kTileSearchMaxN && tile_search_can_run(plan);
 }
 
-static uint64_t tile_share(uint64_t n)
+static uint64_t tile_share(uint64_t n, uint32_t count)
 {
-    // Shares of whole 128-element groups, at least 512 elements.  The grid is a whole number of blocks per
-    // compute unit (no unit gets one more than another): one while its share is one sub-tile, else two, whose staging
-    // and scoring then overlap (sender path, one / two blocks: 1 M elements 42.2 / 42.7 us, 1.23 M 48.8 / 47.5 us; 2 M
-    // search 62 / 57 us; coarse-to-fine on 9.7 M 103 / 90 us).
-    const uint64_t blocks = (uint64_t)kStMaxBlocks * (n > (uint64_t)kStMaxBlocks * kStSub ? 2 : 1);
+    // Shares of whole 128-element groups, at least 512 elements, for at most one block per compute unit while its share is one
+    // sub-tile, else at most two, whose staging and scoring then overlap (sender path, one / two blocks: 1 M elements 42.2 /
+    // 42.7 us, 1.23 M 48.8 / 47.5 us; 2 M search 62 / 57 us; coarse-to-fine on 9.7 M 103 / 90 us).  Lists of fewer than 10
+    // candidates have too little scoring to pay for the second block's set-up until there are three sub-tiles for two units
+    // (search, one / two: 4 candidates 1.05 M 11.2 / 11.8, 1.5 M 11.6 / 11.8; 9 candidates 11.5 / 12.0, 12.2 / 12.4; 11 candidates
+    // 12.0 / 12.1, 12.8 / 12.5).
+    const uint64_t per_unit = (uint64_t)kStUnits * kStSub;
+    const uint64_t two_above = count < 10u ? per_unit + per_unit / 2 - 1 : per_unit;
+    const uint64_t blocks = (uint64_t)kStUnits * (n > two_above ? 2 : 1);
     uint64_t share = (n + blocks - 1) / blocks;
     share = (share + 127) / 128 * 128;
     return share < 512 ? 512 : share;
 }
 
-uint32_t tile_search_blocks(uint64_t n) { return ceil_div_u64(n, tile_share(n)); }
+// the most blocks of a sweep, whatever its list
+uint32_t tile_search_blocks(uint64_t n) { return ceil_div_u64(n, tile_share(n, kStMaxCands)); }
 
 static hipError_t launch_tile_sweep(const void *x, uint64_t n, int dtype, const SearchPlan &plan, const qp_stats_t *st,
                                     uint32_t finalize_nbins, uint32_t list_mode, uint32_t count, void *ws, hipStream_t s)
@@ -242,7 +247,7 @@ static hipError_t launch_tile_sweep(const void *x, uint64_t n, int dtype, const 
     TileSearchArgs a;
     a.x = x;
     a.n = n;
-    a.share = tile_share(n);
+    a.share = tile_share(n, count);
     a.m = model_args(plan, st, list_mode, count, ws);
     a.fin = FinalizeArgs{reinterpret_cast<const Part1 *>(w + kOffPart1), reinterpret_cast<const Part2 *>(w + kOffPart2),
                          reinterpret_cast<const uint32_t *>(w + kOffHist), 0u, 0u, finalize_nbins};

@@ -976,7 +976,10 @@ def test_sender_and_receiver_on_random_sizes(qp):
 # counting kernel's smallest chunk counts with partials of their own
 @pytest.mark.parametrize("kind,n,t", [("fp32", (1 << 20) - 1, 100), ("fp32", (1 << 20) + 1, 100), ("fp32", 4 * 5 * 205 + 3, 100),
                                       ("fp32", 70_001, 10), ("bf16", 594_059, 100), ("bf16", 594_060, 100),
-                                      ("bf16", 480_001, 127), ("bf16", 1_048_576, 100), ("bf16", 1_048_575, 7)])
+                                      ("bf16", 480_001, 127), ("bf16", 1_048_576, 100), ("bf16", 1_048_575, 7),
+                                      # lists of fewer than 10 candidates: one block per unit up to 3 2^19 elements
+                                      ("fp32", (1 << 20) + 1, 8), ("fp32", (1 << 20) + 1, 9), ("fp32", (3 << 19) - 1, 8),
+                                      ("fp32", 3 << 19, 8)])
 def test_search_routes_and_tile_remainders(qp, kind, n, t):
     """Scores and winner against the oracle on either side of the search's size rules, the fused path equal to the calls one
     by one, and the winner's record copied to a pointer of any alignment."""
