@@ -24,11 +24,23 @@ constexpr uint32_t kNumValues16 = 65536;   // bit patterns of a bfloat16
 #endif
 constexpr uint64_t kValueTableMinN = QP_VALUE_TABLE_MIN_N;
 // Below that, a full sweep of a bf16 tensor still goes through a table of its own once it has this many element-candidate
-// pairs (0.6 M elements with 101 candidates): the one-candidate-per-lane search grows with the pairs, counting hardly.
-// Sender path with 101 candidates, without / with the table: 0.35 M elements 32.0 / 34.2 us, 0.52 M 32.9 / 32.5, 0.7 M
-// 37.5 / 34.1, 1 M 42.3 / 33.7.  The statistics stay with their two streaming passes there (without a search those are the
+// pairs (0.6 M elements with 101 candidates): the searches over the tensor grow with the pairs, counting hardly and the search
+// over the table with the candidates only.  Sender path with 101 candidates, without / with the table: 0.35 M elements
+// 32.0 / 34.2 us, 0.52 M 32.9 / 32.5, 0.7 M 37.5 / 34.1, 1 M 42.3 / 33.7; 256 candidates 0.23 M 42.1 / 35.6; 512 candidates
+// 0.12 M 44.2 / 41.0.  The statistics stay with their two streaming passes there (without a search those are the
 // faster: 1 M elements 19.5 / 24.2 us), so that they do not depend on what follows.
-constexpr uint64_t kValueTableMinPairs = 60000000ull;
+#ifndef QP_VALUE_TABLE_MIN_PAIRS
+#define QP_VALUE_TABLE_MIN_PAIRS 60000000ull
+#endif
+constexpr uint64_t kValueTableMinPairs = QP_VALUE_TABLE_MIN_PAIRS;
+// ... and at least this many elements, one and a half times the table's entries: with very many candidates the line in pairs
+// lies where the table is the longer of the two.  Sender path with 1024 candidates, without / with the table: 59 K elements
+// 45.2 / 47.9 us, 66 K 44.5 / 47.1, 76 K 50.4 / 48.6, 98 K 49.9 / 47.0; 768 candidates, 82 K 43.3 / 43.3 (search alone
+// 28.1 / 28.7), 98 K 44.2 / 43.1.
+#ifndef QP_VALUE_TABLE_SEARCH_MIN_N
+#define QP_VALUE_TABLE_SEARCH_MIN_N (kNumValues16 + kNumValues16 / 2u)
+#endif
+constexpr uint64_t kValueTableSearchMinN = QP_VALUE_TABLE_SEARCH_MIN_N;
 // Tensors at least this large take the forms of quantize+pack (3 and 6 bit) and unpack+dequantize that pay on
 // large tensors only (measured break-even between 9.7 M and 77 M elements).
 #ifndef QP_LARGE_FORMS_MIN_N

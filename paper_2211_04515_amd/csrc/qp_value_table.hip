@@ -17,7 +17,8 @@ bool uses_value_table(uint64_t n, int dtype) { return dtype == QP_BF16 && n >= k
 bool searches_value_table(uint64_t n, int dtype, const SearchPlan &plan)
 {
     if (uses_value_table(n, dtype)) return true;
-    return dtype == QP_BF16 && !plan.aciq_only && plan.stride <= 1u && n * (plan.t_steps + 1u) >= kValueTableMinPairs;
+    return dtype == QP_BF16 && !plan.aciq_only && plan.stride <= 1u && n >= kValueTableSearchMinN &&
+           n * (plan.t_steps + 1u) >= kValueTableMinPairs;
 }
 
 // Also clears the tickets (the search over the table has no set-up launch that could) and, for statistics, the

@@ -1,5 +1,6 @@
 // TEST INFRASTRUCTURE ONLY: drives the library's C ABI on the CPU emulation (host memory stands in
 // for device memory) and writes everything it produced to files, for comparison with the oracle.
+//   emu_driver route <n> <dtype 0|1> <t_steps> <stride>: only names the search that such a tensor takes
 //   emu_driver <in.bin> <n> <dtype 0|1> <bits> <t_steps> <dist> <flags> <stride> <nbins> <cus> <outdir> [cands_per_round]
 #include <hip/hip_runtime.h>
 
@@ -8,7 +9,7 @@
 #include <string>
 #include <vector>
 
-#include "quantpipe.h"
+#include "qp_common.hpp"
 
 namespace emu { extern int g_occupancy, g_cus; void *shared_alloc(size_t); }
 
@@ -43,6 +44,14 @@ static void release(void *p)
 
 int main(int argc, char **argv)
 {
+    if (argc == 6 && std::string(argv[1]) == "route") {
+        const uint64_t n = strtoull(argv[2], nullptr, 10);
+        qp::SearchPlan plan{};
+        plan.t_steps = (uint32_t)atoi(argv[4]);
+        plan.stride = (uint32_t)atoi(argv[5]);
+        puts(qp::searches_value_table(n, atoi(argv[3]), plan) ? "table" : qp::tile_search_eligible(n, plan) ? "tile" : "streaming");
+        return 0;
+    }
     if (argc != 12 && argc != 13) { fprintf(stderr, "usage: see source\n"); return 2; }
     const char *in = argv[1];
     const uint64_t n = strtoull(argv[2], nullptr, 10);

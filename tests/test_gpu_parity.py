@@ -979,7 +979,9 @@ def test_sender_and_receiver_on_random_sizes(qp):
                                       ("bf16", 480_001, 127), ("bf16", 1_048_576, 100), ("bf16", 1_048_575, 7),
                                       # lists of fewer than 10 candidates: one block per unit up to 3 2^19 elements
                                       ("fp32", (1 << 20) + 1, 8), ("fp32", (1 << 20) + 1, 9), ("fp32", (3 << 19) - 1, 8),
-                                      ("fp32", 3 << 19, 8)])
+                                      ("fp32", 3 << 19, 8),
+                                      # very many candidates: no table for fewer elements than one and a half times its entries
+                                      ("bf16", 98_303, 1023), ("bf16", 98_304, 1023)])
 def test_search_routes_and_tile_remainders(qp, kind, n, t):
     """Scores and winner against the oracle on either side of the search's size rules, the fused path equal to the calls one
     by one, and the winner's record copied to a pointer of any alignment."""
