@@ -1079,8 +1079,8 @@ def test_sender_path_is_bit_reproducible(qp):
     assert all(o == outs[0] for o in outs[1:])
 
 
-@pytest.mark.parametrize("kind,n", [("fp32", 700_003), ("fp32", 2_500_003), ("bf16", 1_300_003)],
-                         ids=["tile_search", "streaming_search", "value_table"])
+@pytest.mark.parametrize("kind,n", [("fp32", 700_003), ("fp32", 2_500_003), ("bf16", 1_300_003), ("bf16", 700_003)],
+                         ids=["tile_search", "streaming_search", "value_table", "value_table_of_the_search"])
 def test_sender_and_receiver_replay_from_a_hip_graph(qp, kind, n):
     """The async entry points launch kernels only (no allocation, no memset, no host sync), so they
     capture into a HIP graph; every replay must reproduce the eager result.  One size per search kernel."""
@@ -1356,6 +1356,49 @@ def test_bf16_value_table_search_edge_cases(qp, kind):
         assert res.mse_star == pytest.approx(scores[res.j_star] / n, rel=1e-15) or np.isnan(res.mse_star)
 
 
+@pytest.mark.parametrize("nbins", [16, 100, 2048, 4096])
+@pytest.mark.parametrize("kind", ["laplace", "wide", "wide_negative"])
+def test_bf16_table_statistics_bin_counts_and_wide_ranges(qp, kind, nbins):
+    """Histogram, peak and moments from the value table; "wide" holds small values and others up to bf16's largest, of one
+    sign so that the range stays finite: the patterns from 2^121 on share a block with NaN patterns, whose bin is 0."""
+    n = (1 << 20) + 13
+    g = np.random.default_rng(nbins)
+    x = g.laplace(0.2, 0.8, size=n)
+    if kind != "laplace":
+        x = np.where(g.random(n) < 0.9, np.abs(x), np.minimum(10.0 ** g.uniform(-3, 38.5, size=n), 3.3e38))
+    h = si.f32_to_bf16_bits(x.astype(np.float32))
+    if kind == "wide_negative":
+        h = h | np.uint16(0x8000)
+    ws = qp.alloc_workspace(n)
+    ws.fill_(0x6D)
+    st = qp.qp_stats(to_dev(h), ws, nbins=nbins)
+    rc, ref, hist_ref = orc.stats(orc.widen_bf16(h), nbins=nbins, want_hist=True)
+    off = qp.qp_ws_offset(qp.QP_WS_HIST)
+    assert np.array_equal(ws[off:off + 4 * nbins].cpu().numpy().view(np.uint32), hist_ref[:nbins])
+    assert (st.n, st.n_nonfinite, st.min, st.max, st.nbins, st.peak_count) == (n, 0, ref.min, ref.max, nbins, ref.peak_count)
+    assert st.b_r == pytest.approx(ref.b_r, rel=1e-14)
+    # the oracle's own sequential sum of a million terms is off by up to 1e-10 (see REL_STATS_FULL)
+    for f in ("mean", "mad", "abs_mean", "var"):
+        assert abs(getattr(st, f) - getattr(ref, f)) <= REL_STATS_FULL * max(abs(getattr(ref, f)), 1e-3 * ref.abs_mean), f
+
+
+def test_bf16_table_statistics_count_nan_and_inf(qp):
+    n = (1 << 20) + 13
+    h = si.make_config("C5", n=n).copy()
+    clean = to_dev(h)
+    h[[1, 100, 70_000, n - 1]] = 0x7FC0, 0xFF81, 0x7F81, 0xFFFF       # NaN patterns of both signs, quiet and signalling
+    h[[7, 900_000]] = 0x7F80, 0xFF80                                  # both infinities
+    xd = to_dev(h)
+    ws = qp.alloc_workspace(n)
+    first = bytes(qp.qp_stats(clean, ws))
+    with pytest.raises(qp.QuantPipeError) as e:
+        qp.qp_stats(xd, ws)
+    assert e.value.status == qp.QP_ENONFINITE
+    st = qp.qp_stats(xd, ws, allow_nonfinite=True)
+    assert (st.n_nonfinite, st.min, st.max) == (6, -np.inf, np.inf)
+    assert bytes(qp.qp_stats(clean, ws)) == first     # and nothing of it stays in the workspace
+
+
 @pytest.mark.timeout(600)
 @pytest.mark.parametrize("kind", ["constant", "three_values", "hot_value_in_noise"])
 def test_bf16_value_table_counters_with_hot_values(qp, kind):
@@ -1397,8 +1440,8 @@ def test_bf16_value_table_counters_with_hot_values(qp, kind):
 
 VARIANTS = [dict(dist=1), dict(clip=True), dict(stride=10), dict(clip=True, stride=7), dict(dist=1, clip=True, stride=10),
             dict(stride=64), dict(stride=1, clip=True, dist=1)]
-# one input per search kernel: tile search (fp32, bf16), streaming search, bf16 value table
-VARIANT_INPUTS = [("C3", 300_007), ("C5", 200_003), ("C3", 2_600_011), ("C5", 1_300_001), ("C1", None)]
+# one input per search kernel: tile search (fp32, bf16), streaming search, bf16 value table, bf16 value table built by the search
+VARIANT_INPUTS = [("C3", 300_007), ("C5", 200_003), ("C3", 2_600_011), ("C5", 1_300_001), ("C1", None), ("C5", 700_001)]
 
 
 def variant_cfg(qp, v, t=100):
@@ -1469,7 +1512,7 @@ def test_search_variants_other_step_counts_and_strides(qp):
 
 def test_sender_path_with_variants(qp):
     """qp_compress_async with a variant configuration: same bits as the step-by-step calls, payload = the oracle's."""
-    for name, n in (("C3", 400_003), ("C3", 2_300_001), ("C5", 1_250_003)):
+    for name, n in (("C3", 400_003), ("C3", 2_300_001), ("C5", 1_250_003), ("C5", 700_001)):
         x = si.make_config(name, n=n)
         xf = as_f32(x)
         xd = to_dev(x)
