@@ -121,16 +121,10 @@ def small_input(kind, n):
         return (np.random.default_rng(n).standard_normal(n) * 0.8 + 0.3).astype(np.float32)
     if kind == "gauss_bf16":
         return si.f32_to_bf16_bits((np.random.default_rng(n).standard_normal(n) * 0.8 + 0.3).astype(np.float32))
-    if kind.startswith("wide"):   # one-sided and up to bf16's largest values, the range still finite
+    if kind == "wide_negative":   # one-sided and up to bf16's largest values, the range still finite
         g = np.random.default_rng(n)
         x = np.where(g.random(n) < 0.9, np.abs(g.laplace(0.0, 0.5, size=n)), 10.0 ** g.uniform(-3, 38.5, size=n))
-        h = si.f32_to_bf16_bits(np.minimum(x, 3.3e38).astype(np.float32))
-        return h | np.uint16(0x8000) if kind == "wide_negative" else h
-    if kind == "nonfinite":
-        h = si.make_config("C5", n=n).copy()
-        h[[1, 100, 1000, n - 1]] = 0x7FC0, 0xFF81, 0x7F81, 0xFFFF       # NaN patterns of both signs, quiet and signalling
-        h[[7, 4_000]] = 0x7F80, 0xFF80                                  # both infinities
-        return h
+        return si.f32_to_bf16_bits(np.minimum(x, 3.3e38).astype(np.float32)) | np.uint16(0x8000)
     if kind == "subnormal":   # the grid's reciprocal is infinite: the search's full clamp sequence
         return (np.random.default_rng(n).laplace(0.0, 1.0, size=n) * 1e-41).astype(np.float32)
     return si.make_config(kind, n=n)
@@ -158,13 +152,11 @@ STREAM_CASES = [("C3", 10_011, 2, {}, 100), ("C2", 6_007, 8, dict(clip=True), 37
                 ("gauss", 6_001, 4, dict(dist=2), 20), ("gauss_bf16", 5_003, 3, dict(dist=2), 20), ("C2", 5_555, 2, dict(dist=2, cpr=4), 9)]
 REFUSED = ("bf16", 5_000, 4, dict(stride=10), 100)
 ACIQ_ONLY = [("default", ("C3", 3_003, 8, dict(low_bits_only=True), 100)), ("streaming", ("bf16", 6_001, 6, dict(low_bits_only=True, clip=True), 100))]
-# The statistics from the value table with other bin counts, and with values of 2^121 and more (their patterns share a
-# block with NaN patterns, whose bin is 0)
-TABLE_STATS_CASES = [("streaming", ("wide", 5_003, 4, dict(nbins=100, conc=4), 1)), ("streaming", ("wide_negative", 5_003, 4, dict(nbins=4096, conc=4), 1))]
-NONFINITE = ("streaming", ("nonfinite", 5_001, 4, dict(conc=4), 1))
+# The statistics from the value table with another bin count and values of -2^121 and less (their patterns share a block
+# with NaN patterns, whose bin is 0)
+TABLE_STATS_CASES = [("streaming", ("wide_negative", 5_003, 4, dict(nbins=100, conc=4), 1))]
 # Two-pass statistics, then a table that the search builds over their partials
-PAIRS_CASES = [("pairs", c) for c in (("bf16", 4_003, 2, dict(dist=1, clip=True), 5),
-                                      ("gauss_bf16", 5_003, 3, dict(dist=2), 5), ("bf16", 7_001, 8, dict(conc=4, seed=1), 3))]
+PAIRS_CASES = [("pairs", c) for c in (("bf16", 7_001, 8, dict(dist=1, clip=True, conc=4, seed=1), 3), ("bf16", 3_001, 2, dict(conc=3, seed=2), 6))]
 # Blocks of a launch in shuffled order, `conc` at a time (each a process of its own): ticket hand-overs out of order.
 # The tile search and its pick kernel, the streaming search with several rounds, the statistics finalizer, the
 # value-table search; two seeds each.
@@ -183,12 +175,12 @@ STREAM_C2F_CASES = [("streaming_c2f", ("C3", 10_011, 2, dict(stride=10), 100)),
                     ("streaming_c2f", ("C3", 6_007, 4, dict(stride=64, conc=4, seed=5), 100))]
 # Where the fused path's record goes.  The pack kernel writes it only where it may: not over what its other blocks still
 # read or write (the input, the payload, the record itself), and not to memory that only a copy of the runtime reaches.
-RECORD_CASES = [("default", ("C3", 9_001, 4, dict(record=r), 1)) for r in ("in_x", "in_packed", "on_itself", "host", "peer")]
-RECORD_CASES += [("default", ("bf16", 9_001, 3, dict(record="in_x", conc=2, seed=s), 1)) for s in (1, 2)]
+RECORD_CASES = [("default", ("C3", 4_301, 4, dict(record=r), 1)) for r in ("in_x", "in_packed", "on_itself", "host", "peer")]
+RECORD_CASES += [("default", ("bf16", 9_001, 3, dict(record="in_x", conc=2, seed=s), 1)) for s in (1,)]
 RECORD_REFUSED = ("default", ("C3", 3_001, 4, dict(record="short"), 1))
 ALL_CASES = ([("default", c) for c in TILE_CASES] + [("streaming", c) for c in STREAM_CASES] + [("streaming", REFUSED)] + ACIQ_ONLY
              + CONCURRENT_CASES + STREAM_C2F_CASES + RECORD_CASES + [RECORD_REFUSED]
-             + TABLE_STATS_CASES + [NONFINITE] + PAIRS_CASES)
+             + TABLE_STATS_CASES + PAIRS_CASES)
 
 
 def case_id(tag, c):
@@ -216,7 +208,7 @@ def runs(drivers, tmp_path_factory):
         return dict(ex.map(go, sorted(ALL_CASES, key=lambda a: (a[0] != "streaming", small_input(a[1][0], a[1][1]).dtype != np.uint16))))
 
 
-WHOLE = [a for a in ALL_CASES if a[1] is not REFUSED and a not in ACIQ_ONLY and a not in (RECORD_REFUSED, NONFINITE)]
+WHOLE = [a for a in ALL_CASES if a[1] is not REFUSED and a not in ACIQ_ONLY and a is not RECORD_REFUSED]
 
 
 @pytest.mark.parametrize("tag,case", WHOLE, ids=[case_id(*a) for a in WHOLE])
@@ -229,13 +221,6 @@ def test_whole_path_on_the_emulation(runs, tag, case):
     r = read_outputs(p, out_dir)
     check_against_oracle(r, x, bits, t=t, dist=v.get("dist", 0), clip=bool(v.get("clip")), stride=v.get("stride", 1),
                          nbins=v.get("nbins", 2048))
-
-
-def test_table_statistics_count_nan_and_inf(runs):
-    """QP_ENONFINITE, and every NaN and infinity of either sign counted."""
-    p, out_dir, x = runs[case_id(*NONFINITE)]
-    r = read_outputs(p, out_dir)
-    assert r["rc"][0] == -4 and r["stats"].n_nonfinite == 6
 
 
 def test_emulation_refuses_what_the_library_refuses(runs):
@@ -254,7 +239,7 @@ ROUTES = [((594_059, 1, 100, 1), "tile"), ((594_060, 1, 100, 1), "table"), ((594
 
 
 def test_the_pairs_build_takes_the_table(drivers):
-    for n, t, search in ((4_003, 5, "table"), (5_003, 5, "table"), (7_001, 3, "table"), (999, 100, "tile"), (5_001, 2, "tile")):
+    for n, t, search in ((7_001, 3, "table"), (3_001, 6, "table"), (999, 100, "tile"), (5_001, 2, "tile")):
         p = subprocess.run([drivers["pairs"], "route", str(n), "1", str(t), "1"], capture_output=True, timeout=60)
         assert p.stdout.decode().strip() == search, (n, t)
 
