@@ -162,7 +162,10 @@ size_t qp_packed_bytes(uint64_t n, uint32_t bits);
 /* Bytes of device workspace needed by qp_stats / qp_dsaciq_search for an n-element
  * tensor under cfg (NULL = defaults: t_steps 100, cands_per_round 13).  0 on bad arguments.
  * (Sec. 3, Eq. 1: what the statistics and the t+1 candidates of the directed search need between kernels:
- * per-block partial sums, the histogram D_R, the candidate grids and their scores; nothing per element.) */
+ * per-block partial sums, the histogram D_R, the candidate grids and their scores.)
+ * About 1.4 MB for the default t_steps; above 2^21 elements also room for up to 2^24 elements of the tensor sorted by value
+ * and the tables of that sort (29 MB in all at 2^21 elements, 59 MB at 9.7 M, 89 MB at 2^24 and hardly more beyond).  A call
+ * whose workspace holds the first part only is not refused: its search goes over the tensor as it lies, with the same result. */
 size_t qp_workspace_bytes(uint64_t n, const qp_search_cfg_t *cfg);
 
 /* Byte offset of a region inside the workspace; (size_t)-1 for an unknown region. */
@@ -330,9 +333,9 @@ qp_status qp_compress_many_async(const qp_job_t *jobs, uint32_t count, const qp_
 
 /* ---- the same sender path for callers that cannot allocate -----------------------
  * For code under HIP graph capture, tight serving loops and harnesses that forbid hipMalloc: the
- * callers that cannot bring a workspace.  Same kernels and same results as qp_compress_async, with
- * the workspace in a static device array inside the library (1,384,960 bytes per GPU, held until
- * the process ends; its device address is looked up on the first call on each device, so a caller
+ * callers that cannot bring a workspace.  Same results as qp_compress_async (the search of a large fp32
+ * tensor goes over the tensor as it lies, see qp_workspace_bytes), with the workspace in a static device array
+ * inside the library (1,384,960 bytes per GPU, held until the process ends; its device address is looked up on the first call on each device, so a caller
  * that captures into a HIP graph makes one call outside the capture first).  Calls no allocating routine.  The caller still owns x_dev, packed_dev and qparams_out_dev (required:
  * 32 bytes of device memory that receive the winner's qp_qparams_t; the statistics and the search
  * result stay inside the library).  Limits: cfg->t_steps <= 127 (QP_ENOSPC beyond; NULL cfg =

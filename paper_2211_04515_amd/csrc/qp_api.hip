@@ -5,7 +5,7 @@
 #include <cmath>
 #include <cstring>
 
-#include "qp_common.hpp"
+#include "qp_bucket.hpp"
 
 using namespace qp;
 
@@ -52,15 +52,6 @@ double gauss_constant(uint32_t bits)
     return a;
 }
 
-qp_status check_ws(uint64_t n, const qp_search_cfg_t *cfg, const void *ws, size_t ws_bytes)
-{
-    if (!ws || !aligned16(ws)) return QP_EINVAL;
-    const size_t need = qp_workspace_bytes(n, cfg);
-    if (need == 0) return QP_EINVAL;
-    if (ws_bytes < need) return QP_ENOSPC;
-    return QP_OK;
-}
-
 qp_status check_cfg(const qp_search_cfg_t *cfg)
 {
     if (!cfg) return QP_OK;
@@ -69,6 +60,30 @@ qp_status check_cfg(const qp_search_cfg_t *cfg)
     if (cfg->dist != QP_LAPLACE && cfg->dist != QP_GAUSS && cfg->dist != QP_DIST_AUTO) return QP_EINVAL;
     if (cfg->flags & ~(QP_SEARCH_CLIP_TO_DATA | QP_SEARCH_COARSE_TO_FINE | QP_SEARCH_LOW_BITS_ONLY)) return QP_EINVAL;
     if (cfg->coarse_stride > 64u) return QP_EINVAL;
+    return QP_OK;
+}
+
+// The least that a search needs; 0: refused.  (What qp_workspace_bytes asks for beyond it is for the search by value buckets:
+// with less a call takes the streaming kernel.)
+size_t least_workspace(uint64_t n, const qp_search_cfg_t *cfg)
+{
+    if (n == 0 || n > kMaxN) return 0;
+    if (check_cfg(cfg) != QP_OK) return 0;
+    const uint32_t t = cfg ? cfg->t_steps : 100u;
+    // partial sums: one column per block of whichever search kernel the size selects, one row per
+    // candidate of the longest sweep (the fine sweep of a coarse-to-fine search has up to 127)
+    uint32_t cols = search_blocks(n);
+    if (tile_search_blocks(n) > cols) cols = tile_search_blocks(n);
+    const uint32_t rows = t + 1u > 128u ? t + 1u : 128u;
+    return kOffSearchPart + (size_t)cols * rows * sizeof(double);
+}
+
+qp_status check_ws(uint64_t n, const qp_search_cfg_t *cfg, const void *ws, size_t ws_bytes)
+{
+    if (!ws || !aligned16(ws)) return QP_EINVAL;
+    const size_t need = least_workspace(n, cfg);
+    if (need == 0) return QP_EINVAL;
+    if (ws_bytes < need) return QP_ENOSPC;
     return QP_OK;
 }
 
@@ -84,6 +99,8 @@ SearchPlan make_plan(uint32_t bits, const qp_search_cfg_t *cfg)
     p.C_alt = p.dist == QP_DIST_AUTO ? gauss_constant(bits) : 0.0;
     p.clip = (cfg && (cfg->flags & QP_SEARCH_CLIP_TO_DATA)) ? 1u : 0u;
     p.stride = 1u;
+    p.bucket_room = 0u;
+    p.bucket_at = 0u;
     if (cfg && (cfg->flags & QP_SEARCH_COARSE_TO_FINE)) p.stride = cfg->coarse_stride ? cfg->coarse_stride : 10u;
     p.aciq_only = (cfg && (cfg->flags & QP_SEARCH_LOW_BITS_ONLY) && bits > 4u) ? 1u : 0u;
     return p;
@@ -139,15 +156,8 @@ void qp_default_search_cfg(qp_search_cfg_t *cfg)
 
 size_t qp_workspace_bytes(uint64_t n, const qp_search_cfg_t *cfg)
 {
-    if (n == 0 || n > kMaxN) return 0;
-    if (check_cfg(cfg) != QP_OK) return 0;
-    const uint32_t t = cfg ? cfg->t_steps : 100u;
-    // partial sums: one column per block of whichever search kernel the size selects, one row per
-    // candidate of the longest sweep (the fine sweep of a coarse-to-fine search has up to 127)
-    uint32_t cols = search_blocks(n);
-    if (tile_search_blocks(n) > cols) cols = tile_search_blocks(n);
-    const uint32_t rows = t + 1u > 128u ? t + 1u : 128u;
-    return kOffSearchPart + (size_t)cols * rows * sizeof(double);
+    const size_t least = least_workspace(n, cfg);
+    return least == 0 ? 0 : bucket_search_end(n, least);   // (whatever t_steps: a longer sweep asks for no less)
 }
 
 size_t qp_ws_offset(qp_ws_region region)
@@ -234,7 +244,9 @@ static qp_status search_common(const void *x_dev, uint64_t n, qp_dtype dtype, co
     if (check_cfg(cfg) != QP_OK) return QP_EINVAL;
     const qp_status w = check_ws(n, cfg, ws_dev, ws_bytes);
     if (w != QP_OK) return w;
-    const SearchPlan plan = make_plan(bits, cfg);
+    SearchPlan plan = make_plan(bits, cfg);
+    plan.bucket_at = least_workspace(n, cfg);
+    plan.bucket_room = ws_bytes >= bucket_search_end(n, plan.bucket_at) ? 1u : 0u;
     if (!plan.aciq_only && plan.stride > 1u && !coarse_to_fine_supported(n, dtype, plan)) return QP_EINVAL;   // see quantpipe.h
     if (plan.dist == QP_DIST_AUTO) {   // the choice of the model, on the record and histogram in the workspace
         if (finalize_nbins) return QP_EINVAL;   // (internal: the record must already be final)
@@ -478,7 +490,7 @@ qp_status qp_compress_noalloc(const void *x_dev, uint64_t n, qp_dtype dtype, uin
     if (n == 0 || n > kMaxN || check_cfg(cfg) != QP_OK) return QP_EINVAL;
     // sizes beyond what the static workspace holds
     if (cfg && cfg->t_steps > kScratchMaxT) return QP_ENOSPC;
-    const size_t need = qp_workspace_bytes(n, cfg);
+    const size_t need = least_workspace(n, cfg);
     if (need == 0) return QP_EINVAL;
     if (need > kScratchBytes) return QP_ENOSPC;
     void *ws = nullptr;

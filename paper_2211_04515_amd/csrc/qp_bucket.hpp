@@ -1,0 +1,142 @@
+// The directed search by value buckets (qp_search_bucket.hip): the plan that its set-up makes on the device, and the
+// layout of its part of the workspace.
+#pragma once
+
+#include "qp_common.hpp"
+
+namespace qp {
+
+constexpr uint32_t kBkThreads = 1024;        // lanes of a sorting block
+constexpr uint32_t kBkCands = 128;           // most candidates of a sweep
+#ifndef QP_BUCKET_TILES
+#define QP_BUCKET_TILES 256                  // sorting blocks that run side by side: one per compute unit
+#endif
+#ifndef QP_BUCKET_WIDTH
+#define QP_BUCKET_WIDTH 1024                 // most buckets of a sign
+#endif
+#ifndef QP_BUCKET_SUM_BLOCKS
+#define QP_BUCKET_SUM_BLOCKS 1024            // summing blocks: four per compute unit
+#endif
+#ifndef QP_BUCKET_DEPTH
+#define QP_BUCKET_DEPTH 0x1p-10              // smallest element that has a bucket, as a share of |mean| + s_E
+#endif
+#ifndef QP_BUCKET_SEGMENT
+#define QP_BUCKET_SEGMENT (1u << 24)         // elements that are sorted at a time (bounds the workspace: 67 MB)
+#endif
+constexpr uint32_t kBkTiles = QP_BUCKET_TILES, kBkWidth = QP_BUCKET_WIDTH, kBkSumBlocks = QP_BUCKET_SUM_BLOCKS;
+constexpr uint32_t kBkOtherBlocks = kBkTiles;
+constexpr uint32_t kBkColumns = kBkSumBlocks + kBkOtherBlocks;   // partial sums of a candidate per segment
+constexpr uint32_t kBkRounds = 10;                               // 16-byte loads of a lane of a sorting block
+constexpr uint32_t kBkTileMax = 37u * kBkThreads;                // elements of a tile: 148 KB of LDS
+constexpr uint32_t kBkKeys = 2u * kBkWidth;                      // buckets of both signs
+constexpr uint32_t kBkRow = kBkKeys + 4u;                        // table entries of a tile
+// entries of one bucket's lists, and of those that one block makes
+constexpr uint32_t kBkCutCap = 512, kBkOwnCap = 96, kBkPieceCap = 768;
+constexpr uint32_t kBkCutAll = (1u << 19) / kBkTiles, kBkClassAll = (1u << 16) / kBkTiles, kBkPieceAll = (1u << 19) / kBkTiles;   // of one sorting block
+
+struct BucketPlan {
+    uint32_t unsuited;    // 1: the set-up leaves this tensor to the streaming kernel ...
+    uint32_t fallback;    // ... or the sort does
+    uint32_t shift;       // bits of an element's pattern below its bucket
+    uint32_t first;       // |pattern| >> shift of bucket 0
+    uint32_t width;       // buckets of a sign
+    uint32_t centre;      // the bucket of the mean: every candidate has a threshold there, so its elements count as outside
+};
+constexpr uint32_t kBkDirect = 24;    // most sums of a bucket that are formed in registers
+// One of them: a class's r(x) - r(base) over the elements with |x - base| >= from.  As they are (mode 0); by adding and taking
+// away m, a whole multiple of 2^k that puts the sum's last place there (mode 1); in 64 bits (mode 2).
+struct BucketSum { float from, m, mr, unit; float frac; int k2; uint32_t mode, pad; };
+struct BucketRec {
+    uint32_t cut, cls, piece;         // where the bucket's cuts, classes and further pieces start
+    uint32_t ncut, ncls;
+    uint32_t nsum;                    // sums that its pieces refer to; 0: summed by interval
+    uint32_t pad[2];
+    BucketSum sum[kBkDirect];
+};
+// How the elements of a bucket are rounded for some candidates: r(x) = x / 2^k - frac to the nearest whole number, ties to the
+// even (odd: to the odd) one.  Class 0 of every bucket leaves them as they are (k: the bucket's last place).
+struct BucketClass { float frac; int k2; };          // k2 = 2 k + odd
+// A candidate's constant piece of a bucket: sum of 4^k (r(x) - r(base) + e)^2, k the bucket's last place + dk, over the elements
+// from cut `from` on and before cut `to` (0: the bucket's start; kBkNone: its end; cuts count from 1).  Where the sums are formed in
+// registers, from and to are places in BucketRec::sum.
+struct BucketPiece { double e; uint8_t cls, dk; uint16_t from, to, next; };
+static_assert(sizeof(BucketPiece) == 16 && sizeof(BucketRec) == 800 && sizeof(BucketClass) == 8, "layout");
+constexpr uint32_t kBkNone = 0xffffu;
+
+struct BucketLayout {
+    uint32_t segments, tile, tiles;   // of the largest segment
+    size_t plan, totals, recs, shapes, cuts, classes, pieces, further, table, partials, sorted, end;
+};
+inline BucketLayout bucket_layout(uint64_t n, size_t at)
+{
+    BucketLayout l;
+    l.segments = ceil_div_u64(n, QP_BUCKET_SEGMENT);
+    const uint64_t m = (n + l.segments - 1) / l.segments;
+    const uint32_t rounds = ceil_div_u64(m, (uint64_t)kBkTiles * kBkTileMax);
+    l.tile = (ceil_div_u64(m, (uint64_t)kBkTiles * rounds) + 3u) / 4u * 4u;
+    l.tiles = ceil_div_u64(m, l.tile);
+    auto take = [&](size_t bytes) { const size_t o = at; at += (bytes + 255) / 256 * 256; return o; };
+    at = (at + 255) / 256 * 256;
+    l.plan = take(sizeof(BucketPlan));
+    l.totals = take((size_t)l.segments * kBkKeys * 4 + (size_t)l.segments * 4);   // the last words: zeros of a segment
+    l.recs = take(kBkKeys * sizeof(BucketRec));
+    l.shapes = take(kBkKeys * 4);
+    l.cuts = take((size_t)kBkTiles * kBkCutAll * 4);
+    l.classes = take((size_t)kBkTiles * kBkClassAll * sizeof(BucketClass));
+    l.pieces = take((size_t)kBkKeys * kBkCands * sizeof(BucketPiece));
+    l.further = take((size_t)kBkTiles * kBkPieceAll * sizeof(BucketPiece));
+    l.table = take((size_t)l.tiles * kBkRow * 2);
+    l.partials = take((size_t)kBkCands * kBkColumns * l.segments * 8);
+    l.sorted = take(((size_t)l.tiles * l.tile + 4) * 4);
+    l.end = at;
+    return l;
+}
+
+struct BucketSetup {
+    BucketPlan *plan;       // null: no such search follows
+    uint32_t *totals;
+    uint32_t words;         // of totals
+    uint32_t width;         // most buckets of a sign
+};
+
+// One block, behind setup_candidates: where the buckets lie, and whether this tensor suits them.
+__device__ inline void bucket_plan(const BucketSetup &b, const GridModel &g, int safe, const Cand *cands, uint32_t ncand)
+{
+    __shared__ double sh_inv[kFinThreads / kWave];
+    const uint32_t tid = threadIdx.x;
+    for (uint32_t i = tid; i < b.words; i += blockDim.x) b.totals[i] = 0u;
+    double inv = 0.0;
+    if (tid < ncand && cands[tid].scale > 0.0f) inv = 1.0 / (double)cands[tid].scale;   // (the lane's own store, see setup_candidates)
+    inv = wave_sum(inv);
+    if (tid % kWave == 0) sh_inv[tid / kWave] = inv;
+    __syncthreads();
+    if (tid != 0) return;
+    for (uint32_t w = 1; w < blockDim.x / kWave; ++w) inv += sh_inv[w];
+    const double am = fabs(g.mean) + g.s_e, reach = 16.0 * g.s_e;
+    const double lo = fmax(am * QP_BUCKET_DEPTH, fabs(g.mean) - reach), hi = fabs(g.mean) + reach;
+    const uint32_t plo = __float_as_uint((float)lo), phi = __float_as_uint((float)hi);
+    const bool ok = g.s_e > 0.0 && hi >= lo && plo >= (27u << 23) && phi <= (227u << 23);
+    uint32_t shift = 8u;
+    if (ok)
+        while ((phi >> shift) - (plo >> shift) + 1u > b.width) ++shift;
+    // thresholds that a typical bucket holds, all candidates together
+    const double cell = (double)__uint_as_float(__float_as_uint((float)am) & 0x7f800000u) * (double)(1u << shift) * 0x1p-23;
+    BucketPlan p{};
+    p.unsuited = (!ok || !safe || shift > 19u || !(inv * cell <= 250.0)) ? 1u : 0u;
+    p.fallback = p.unsuited;
+    p.shift = shift;
+    p.first = plo >> shift;
+    p.width = ok ? (phi >> shift) - (plo >> shift) + 1u : 1u;
+    const uint32_t mean = __float_as_uint((float)g.mean), u = ((mean & 0x7fffffffu) >> shift) - p.first;
+    p.centre = u < p.width ? u + (mean >> 31) * p.width : 0xffffffffu;
+    *b.plan = p;
+}
+
+// Whether such a search takes this call, given room in the workspace (the caller's business).
+bool bucket_search_eligible(uint64_t n, int dtype, const SearchPlan &plan);
+size_t bucket_search_end(uint64_t n, size_t at);   // bytes of a workspace with the search's part behind `at`
+BucketSetup bucket_setup_args(uint64_t n, const SearchPlan &plan, void *ws);
+// Behind the set-up: sort, sum, pick.  *fallback (device) is 1 afterwards if nothing was scored.
+hipError_t launch_bucket_search(const void *x, uint64_t n, const SearchPlan &plan, void *ws, const uint32_t **fallback, hipStream_t s);
+
+}  // namespace qp

@@ -515,6 +515,8 @@ struct SearchPlan {
     uint32_t clip;       // intersect candidate ranges with the data's range
     uint32_t stride;     // 1: all t + 1 candidates; > 1: coarse sweep with this stride, then a fine one
     uint32_t aciq_only;  // 1: score nothing, the result is plain ACIQ (j = 0)
+    uint32_t bucket_room;   // 1: the workspace holds what the search by value buckets needs ...
+    size_t bucket_at;       // ... behind this many bytes
 };
 
 // The two ends of the scale grid under a model: the moment estimate and the bound given by the
@@ -758,6 +760,9 @@ hipError_t launch_quant_pack(const void *x, uint64_t n, int dtype, uint32_t bits
 // The search with one candidate per lane over LDS-staged tiles, for tensors of at most
 // kTileSearchMaxN elements and at most 256 candidates (same arguments as launch_search).
 bool tile_search_eligible(uint64_t n, const SearchPlan &plan);
+// Adds `nblocks` partial sums of each candidate and takes the first minimum; does nothing where *skip (device, or null) is set.
+hipError_t launch_search_pick(const double *partials, uint32_t nblocks, uint32_t count, uint64_t n, void *ws, double *scores_list,
+                              const uint32_t *skip, hipStream_t s);
 bool tile_search_can_run(const SearchPlan &plan);
 uint32_t tile_search_blocks(uint64_t n);
 hipError_t launch_tile_search(const void *x, uint64_t n, int dtype, const SearchPlan &plan,

@@ -26,7 +26,7 @@
 // score is exactly the error of the tensor that would come out of the receiver.
 #include <atomic>
 
-#include "qp_common.hpp"
+#include "qp_bucket.hpp"
 
 namespace qp {
 
@@ -41,13 +41,15 @@ __global__ __launch_bounds__(kFinThreads) void k_search_setup(ModelArgs m, qp_st
                                                               Cand *__restrict__ cands, Ctl *__restrict__ ctl,
                                                               uint32_t *__restrict__ round_tickets, FinalizeArgs fin,
                                                               const qp_search_result_t *__restrict__ prev,
-                                                              double *__restrict__ scores_by_j)
+                                                              double *__restrict__ scores_by_j, BucketSetup buckets)
 {
     for (uint32_t j = threadIdx.x; j <= kMaxT; j += blockDim.x) round_tickets[j] = 0u;
     if (fin.nbins) finalize_stats_block(fin.part1, fin.nb1, fin.part2, fin.nb2, fin.hist, fin.nbins, n, stats_dev);
     m = resolve_model(m);
     const uint32_t j1 = (m.list_mode == kListFine) ? prev->j_star : 0u;
-    setup_candidates(m, m.from_ws ? stats_dev : nullptr, j1, n, cands, nullptr, ctl, scores_by_j);
+    const qp_stats_t *st = m.from_ws ? stats_dev : nullptr;
+    const int safe = setup_candidates(m, st, j1, n, cands, nullptr, ctl, scores_by_j);
+    if (buckets.plan) bucket_plan(buckets, grid_model(m, st), safe, cands, m.count);
 }
 
 // No search: the result is plain ACIQ, candidate j = 0 (the paper's deployment switches the directed search
@@ -177,8 +179,10 @@ __global__ __launch_bounds__(kSrThreads, (search_waves<DT, CMAX>())) void k_sear
                                                            uint32_t *__restrict__ round_tickets,
                                                            qp_search_result_t *__restrict__ res,
                                                            qp_qparams_t *__restrict__ best,
-                                                           double *__restrict__ scores_by_j)
+                                                           double *__restrict__ scores_by_j,
+                                                           const uint32_t *__restrict__ run_if)
 {
+    if (run_if && !*run_if) return;   // the search by value buckets has scored the tensor
     const uint32_t tid = threadIdx.x;
     const bool is_full = blockIdx.y < full;
     const uint32_t slots = is_full ? (uint32_t)CMAX : (uint32_t)CMAX - 1u;
@@ -465,6 +469,7 @@ struct SearchArgs {
     qp_search_result_t *res;
     qp_qparams_t *best;
     double *scores_by_j;   // where a coarse-to-fine sweep scatters its scores
+    const uint32_t *run_if;   // (device, or null) the kernel runs only where this is set
 };
 
 // One kernel variant: the grid is one wave of resident blocks, split over the rounds.
@@ -486,7 +491,7 @@ template <int DT, int CMAX> static hipError_t launch_variant(const SearchArgs &a
     if (gx > cols) gx = cols;
     if (gx < 1) gx = 1;
     hipLaunchKernelGGL((k_search_mse<DT, CMAX>), dim3(gx, rounds), dim3(kSrThreads), 0, s, a.x, a.n, a.cands, a.ncand, full,
-                       a.Lf, a.partials, a.scores, a.ctl, a.round_tickets, a.res, a.best, a.scores_by_j);
+                       a.Lf, a.partials, a.scores, a.ctl, a.round_tickets, a.res, a.best, a.scores_by_j, a.run_if);
     return hipGetLastError();
 }
 
@@ -584,14 +589,21 @@ static hipError_t launch_sweep(const void *x, uint64_t n, int dtype, const Searc
                      reinterpret_cast<const uint32_t *>(w + kOffHist), 0u, 0u, finalize_nbins};
     if (finalize_nbins) stats_grid(n, dtype, fin.nb1, fin.nb2);
     const ModelArgs m = model_args(plan, st, list_mode, count, ws);
+    const bool buckets = list_mode == kListFull && bucket_search_eligible(n, dtype, plan);
+    const BucketSetup bs = buckets ? bucket_setup_args(n, plan, ws) : BucketSetup{};
     hipLaunchKernelGGL(k_search_setup, dim3(1), dim3(kFinThreads), 0, s, m, stats_dev, n, cands, ctl, round_tickets, fin,
-                       res, scores_by_j);
-    const hipError_t e = hipGetLastError();
+                       res, scores_by_j, bs);
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    const uint32_t *run_if = nullptr;
+    if (buckets) {   // what it finds unsuitable is scored here; else this kernel's blocks end at once
+        e = launch_bucket_search(x, n, plan, ws, &run_if, s);
+        if (e != hipSuccess) return e;
+    }
 
     const SearchArgs a{x, n, cands, count, (float)((1u << plan.bits) - 1u),
                        reinterpret_cast<double *>(w + kOffSearchPart), scores_list, ctl, round_tickets, res,
-                       reinterpret_cast<qp_qparams_t *>(w + kOffQParams), scores_by_j};
+                       reinterpret_cast<qp_qparams_t *>(w + kOffQParams), scores_by_j, run_if};
     return dtype == QP_F32 ? launch_rounds<QP_F32>(a, plan.cpr, s) : launch_rounds<QP_BF16>(a, plan.cpr, s);
 }
 

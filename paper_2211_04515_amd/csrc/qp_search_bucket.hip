@@ -1,0 +1,1008 @@
+// Step 2b for large fp32 tensors at up to 8 bit: the DS-ACIQ directed search (Sec. 3, Eq. 1) by value buckets.
+//
+// Eq. 1 sums e^2 over the elements, e = fl(x - x^), x^ the value of x's level on the candidate's grid.  Scoring every
+// element against every candidate is 24 clocks of vector ALU work per pair and wave (qp_search.hip).  But over a short run of
+// values x^ is one constant, and if e keeps its binade there too, then fl(x - x^) moves with x alone: candidates whose x^ agree
+// below e's last place round x alike, e = f + E with one f for all of them, and sum e^2 = sum f^2 + 2 E sum f + n E^2.
+// So the tensor is sorted into buckets of neighbouring values (equal sign, exponent and leading bits of the mantissa) and a bucket
+// keeps three sums (n, sum f, sum f^2) for each of the few ways f that its elements are rounded.  All f are whole multiples of
+// the bucket's last place below 2^24 of it, so these sums are exact, whatever their order: the sort need not be stable, and
+// the scores are those of the element-by-element sum with equal terms grouped, bit-reproducible.
+//   k_bucket_sort   a block sorts one tile of the tensor by bucket in LDS and writes it back, with the tile's table of
+//                   bucket starts; then it takes its share of the buckets and lists, for each, the pieces on which a
+//                   candidate's x^ and e's binade are constant, and the sums that these pieces need;
+//   k_bucket_sum    blocks gather a bucket's elements from the tiles, form its sums, and add each candidate's pieces;
+//                   elements outside the buckets' range (about 0.1 % of them) are scored one by one;
+//   k_search_pick   adds the blocks' partial sums and takes the first minimum, as for the tile search.
+// A tensor that this does not suit (NaN or Inf, a grid that needs the full clamp sequence, so many thresholds to a bucket that
+// the pieces outgrow their lists) is found out on the device and left to the streaming kernel, which is launched behind.
+#include "qp_bucket.hpp"
+
+namespace qp {
+
+struct BucketArgs {
+    const float *x;             // the segment
+    uint64_t n;
+    uint32_t tile, tiles, ncand;
+    uint32_t first_segment;     // 1: the lists are still to be made
+    BucketPlan *plan;
+    uint32_t *totals;           // the segment's
+    uint32_t *zeros;            // elements that are zero, the segment's
+    uint16_t *table;
+    float *sorted;
+    const Cand *cands;
+    BucketRec *recs;
+    uint32_t *shapes;           // of a bucket: 0 or the number of its classes, see k_bucket_sum
+    uint32_t *cuts;
+    BucketClass *classes;
+    BucketPiece *pieces;        // a candidate's first piece of a bucket
+    BucketPiece *further;       // the others
+    double *partials;           // the segment's first column
+    uint32_t columns;           // of all segments
+};
+
+// ---- pieces ---------------------------------------------------------------------------------------
+
+// A bucket: elements of one sign with patterns base .. base + 2^shift - 1.
+struct BucketAt {
+    uint32_t base, size;
+    int a;                      // exponent of its last place
+    __device__ float value(uint32_t d) const { return __uint_as_float(base + d); }
+};
+__device__ inline BucketAt bucket_at(const BucketPlan &p, uint32_t b)
+{
+    const uint32_t neg = b >= p.width ? 1u : 0u, u = b - neg * p.width;
+    BucketAt t;
+    t.base = ((p.first + u) << p.shift) | (neg << 31);
+    t.size = 1u << p.shift;
+    t.a = (int)((t.base >> 23) & 0xffu) - 150;
+    return t;
+}
+__device__ inline double pow2(int e) { return __longlong_as_double((long long)(e + 1023) << 52); }   // -1022 <= e <= 1023
+// exponent of the last place that fl32 gives a difference
+__device__ inline int place_of(double e)
+{
+    const int x = (int)((uint32_t)__double2hiint(e) >> 20 & 0x7ffu) - 1046;
+    return e == 0.0 ? -2000 : (x < -149 ? -149 : x);
+}
+__device__ inline int place_of_value(float v)
+{
+    const int x = (int)(__float_as_uint(v) >> 23 & 0xffu) - 150;
+    return v == 0.0f ? 2000 : (x < -149 ? -149 : x);
+}
+__device__ __forceinline__ float bucket_level(const Cand &c, float x)
+{
+    const float xc = __builtin_amdgcn_fmed3f(x, c.lo, c.hi);
+    const float d = xc - c.lo;
+    return rintf(d * c.inv_scale);   // the short sequence: candidate_grid has shown that it needs no upper clamp
+}
+
+// A bucket's lists while 128 lanes, one a candidate, fill them.
+constexpr uint32_t kBkKeyed = 128;    // classes that candidates share: place - a < 32, parity, frac 0 or a half
+constexpr uint32_t kBkAsIs = 255u;    // class 0
+static_assert(kBkKeyed + kBkOwnCap < kBkAsIs, "a class is a byte");
+struct alignas(16) BucketLists {
+    uint32_t ncut, nown, npiece, over, ncls, need[2], pad;
+    uint32_t cut[kBkCutCap];          // its place in the bucket << 9 | number, so that no two are equal
+    uint16_t order[kBkCutCap];        // a cut's place among the sorted ones
+    uint16_t keyed[kBkKeyed];         // 1: wanted; then its number
+    BucketClass own[kBkOwnCap];
+    BucketPiece piece[kBkPieceCap];
+};
+
+__device__ inline double class_round(double x, double inv, double frac, double magic) { return (fma(x, inv, -frac) + magic) - magic; }
+
+// All pieces of one candidate in one bucket.
+__device__ inline void candidate_pieces(const BucketAt &t, const Cand &c, uint32_t j, BucketLists &l)
+{
+    const double sgn = (t.base >> 31) ? -1.0 : 1.0;
+    const double unit = pow2(-t.a), base = (double)t.value(0), abase = fabs(base);
+    const uint32_t last = t.size - 1u;
+    const float r_end = bucket_level(c, t.value(last));
+    uint32_t prev = kBkNone, cut_d = 0u, cut_ref = 0u;   // the piece before; the last cut
+    bool over = false;
+    auto cut = [&](uint32_t d) -> uint32_t {
+        if (d == 0u) return 0u;
+        if (d == t.size) return kBkNone;
+        if (d == cut_d) return cut_ref;
+        const uint32_t i = atomicAdd(&l.ncut, 1u);
+        if (i >= kBkCutCap) { over = true; return 0u; }
+        l.cut[i] = d << 9 | i;
+        cut_d = d;
+        cut_ref = i + 1u;
+        return cut_ref;
+    };
+    auto emit = [&](double e, uint32_t cls, int dk, uint32_t from, uint32_t to) {
+        const uint32_t cf = cut(from), ct = cut(to);
+        uint32_t slot = j;
+        if (prev != kBkNone) {
+            slot = kBkCands + atomicAdd(&l.npiece, 1u);
+            if (slot >= kBkPieceCap) { over = true; return; }
+            l.piece[prev].next = (uint16_t)slot;
+        }
+        l.piece[slot] = BucketPiece{e, (uint8_t)cls, (uint8_t)dk, (uint16_t)cf, (uint16_t)ct, (uint16_t)kBkNone};
+        prev = slot;
+    };
+    uint32_t from = 0u;
+    while (from < t.size && !over) {
+        const float r = bucket_level(c, t.value(from));
+        uint32_t to = t.size;
+        if (r != r_end) {
+            // the level's end: bisection around where it lies but for a few roundings at the size of the range's ends
+            auto same = [&](uint32_t d) { return bucket_level(c, t.value(d)) == r; };
+            const double at = ((double)c.lo + ((double)r + 0.5 * sgn) * (double)c.scale) * sgn;
+            const double g = fmin(fmax((at - abase) * unit, 0.0), (double)last);
+            const double w = 8.0 * fmax(1.0, fmax(fabs((double)c.lo), fabs((double)c.hi)) * unit * 0x1p-23);
+            uint32_t lo = g - w > (double)from ? (uint32_t)(g - w) : from, hi = g + w < (double)last ? (uint32_t)(g + w) : last;
+            if (lo < from || !same(lo)) lo = from;
+            if (hi <= lo || same(hi)) hi = last;
+            while (hi - lo > 1u) {
+                const uint32_t mid = lo + (hi - lo) / 2u;
+                if (same(mid)) lo = mid;
+                else hi = mid;
+            }
+            to = hi;
+        }
+        const float xh = dequant_level(r, c.scale, c.lo);
+        const double xd = (double)xh;
+        const int low = min(t.a, place_of_value(xh));
+        while (from < to && !over) {
+            const double e0 = (double)t.value(from) - xd, e1 = (double)t.value(to - 1u) - xd;
+            const int k = place_of(e0), k1 = place_of(e1);
+            // every x - x^ is a float: nothing is rounded
+            if (max(k, k1) <= low) {
+                emit((base - xd) * unit, kBkAsIs, 0, from, to);
+                from = to;
+                continue;
+            }
+            uint32_t end = to;
+            if (k1 != k || (e0 < 0.0) != (e1 < 0.0)) {   // the end of e's binade: |x| = |x^| +- a power of two
+                auto alike = [&](uint32_t d) {
+                    const double e = (double)t.value(d) - xd;
+                    return place_of(e) == k && (e < 0.0) == (e0 < 0.0);
+                };
+                const bool grows = (e0 < 0.0) == (sgn < 0.0);
+                const double at = grows ? ceil((sgn * xd + pow2(k + 24) - abase) * unit) : floor((sgn * xd - pow2(k + 23) - abase) * unit) + 1.0;
+                const uint32_t g = at > (double)from && at < (double)to ? (uint32_t)at : 0u;
+                uint32_t lo = from, hi = to - 1u;
+                if (g > lo && g <= hi) {
+                    if (alike(g - 1u)) lo = g - 1u;
+                    if (!alike(g)) hi = g;
+                }
+                while (hi - lo > 1u) {
+                    const uint32_t mid = lo + (hi - lo) / 2u;
+                    if (alike(mid)) lo = mid;
+                    else hi = mid;
+                }
+                end = hi;
+            }
+            // one binade: e is a whole multiple of 2^k
+            const double y = xd * pow2(-k), fl = floor(y);
+            double frac = y - fl;
+            if (k < t.a || (k == t.a && frac != 0.5)) {   // x is one too: x^ is rounded instead
+                emit((base - rint(y) * pow2(k)) * unit, kBkAsIs, 0, from, end);
+            } else {
+                const uint32_t odd = fl != 2.0 * floor(0.5 * fl) ? 1u : 0u;
+                const double magic = 0x1.8p52 + (double)odd;
+                uint32_t cls;
+                if (k - t.a < 32 && (frac == 0.0 || frac == 0.5)) {
+                    cls = ((uint32_t)(k - t.a) * 2u + odd) * 2u + (frac == 0.5 ? 1u : 0u);
+                    l.keyed[cls] = 1u;
+                } else {
+                    // x has at most 24 places below 2^k: what lies further down in frac only breaks ties
+                    const double f26 = floor(frac * 0x1p26);
+                    frac = f26 * 0x1p-26 + (frac * 0x1p26 != f26 ? 0x1p-27 : 0.0);
+                    const uint32_t i = atomicAdd(&l.nown, 1u);
+                    if (i >= kBkOwnCap) over = true;
+                    else l.own[i] = BucketClass{(float)frac, 2 * k + (int)odd};
+                    cls = kBkKeyed + i;
+                }
+                if (k - t.a > 24) over = true;
+                emit(class_round(base, pow2(-k), (double)(float)frac, magic) - fl, cls, k - t.a, from, end);
+            }
+            from = end;
+        }
+    }
+    if (over) l.over = 1u;
+}
+
+// The block's share of the buckets, eight at a time (128 lanes each).  Its lists go to stretches of its own.
+__device__ inline void bucket_lists(const BucketArgs &a, const BucketPlan &p, BucketLists *lists, uint32_t *used /* [3], shared */)
+{
+    const uint32_t tid = threadIdx.x, g = tid / kBkCands, j = tid % kBkCands;
+    constexpr uint32_t groups = kBkThreads / kBkCands;
+    static_assert(kBkKeyed == kBkCands, "a keyed class a lane");
+    const uint32_t blocks = min(gridDim.x, kBkTiles);
+    BucketLists &l = lists[g];
+    Cand c{0.0f, 0.0f, 0.0f, 0.0f};
+    const bool has = j < a.ncand;
+    if (has) c = a.cands[j];
+    if (tid < 3u) used[tid] = 0u;
+    for (uint32_t first = blockIdx.x; first < 2u * p.width; first += blocks * groups) {
+        const uint32_t b = first + g * blocks;
+        const bool live = b < 2u * p.width && b != p.centre;
+        if (j == 0u) {
+            l.ncut = l.nown = l.npiece = l.over = l.need[0] = l.need[1] = 0u;
+            l.ncls = 1u;   // class 0
+        }
+        l.keyed[j] = 0u;
+        __syncthreads();
+        const BucketAt t = bucket_at(p, live ? b : 0u);
+        if (live && has) candidate_pieces(t, c, j, l);
+        __syncthreads();
+        const uint32_t nc = min(l.ncut, kBkCutCap), nown = min(l.nown, kBkOwnCap), np = min(l.npiece, kBkPieceCap - kBkCands);
+        const bool want = l.keyed[j] != 0u;
+        uint32_t number = 0u;
+        if (want) number = atomicAdd(&l.ncls, 1u);
+        if (j < 8u && nc + j < kBkCutCap) l.cut[nc + j] = 0xffffffffu;
+        __syncthreads();
+        // the cuts' order
+        for (uint32_t i = j; i < nc; i += kBkCands) {
+            const uint32_t d = l.cut[i];
+            uint32_t below = 0u;
+            for (uint32_t k = 0; k < nc; k += 8u) {   // (places past the end hold larger values)
+                const uint4 u = *reinterpret_cast<const uint4 *>(&l.cut[k]), v = *reinterpret_cast<const uint4 *>(&l.cut[k + 4u]);
+                below += (u.x < d ? 1u : 0u) + (u.y < d ? 1u : 0u) + (u.z < d ? 1u : 0u) + (u.w < d ? 1u : 0u) + (v.x < d ? 1u : 0u) +
+                         (v.y < d ? 1u : 0u) + (v.z < d ? 1u : 0u) + (v.w < d ? 1u : 0u);
+            }
+            l.order[i] = (uint16_t)below;
+        }
+        __syncthreads();
+        if (want) l.keyed[j] = (uint16_t)number;
+        const uint32_t shared = l.ncls, ncls = shared + nown;
+        if (j == 0u) {   // (a dead group has a class and nothing else)
+            l.ncut = atomicAdd(&used[0], nc);
+            l.nown = atomicAdd(&used[1], ncls);
+            l.npiece = atomicAdd(&used[2], np);
+            if (l.ncut + nc > kBkCutAll || l.nown + ncls > kBkClassAll || l.npiece + np > kBkPieceAll) l.over = 1u;
+            if (live && l.over) st_dev(&a.plan->fallback, 1u);
+        }
+        __syncthreads();
+        const uint32_t at_cut = blockIdx.x * kBkCutAll + l.ncut, at_cls = blockIdx.x * kBkClassAll + l.nown, at_piece = blockIdx.x * kBkPieceAll + l.npiece;
+        const bool few = ncls * (nc + 1u) <= 64u;
+        if (live && !l.over) {
+            for (uint32_t i = j; i < nc; i += kBkCands) a.cuts[at_cut + l.order[i]] = l.cut[i] >> 9;
+            BucketClass *cls = a.classes + at_cls;
+            if (j == 0u) cls[0] = BucketClass{0.0f, 2 * t.a};
+            if (want) cls[number] = BucketClass{(j & 1u) ? 0.5f : 0.0f, 2 * (t.a + (int)(j >> 2)) + (int)((j >> 1) & 1u)};
+            for (uint32_t i = j; i < nown; i += kBkCands) cls[shared + i] = l.own[i];
+            for (uint32_t i = j; i < kBkCands + np; i += kBkCands) {
+                if (i < kBkCands && !has) continue;
+                BucketPiece &q = l.piece[i];
+                q.cls = (uint8_t)(q.cls == kBkAsIs ? 0u : q.cls < kBkKeyed ? l.keyed[q.cls] : shared + q.cls - kBkKeyed);
+                if (q.from) q.from = (uint16_t)(l.order[q.from - 1u] + 1u);
+                if (q.to != kBkNone) q.to = (uint16_t)(l.order[q.to - 1u] + 1u);
+                if (few) {
+                    const uint32_t s0 = q.cls * (nc + 1u) + q.from;
+                    atomicOr(&l.need[s0 / 32u], 1u << (s0 % 32u));
+                    if (q.to != kBkNone) {
+                        const uint32_t s1 = q.cls * (nc + 1u) + q.to;
+                        atomicOr(&l.need[s1 / 32u], 1u << (s1 % 32u));
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        const uint64_t need = (uint64_t)l.need[0] | ((uint64_t)l.need[1] << 32);
+        const uint32_t nsum = few && __popcll(need) <= (int)kBkDirect ? (uint32_t)__popcll(need) : 0u;
+        if (live && !l.over) {
+            auto place = [&](uint32_t s) { return (uint16_t)__popcll(need & ((1ull << s) - 1ull)); };
+            for (uint32_t i = j; i < kBkCands + np; i += kBkCands) {
+                if (i < kBkCands && !has) continue;
+                BucketPiece q = l.piece[i];
+                if (nsum) {
+                    q.from = place(q.cls * (nc + 1u) + q.from);
+                    if (q.to != kBkNone) q.to = place(q.cls * (nc + 1u) + q.to);
+                }
+                if (i < kBkCands) a.pieces[(uint64_t)b * kBkCands + i] = q;
+                else a.further[at_piece + i - kBkCands] = q;
+            }
+            BucketRec &r = a.recs[b];
+            if (nsum && j < 64u && (need >> j & 1ull)) {
+                const uint32_t k = j / (nc + 1u), cut = j % (nc + 1u);
+                BucketSum m{0.0f, 0.0f, 0.0f, __uint_as_float((uint32_t)(127 - t.a) << 23), 0.0f, 2 * t.a, 0u, 0u};
+                for (uint32_t i = 0; i < nc; ++i)
+                    if (cut == (uint32_t)l.order[i] + 1u) m.from = fabsf(t.value(l.cut[i] >> 9) - t.value(0));   // exact: one binade
+                if (k) {
+                    BucketClass c{0.0f, 0};
+                    if (k >= shared) c = l.own[k - shared];
+                    else
+                        for (uint32_t i = 0; i < kBkKeyed; ++i)
+                            if (l.keyed[i] == k) c = BucketClass{(i & 1u) ? 0.5f : 0.0f, 2 * (t.a + (int)(i >> 2)) + (int)((i >> 1) & 1u)};
+                    const int e = c.k2 >> 1;
+                    m.frac = c.frac;
+                    m.k2 = c.k2;
+                    m.mode = 2u;
+                    m.unit = (float)pow2(-e);
+                    if (c.frac == 0.0f && e <= 90) {
+                        const double b = rint((double)t.value(0) * pow2(-e));   // the base in whole 2^e
+                        double w = ((t.base >> 31) ? -0x1.8p23 : 0x1.8p23) - b;
+                        if ((w != 2.0 * floor(0.5 * w)) != ((c.k2 & 1) != 0)) w += 1.0;   // ties go to its parity
+                        m.m = (float)(w * pow2(e));
+                        m.mr = t.value(0) + m.m;
+                        m.mode = 1u;
+                    }
+                }
+                r.sum[place(j)] = m;
+            }
+            if (j == 0u) {
+                r.cut = at_cut;
+                r.cls = at_cls;
+                r.piece = at_piece;
+                r.ncut = nc;
+                r.ncls = ncls;
+                r.nsum = nsum;
+                a.shapes[b] = nsum ? 0u : ncls;
+            }
+        }
+        __syncthreads();   // the lists are reused
+    }
+}
+
+// ---- sort -------------------------------------------------------------------------------------------
+
+__global__ __launch_bounds__(kBkThreads) void k_bucket_sort(BucketArgs a)
+{
+    __shared__ __align__(16) float sx[kBkTileMax];
+    __shared__ uint32_t cnt[kBkKeys];
+    __shared__ uint32_t sh_wave[kBkThreads / kWave], sh_other[kBkThreads / kWave], sh_zero[kBkThreads / kWave];
+    __shared__ uint32_t sh_bad;
+    static_assert(sizeof(BucketLists) * (kBkThreads / kBkCands) <= sizeof(sx), "the lists are staged where the tile was");
+    if (a.plan->unsuited) return;   // (`fallback` may change while this kernel runs)
+    const BucketPlan p = *a.plan;
+    const uint32_t tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+    const uint64_t e0 = (uint64_t)blockIdx.x * a.tile;
+    const uint32_t m = (uint32_t)min((uint64_t)a.tile, a.n - e0);   // elements of this tile
+    const uint32_t quads = (m + 3u) / 4u;
+
+    // the whole tile is requested before anything else
+    float v[kBkRounds][4];
+#pragma unroll
+    for (uint32_t i = 0; i < kBkRounds; ++i) {
+        const uint32_t q = i * kBkThreads + tid;
+        if (4u * q + 4u <= m) {
+            Vec4<QP_F32>::load(a.x + e0, q, v[i]);
+        } else {
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k) v[i][k] = 4u * q + k < m ? a.x[e0 + 4u * q + k] : 0.0f;   // zeros are not kept
+        }
+    }
+    for (uint32_t i = tid; i < kBkKeys; i += kBkThreads) cnt[i] = 0u;
+    if (tid == 0) sh_bad = 0u;
+    __syncthreads();
+
+    // an element's place in its bucket (any order), or among the wave's elements outside the buckets (in a fixed order: those
+    // are scored one by one, and their sum depends on it)
+    auto key_of = [&](float x) -> uint32_t {   // 2 width: outside
+        const uint32_t w = __float_as_uint(x), u = ((w & 0x7fffffffu) >> p.shift) - p.first;
+        const uint32_t key = u + (w >> 31) * p.width;
+        return u < p.width && key != p.centre ? key : 2u * p.width;
+    };
+    uint32_t rank[kBkRounds][2];
+    uint32_t wother = 0u, wzero = 0u, bad = 0u;
+#pragma unroll
+    for (uint32_t i = 0; i < kBkRounds; ++i) {
+        if (i * kBkThreads < quads) {
+            uint32_t r[4];
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k) {
+                const uint32_t key = key_of(v[i][k]);
+                const bool zero = v[i][k] == 0.0f;
+                r[k] = 0u;
+                if (key < 2u * p.width) r[k] = atomicAdd(&cnt[key], 1u);
+                const uint64_t out = __ballot(key == 2u * p.width);
+                if (out) {
+                    const uint64_t nul = __ballot(zero);
+                    const uint64_t oth = out & ~nul;
+                    if (key == 2u * p.width) {
+                        r[k] = wother + (uint32_t)__popcll(oth & ((1ull << lane) - 1ull));
+                        bad |= __builtin_isfinite(v[i][k]) ? 0u : 1u;
+                    }
+                    wother += (uint32_t)__popcll(oth);
+                    wzero += (uint32_t)__popcll(nul);
+                }
+            }
+            rank[i][0] = r[0] | (r[1] << 16);
+            rank[i][1] = r[2] | (r[3] << 16);
+        }
+    }
+    if (lane == 0) {
+        sh_other[wave] = wother;
+        sh_zero[wave] = wzero;
+    }
+    if (bad) sh_bad = 1u;
+    __syncthreads();
+
+    // ---- starts of the buckets: an exclusive scan, two of them a lane ----
+    static_assert(kBkKeys <= 2u * kBkThreads && kBkKeys % 2u == 0u, "two buckets a lane");
+    const bool two = 2u * tid < kBkKeys;
+    const uint32_t c0 = two ? cnt[2u * tid] : 0u, c1 = two ? cnt[2u * tid + 1u] : 0u;
+    uint32_t s = c0 + c1;
+#pragma unroll
+    for (uint32_t o = 1; o < (uint32_t)kWave; o <<= 1) {
+        const uint32_t up = __shfl_up(s, o, kWave);
+        if (lane >= o) s += up;
+    }
+    if (lane == (uint32_t)kWave - 1u) sh_wave[wave] = s;
+    __syncthreads();
+    uint32_t before = 0u, kept = 0u, obefore = 0u, others = 0u, zeros = 0u;
+    for (uint32_t w = 0; w < kBkThreads / kWave; ++w) {
+        if (w < wave) {
+            before += sh_wave[w];
+            obefore += sh_other[w];
+        }
+        kept += sh_wave[w];
+        others += sh_other[w];
+        zeros += sh_zero[w];
+    }
+    const uint32_t start0 = before + s - (c0 + c1), start1 = start0 + c0;
+    uint16_t *row = a.table + (uint64_t)blockIdx.x * kBkRow;
+    if (two) {
+        cnt[2u * tid] = start0;
+        cnt[2u * tid + 1u] = start1;
+        if (tid < p.width) reinterpret_cast<uint32_t *>(row)[tid] = start0 | (start1 << 16);
+    }
+    if (tid == 0) {
+        reinterpret_cast<uint32_t *>(row)[p.width] = kept | ((kept + others) << 16);
+        const uint32_t real = zeros - ((quads + kBkThreads - 1u) / kBkThreads * kBkThreads * 4u - m);   // without the places behind the tile's end
+        if (real) atomicAdd(a.zeros, real);
+        // one by one they would take too long
+        if (sh_bad || others > m / 8u + 64u) st_dev(&a.plan->fallback, 1u);
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t i = 0; i < kBkRounds; ++i) {
+        if (i * kBkThreads < quads) {
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k) {
+                const uint32_t key = key_of(v[i][k]);
+                const uint32_t r = (rank[i][k / 2u] >> (16u * (k % 2u))) & 0xffffu;
+                if (key < 2u * p.width) sx[cnt[key] + r] = v[i][k];
+                else if (v[i][k] != 0.0f) sx[kept + obefore + r] = v[i][k];
+            }
+        }
+    }
+    __syncthreads();
+    float4 *out = reinterpret_cast<float4 *>(a.sorted + (uint64_t)blockIdx.x * a.tile);
+    const uint32_t oq = (kept + others + 3u) / 4u;   // at most tile / 4
+    for (uint32_t q = tid; q < oq; q += kBkThreads) out[q] = reinterpret_cast<const float4 *>(sx)[q];
+    // how much work a bucket is: every fourth tile's count
+    if (two && blockIdx.x % 4u == 0u) {
+        if (c0) atomicAdd(&a.totals[2u * tid], 4u * c0);
+        if (c1) atomicAdd(&a.totals[2u * tid + 1u], 4u * c1);
+    }
+    if (!a.first_segment || blockIdx.x >= kBkTiles) return;
+    __syncthreads();
+    bucket_lists(a, p, reinterpret_cast<BucketLists *>(sx), sh_wave);
+}
+
+// ---- sum --------------------------------------------------------------------------------------------
+
+constexpr int kBsThreads = 256;
+constexpr uint32_t kBsTiles = 512;         // most tiles of a segment
+constexpr uint32_t kBsQuads = 4;           // 4-element loads of a lane per batch
+constexpr uint32_t kBsPerLane = 4u * kBsQuads;
+constexpr uint32_t kBsPart = 3584;         // elements of a work item, about: a batch
+constexpr uint32_t kBsBatch = kBsThreads * kBsQuads;   // loads of a batch
+constexpr uint32_t kBsItems = 128;         // most work items that a block lists at a time
+
+struct alignas(4) Float4U { float x, y, z, w; };   // a run starts at any element
+
+// Sums of one work item: those that its pieces refer to, or one class's by interval between cuts.
+struct BucketSums {
+    BucketSum sum[kBkDirect];
+    uint32_t n[kBkDirect];
+    uint64_t f[kBkDirect], q[kBkDirect];
+    uint64_t nf[kBkCutCap + 1], iq[kBkCutCap + 1];   // count << 40 | sum |f|;  sum f^2
+    uint64_t wave_nf[kBsThreads / kWave], wave_q[kBsThreads / kWave];
+    uint32_t cut[kBkCutCap];
+    uint16_t start[257];                             // cuts at or below the start of each 1/256 of the bucket
+};
+
+struct ClassArgs {
+    double inv, frac, magic, ref;
+    __device__ ClassArgs(const BucketClass &c, float base)
+    {
+        const int k = c.k2 >> 1;
+        inv = pow2(-k);
+        frac = (double)c.frac;
+        magic = 0x1.8p52 + (double)(c.k2 & 1);
+        ref = class_round((double)base, inv, frac, magic);
+    }
+    __device__ __forceinline__ double offset(float x) const { return (fma((double)x, inv, -frac) + magic) - (magic + ref); }
+};
+
+// Values that the compiler must take as new: what it would otherwise work out once for all sums (64-bit copies) costs the
+// registers of a wave.
+__device__ __forceinline__ void opaque(float (&v)[kBsPerLane])
+{
+#if defined(__AMDGCN__)
+#pragma unroll
+    for (uint32_t i = 0; i < kBsPerLane; ++i) asm volatile("" : "+v"(v[i]));
+#endif
+}
+
+// The sums that a bucket's pieces refer to, a batch of 4 NQ elements a lane, `valid` of the wave's.
+template <int NQ>
+__device__ __forceinline__ void bucket_batch(float (&f0)[kBsPerLane], uint32_t valid, float base, uint32_t nsum, BucketSums &sh,
+                                             uint32_t lane)
+{
+    for (uint32_t s = 0; s < nsum; ++s) {
+        opaque(f0);
+        const float from = wave_uniform(sh.sum[s].from), unit = wave_uniform(sh.sum[s].unit);
+        const uint32_t mode = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.sum[s].mode);
+        uint32_t n = valid;
+        float fs = 0.0f;   // at most 2^10 elements below 2^20
+        double q0 = 0.0, q1 = 0.0;
+        auto sums = [&](auto value) {   // four running sums
+#pragma unroll
+            for (int i = 0; i < 4 * NQ; i += 2) {
+                const float a = value(i), b = value(i + 1);
+                fs += a;
+                fs += b;
+                const double d0 = (double)a, d1 = (double)b;
+                q0 = fma(d0, d0, q0);
+                q1 = fma(d1, d1, q1);
+            }
+        };
+        if (from > 0.0f) {
+            n = 0u;
+#pragma unroll
+            for (int i = 0; i < 4 * NQ; ++i) n += (uint32_t)__popcll(__ballot(fabsf(f0[i]) >= from));
+        }
+        if (mode == 0u) {
+            if (from > 0.0f) sums([&](int i) { return fabsf(f0[i]) >= from ? f0[i] : 0.0f; });
+            else sums([&](int i) { return f0[i]; });
+        } else if (mode == 1u) {
+            const float m = wave_uniform(sh.sum[s].m), mr = wave_uniform(sh.sum[s].mr);
+            if (from > 0.0f) sums([&](int i) { return fabsf(f0[i]) >= from ? ((base + f0[i]) + m) - mr : 0.0f; });
+            else sums([&](int i) { return ((base + f0[i]) + m) - mr; });
+        } else {
+            const ClassArgs cl(BucketClass{sh.sum[s].frac, sh.sum[s].k2}, base);
+            sums([&](int i) { return fabsf(f0[i]) >= from ? (float)cl.offset(base + f0[i]) : 0.0f; });   // whole numbers
+        }
+        const float u = mode == 2u ? 1.0f : unit;
+        const int fi = (int)wave_sum_u32((uint32_t)(int)(fs * u));
+        const double qs = wave_sum(q0 + q1) * ((double)u * (double)u);
+        if (lane == 0) {
+            atomicAdd(reinterpret_cast<unsigned long long *>(&sh.f[s]), (unsigned long long)(long long)fi);
+            atomicAdd(reinterpret_cast<unsigned long long *>(&sh.q[s]), (unsigned long long)qs);
+            atomicAdd(&sh.n[s], n);
+        }
+    }
+}
+
+__device__ __forceinline__ uint64_t shfl_up_u64(uint64_t v, uint32_t o)
+{
+    return (uint64_t)__shfl_up((uint32_t)v, o, kWave) | ((uint64_t)__shfl_up((uint32_t)(v >> 32), o, kWave) << 32);
+}
+
+// sum (f + e)^2 = q + 2 e f + n e^2 with the rounding errors of its large terms carried along: x^ may lie among the elements,
+// and the sum then is small beside its terms
+__device__ inline double piece_sum(double n, double f, double q, double e)
+{
+    const double p = n * e, pe = fma(n, e, -p);
+    const double f2 = 2.0 * f, s = f2 + p, sb = s - f2, se = (f2 - (s - sb)) + (p - sb);
+    const double t = e * s, te = fma(e, s, -t);
+    const double r = q + t, rb = r - q, re = (q - (r - rb)) + (t - rb);
+    return r + (re + (te + e * (se + pe)));
+}
+
+__global__ __launch_bounds__(kBsThreads, 4) void k_bucket_sum(BucketArgs a)
+{
+    // the sums; before them, the work items' bounds
+    __shared__ __align__(16) uint32_t buffer[sizeof(BucketSums) / 4u > 2u * kBkKeys + 1u ? sizeof(BucketSums) / 4u : 2u * kBkKeys + 1u];
+    BucketSums &sh = *reinterpret_cast<BucketSums *>(buffer);
+    const uint32_t tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+    const BucketPlan p = *a.plan;
+    if (p.fallback) return;
+    const uint32_t nbuckets = 2u * p.width;
+    double total = 0.0;   // of the lane's candidate
+
+    if (blockIdx.x < kBkOtherBlocks) {   // elements outside the buckets: one candidate a lane, two lanes a candidate
+        float *sh_v = reinterpret_cast<float *>(&sh);
+        double *sh_half = reinterpret_cast<double *>(sh_v + 1024);
+        static_assert(sizeof(BucketSums) >= 4096 + kBkCands * sizeof(double), "their place");
+        const uint32_t c = tid % kBkCands, half = tid / kBkCands;
+        Cand g{0.0f, 0.0f, 0.0f, 0.0f};
+        if (c < a.ncand) g = a.cands[c];
+        auto score = [&](float x) { return (double)(x - dequant_level(bucket_level(g, x), g.scale, g.lo)); };
+        double acc[2] = {0.0, 0.0};
+        if (blockIdx.x == 0u && half == 0u) {   // all zeros have one value
+            const double e = score(0.0f);
+            total = (double)*a.zeros * e * e;
+        }
+        for (uint32_t t = blockIdx.x; t < a.tiles; t += kBkOtherBlocks) {
+            const uint16_t *row = a.table + (uint64_t)t * kBkRow;
+            const uint32_t from = row[nbuckets], to = row[nbuckets + 1u];
+            for (uint32_t at = from; at < to; at += 1024u) {
+                const uint32_t nv = min(1024u, to - at), mid = nv / 8u * 4u;
+                __syncthreads();
+                for (uint32_t i = tid; i < nv; i += kBsThreads) sh_v[i] = a.sorted[(uint64_t)t * a.tile + at + i];
+                __syncthreads();
+                const uint32_t end = half ? nv : mid;
+                uint32_t i = half ? mid : 0u;
+                for (; i + 8u <= end; i += 8u) {
+                    const float4 u = *reinterpret_cast<const float4 *>(sh_v + i), v = *reinterpret_cast<const float4 *>(sh_v + i + 4u);
+                    const double e[8] = {score(u.x), score(u.y), score(u.z), score(u.w), score(v.x), score(v.y), score(v.z), score(v.w)};
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) acc[k & 1] = fma(e[k], e[k], acc[k & 1]);
+                }
+                for (; i < end; ++i) {
+                    const double e = score(sh_v[i]);
+                    acc[0] = fma(e, e, acc[0]);
+                }
+            }
+        }
+        total += acc[0] + acc[1];
+        __syncthreads();
+        if (half) sh_half[c] = total;
+        __syncthreads();
+        if (!half && c < a.ncand) a.partials[(uint64_t)c * a.columns + blockIdx.x] = total + sh_half[c];
+        return;
+    }
+
+    // ---- work items: a bucket is cut into parts by tile, and where it is summed by interval, by class as well ----
+    struct Item { uint16_t bucket, part, parts, cls; };
+    __shared__ Item sh_items[kBsItems];
+    __shared__ uint32_t sh_wave[kBsThreads / kWave][2];
+    __shared__ uint32_t runs[kBsTiles], first_load[kBsTiles], loads[kBsBatch];
+    static_assert((kBkKeys & (kBkKeys - 1u)) == 0u && kBsItems <= (uint32_t)kBsThreads, "an item a lane");
+    constexpr uint32_t per = (kBkKeys + kBsThreads - 1) / kBsThreads;
+    const uint32_t me = blockIdx.x - kBkOtherBlocks;
+    for (uint32_t first = me, items = first + 1u; first < items; first += kBsItems * kBkSumBlocks) {
+        // the block's items first, first + kBkSumBlocks, ...
+        {
+            uint32_t parts[per], s1 = 0u, s2 = 0u;   // of the lane's buckets; classes << 16 | parts
+            static_assert(per % 4u == 0u, "16-byte loads");
+#pragma unroll
+            for (uint32_t k = 0; k < per; k += 4u) {
+                const uint4 u = reinterpret_cast<const uint4 *>(a.totals)[(tid * per + k) / 4u], v = reinterpret_cast<const uint4 *>(a.shapes)[(tid * per + k) / 4u];
+                const uint32_t n[4] = {u.x, u.y, u.z, u.w}, shape[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (uint32_t i = 0; i < 4u; ++i) {
+                    const uint32_t b = tid * per + k + i;
+                    const bool used = b < nbuckets && b != p.centre;   // (the others have no shape)
+                    const uint32_t p1 = used ? min(n[i] / kBsPart + 1u, a.tiles) : 0u, c = used ? shape[i] : 0u;
+                    parts[k + i] = p1 | c << 16;
+                    if (c) s1 += p1 * c;
+                    else s2 += p1;
+                }
+            }
+            uint32_t p1 = s1, p2 = s2;
+#pragma unroll
+            for (uint32_t o = 1; o < (uint32_t)kWave; o <<= 1) {
+                const uint32_t u1 = __shfl_up(p1, o, kWave), u2 = __shfl_up(p2, o, kWave);
+                if (lane >= o) {
+                    p1 += u1;
+                    p2 += u2;
+                }
+            }
+            if (lane == (uint32_t)kWave - 1u) {
+                sh_wave[wave][0] = p1;
+                sh_wave[wave][1] = p2;
+            }
+            __syncthreads();
+            uint32_t all1 = 0u, all2 = 0u;
+            for (uint32_t w = 0; w < kBsThreads / kWave; ++w) {
+                if (w < wave) {
+                    p1 += sh_wave[w][0];
+                    p2 += sh_wave[w][1];
+                }
+                all1 += sh_wave[w][0];
+                all2 += sh_wave[w][1];
+            }
+            uint32_t i1 = p1 - s1, i2 = all1 + p2 - s2;   // the costly ones first
+            items = all1 + all2;
+            uint32_t *first_item = buffer;
+#pragma unroll
+            for (uint32_t k = 0; k < per; ++k) {
+                const uint32_t b = tid * per + k, c = parts[k] >> 16, n = parts[k] & 0xffffu;
+                if (b < kBkKeys) {
+                    first_item[b] = i1;
+                    first_item[kBkKeys + b] = i2;
+                }
+                if (c) i1 += n * c;
+                else i2 += n;
+            }
+            if (tid == kBsThreads - 1u) first_item[2u * kBkKeys] = i2;
+            __syncthreads();
+            const uint32_t i = first + tid * kBkSumBlocks;
+            if (tid < kBsItems && i < items) {
+                uint32_t lo = 0u, hi = 2u * kBkKeys;   // first_item[lo] <= i < first_item[hi]
+                while (hi - lo > 1u) {
+                    const uint32_t mid = (lo + hi) / 2u;
+                    if (first_item[mid] <= i) lo = mid;
+                    else hi = mid;
+                }
+                const uint32_t b = lo & (kBkKeys - 1u), ncls = lo < kBkKeys ? a.shapes[b] : 1u;
+                const uint32_t n = (first_item[lo + 1u] - first_item[lo]) / ncls, at = i - first_item[lo], cls = at / n;
+                sh_items[tid] = Item{(uint16_t)b, (uint16_t)(at - cls * n), (uint16_t)n, (uint16_t)cls};
+            }
+        }
+        __syncthreads();
+        for (uint32_t item = 0; item < kBsItems && first + item * kBkSumBlocks < items; ++item) {
+            auto uniform = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); };
+            const uint32_t b = uniform(sh_items[item].bucket), part = uniform(sh_items[item].part), parts = uniform(sh_items[item].parts);
+            const uint32_t cls = uniform(sh_items[item].cls);
+            const uint32_t t0 = a.tiles * part / parts, nruns = a.tiles * (part + 1u) / parts - t0;   // tiles <= 512
+            const BucketRec *rec = a.recs + b;
+            const uint32_t nsum = uniform(rec->nsum), ncut = uniform(rec->ncut), cuts1 = ncut + 1u;
+            const uint32_t further = uniform(rec->piece);
+            const bool direct = nsum != 0u;
+            const uint32_t *cuts = a.cuts + uniform(rec->cut);
+            const BucketClass *classes = a.classes + uniform(rec->cls);
+            if (tid < kBkDirect) sh.sum[tid] = rec->sum[tid];   // (what lies past nsum is not used)
+            const BucketAt at = bucket_at(p, b);
+            const float base = at.value(0);
+            BucketPiece pc{};
+            if (tid < a.ncand) pc = a.pieces[(uint64_t)b * kBkCands + tid];
+            // the runs, two a lane, and where their loads come in the item's list of loads
+            uint32_t nl[2], sum = 0u;
+#pragma unroll
+            for (uint32_t i = 0; i < 2u; ++i) {
+                const uint32_t t = 2u * tid + i;
+                nl[i] = 0u;
+                if (t < nruns) {
+                    const uint16_t *row = a.table + (uint64_t)(t0 + t) * kBkRow + b;
+                    const uint32_t from = row[0], len = (uint32_t)row[1] - from;
+                    runs[t] = from | (len << 16);
+                    nl[i] = (len + 3u) / 4u;
+                }
+                sum += nl[i];
+            }
+            static_assert(kBsTiles <= 2u * kBsThreads, "two runs a lane");
+            uint32_t up = sum;
+#pragma unroll
+            for (uint32_t o = 1; o < (uint32_t)kWave; o <<= 1) {
+                const uint32_t v = __shfl_up(up, o, kWave);
+                if (lane >= o) up += v;
+            }
+            if (lane == (uint32_t)kWave - 1u) sh_wave[wave][0] = up;
+            if (direct) {
+                if (tid < kBkDirect) {
+                    sh.n[tid] = 0u;
+                    sh.f[tid] = sh.q[tid] = 0u;
+                }
+            } else {
+                for (uint32_t i = tid; i < ncut; i += kBsThreads) sh.cut[i] = cuts[i];
+                for (uint32_t i = tid; i < cuts1; i += kBsThreads) sh.nf[i] = sh.iq[i] = 0u;
+            }
+            __syncthreads();
+            uint32_t total_loads = 0u;
+            for (uint32_t w = 0; w < kBsThreads / kWave; ++w) {
+                if (w < wave) up += sh_wave[w][0];
+                total_loads += sh_wave[w][0];
+            }
+            up -= sum;
+            if (2u * tid < nruns) first_load[2u * tid] = up;
+            if (2u * tid + 1u < nruns) first_load[2u * tid + 1u] = up + nl[0];
+            if (!direct) {
+                // by interval between cuts: first the cuts at or below each 1/256 of the bucket, a few steps on from there
+                for (uint32_t i = tid; i <= 256u; i += kBsThreads) {
+                    const uint32_t d = i << (p.shift - 8u);
+                    uint32_t l0 = 0u, h0 = ncut;   // cuts below l0 are <= d, cuts from h0 on are > d
+                    while (l0 < h0) {
+                        const uint32_t mid = (l0 + h0) / 2u;
+                        if (sh.cut[mid] <= d) l0 = mid + 1u;
+                        else h0 = mid;
+                    }
+                    sh.start[i] = (uint16_t)l0;
+                }
+            }
+            uint32_t share = 0u;   // 2^share lanes list a run's loads
+            while (share < 6u && (nruns << (share + 1u)) <= (uint32_t)kBsThreads) ++share;
+            for (uint32_t batch = 0; batch < total_loads; batch += kBsBatch) {
+                __syncthreads();   // runs and their places are there; the last batch's list has been read
+                for (uint32_t r = tid >> share; r < nruns; r += (uint32_t)kBsThreads >> share) {
+                    const uint32_t run = runs[r], at0 = first_load[r], len = run >> 16, n4 = (len + 3u) / 4u;
+                    if (at0 + n4 <= batch || at0 >= batch + kBsBatch) continue;
+                    const uint32_t where = r * a.tile + (run & 0xffffu);
+                    uint32_t q = tid & ((1u << share) - 1u);
+                    if (at0 + q < batch) q += ((batch - at0 - q + (1u << share) - 1u) >> share) << share;
+                    for (; q < n4 && at0 + q < batch + kBsBatch; q += 1u << share)
+                        loads[at0 + q - batch] = (where + 4u * q) << 2 | min(len - 4u * q - 1u, 3u);   // where < 2^25
+                }
+                __syncthreads();
+                const uint32_t left = min(total_loads - batch, kBsBatch);
+                const float *sorted = a.sorted + (uint64_t)t0 * a.tile;
+                float f0[kBsPerLane];
+                uint32_t have[kBsQuads], valid = 0u;
+                Float4U x[kBsQuads];
+#pragma unroll
+                for (uint32_t k = 0; k < kBsQuads; ++k) {
+                    const uint32_t i = k * kBsThreads + tid;
+                    x[k] = Float4U{base, base, base, base};
+                    have[k] = 0u;
+                    if (i < left) {
+                        const uint32_t l = loads[i];
+                        x[k] = *reinterpret_cast<const Float4U *>(sorted + (l >> 2));
+                        have[k] = (l & 3u) + 1u;
+                    }
+                }
+#pragma unroll
+                for (uint32_t k = 0; k < kBsQuads; ++k) {
+                    f0[4 * k] = x[k].x - base;
+                    f0[4 * k + 1] = have[k] > 1u ? x[k].y - base : 0.0f;
+                    f0[4 * k + 2] = have[k] > 2u ? x[k].z - base : 0.0f;
+                    f0[4 * k + 3] = have[k] > 3u ? x[k].w - base : 0.0f;
+                    valid += have[k];
+                }
+                if (direct) {
+                    const uint32_t all = wave_sum_u32(valid);
+                    if (left <= kBsThreads) bucket_batch<1>(f0, all, base, nsum, sh, lane);
+                    else bucket_batch<4>(f0, all, base, nsum, sh, lane);
+                } else {
+                    const float unit = __uint_as_float((uint32_t)(127 - at.a) << 23);
+                    const ClassArgs cl(classes[cls], base);
+#pragma unroll
+                    for (uint32_t k = 0; k < kBsQuads; ++k) {
+                        uint32_t d[4], v[4];
+#pragma unroll
+                        for (uint32_t e = 0; e < 4u; ++e) {
+                            d[e] = (uint32_t)(fabsf(f0[4u * k + e]) * unit);
+                            v[e] = sh.start[d[e] >> (p.shift - 8u)];
+                        }
+#pragma unroll
+                        for (uint32_t e = 0; e < 4u; ++e) {
+                            if (e < have[k]) {
+                                while (v[e] < ncut && sh.cut[v[e]] <= d[e]) ++v[e];
+                                const uint32_t r = cls == 0u ? d[e] : (uint32_t)fabs(cl.offset(base + f0[4u * k + e]));
+                                atomicAdd(reinterpret_cast<unsigned long long *>(&sh.nf[v[e]]), (1ull << 40) + r);
+                                atomicAdd(reinterpret_cast<unsigned long long *>(&sh.iq[v[e]]), (unsigned long long)r * r);
+                            }
+                        }
+                        asm volatile("" ::: "memory");   // a load at a time: registers
+                    }
+                }
+            }
+            __syncthreads();
+            if (!direct) {
+                // sums from each cut on: a suffix scan, three intervals a lane, from the last interval down
+                constexpr uint32_t pl = (kBkCutCap + 1 + kBsThreads - 1) / kBsThreads;
+                uint64_t nf[pl], iq[pl], snf = 0u, sq = 0u;
+#pragma unroll
+                for (uint32_t i = 0; i < pl; ++i) {
+                    const uint32_t v = tid * pl + i;   // counted from the end
+                    nf[i] = v < cuts1 ? sh.nf[ncut - v] : 0u;
+                    iq[i] = v < cuts1 ? sh.iq[ncut - v] : 0u;
+                    snf += nf[i];
+                    sq += iq[i];
+                }
+                uint64_t anf = snf, aq = sq;
+#pragma unroll
+                for (uint32_t o = 1; o < (uint32_t)kWave; o <<= 1) {
+                    const uint64_t unf = shfl_up_u64(anf, o), uq = shfl_up_u64(aq, o);
+                    if (lane >= o) {
+                        anf += unf;
+                        aq += uq;
+                    }
+                }
+                if (lane == (uint32_t)kWave - 1u) {
+                    sh.wave_nf[wave] = anf;
+                    sh.wave_q[wave] = aq;
+                }
+                __syncthreads();
+                anf -= snf;
+                aq -= sq;
+                for (uint32_t w = 0; w < wave; ++w) {
+                    anf += sh.wave_nf[w];
+                    aq += sh.wave_q[w];
+                }
+#pragma unroll
+                for (uint32_t i = 0; i < pl; ++i) {
+                    const uint32_t v = tid * pl + i;
+                    anf += nf[i];
+                    aq += iq[i];
+                    if (v < cuts1) {
+                        sh.nf[ncut - v] = anf;
+                        sh.iq[ncut - v] = aq;
+                    }
+                }
+                __syncthreads();
+            }
+            // the candidate's pieces (of the item's class)
+            if (tid < a.ncand) {
+                const double sgn = (at.base >> 31) ? -1.0 : 1.0;
+                double mine = 0.0;
+                for (;;) {
+                    if (direct || pc.cls == cls) {
+                        double n, f, q;
+                        if (direct) {
+                            uint32_t ni = sh.n[pc.from];
+                            uint64_t fi = sh.f[pc.from], qi = sh.q[pc.from];
+                            if (pc.to != kBkNone) {
+                                ni -= sh.n[pc.to];
+                                fi -= sh.f[pc.to];
+                                qi -= sh.q[pc.to];
+                            }
+                            n = (double)ni;
+                            f = (double)(long long)fi;
+                            q = (double)qi;
+                        } else {
+                            uint64_t nfi = sh.nf[pc.from], qi = sh.iq[pc.from];
+                            if (pc.to != kBkNone) {
+                                nfi -= sh.nf[pc.to];
+                                qi -= sh.iq[pc.to];
+                            }
+                            n = (double)(nfi >> 40);
+                            f = sgn * (double)(nfi & ((1ull << 40) - 1ull));
+                            q = (double)qi;
+                        }
+                        mine += piece_sum(n, f, q, pc.e) * pow2(2 * (at.a + (int)pc.dk));
+                    }
+                    if (pc.next == kBkNone) break;
+                    pc = a.further[further + pc.next - kBkCands];
+                }
+                total += mine;
+            }
+            __syncthreads();   // runs and sums are reused
+        }
+        __syncthreads();
+    }
+    if (tid < a.ncand) a.partials[(uint64_t)tid * a.columns + blockIdx.x] = total;
+}
+
+// ---- launch -----------------------------------------------------------------------------------------
+
+#ifndef QP_BUCKET_MIN_N
+#define QP_BUCKET_MIN_N ((1ull << 21) + 1ull)
+#endif
+
+bool bucket_search_eligible(uint64_t n, int dtype, const SearchPlan &plan)
+{
+    return plan.bucket_room && dtype == QP_F32 && n >= QP_BUCKET_MIN_N && plan.bits <= 8u && plan.stride <= 1u &&
+           plan.t_steps + 1u <= kBkCands;
+}
+
+size_t bucket_search_end(uint64_t n, size_t at) { return n >= QP_BUCKET_MIN_N ? bucket_layout(n, at).end : at; }
+
+BucketSetup bucket_setup_args(uint64_t n, const SearchPlan &plan, void *ws)
+{
+    const BucketLayout l = bucket_layout(n, plan.bucket_at);
+    char *w = static_cast<char *>(ws);
+    return BucketSetup{reinterpret_cast<BucketPlan *>(w + l.plan), reinterpret_cast<uint32_t *>(w + l.totals),
+                       l.segments * (kBkKeys + 1u), plan.bits <= 3u ? kBkWidth / 4u : plan.bits <= 4u ? kBkWidth / 2u : kBkWidth};
+}
+
+hipError_t launch_bucket_search(const void *x, uint64_t n, const SearchPlan &plan, void *ws, const uint32_t **fallback, hipStream_t s)
+{
+    const BucketLayout l = bucket_layout(n, plan.bucket_at);
+    char *w = static_cast<char *>(ws);
+    BucketArgs a;
+    a.tile = l.tile;
+    a.ncand = plan.t_steps + 1u;
+    a.plan = reinterpret_cast<BucketPlan *>(w + l.plan);
+    a.table = reinterpret_cast<uint16_t *>(w + l.table);
+    a.sorted = reinterpret_cast<float *>(w + l.sorted);
+    a.cands = reinterpret_cast<const Cand *>(w + kOffCands);
+    a.recs = reinterpret_cast<BucketRec *>(w + l.recs);
+    a.shapes = reinterpret_cast<uint32_t *>(w + l.shapes);
+    a.cuts = reinterpret_cast<uint32_t *>(w + l.cuts);
+    a.classes = reinterpret_cast<BucketClass *>(w + l.classes);
+    a.pieces = reinterpret_cast<BucketPiece *>(w + l.pieces);
+    a.further = reinterpret_cast<BucketPiece *>(w + l.further);
+    a.columns = kBkColumns * l.segments;
+    *fallback = &a.plan->fallback;
+    const uint64_t step = (uint64_t)l.tile * l.tiles;
+    for (uint32_t seg = 0; seg < l.segments; ++seg) {
+        const uint64_t from = seg * step;
+        a.x = static_cast<const float *>(x) + from;
+        a.n = n - from < step ? n - from : step;
+        a.tiles = ceil_div_u64(a.n, l.tile);
+        a.totals = reinterpret_cast<uint32_t *>(w + l.totals) + (size_t)seg * kBkKeys;
+        a.zeros = reinterpret_cast<uint32_t *>(w + l.totals) + (size_t)l.segments * kBkKeys + seg;
+        a.partials = reinterpret_cast<double *>(w + l.partials) + (size_t)seg * kBkColumns;
+        a.first_segment = seg == 0 ? 1u : 0u;
+        hipLaunchKernelGGL(k_bucket_sort, dim3(a.tiles), dim3(kBkThreads), 0, s, a);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_bucket_sum, dim3(kBkColumns), dim3(kBsThreads), 0, s, a);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return launch_search_pick(reinterpret_cast<const double *>(w + l.partials), a.columns, a.ncand, n, ws,
+                              reinterpret_cast<double *>(w + kOffScores), *fallback, s);
+}
+
+}  // namespace qp

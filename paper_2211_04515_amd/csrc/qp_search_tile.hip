@@ -177,8 +177,10 @@ __global__ __launch_bounds__(kPkThreadsPick) void k_search_pick(const double *__
                                                                 double *__restrict__ scores, Ctl *__restrict__ ctl,
                                                                 qp_search_result_t *__restrict__ res,
                                                                 qp_qparams_t *__restrict__ best, uint64_t n,
-                                                                double *__restrict__ scores_by_j)
+                                                                double *__restrict__ scores_by_j,
+                                                                const uint32_t *__restrict__ skip)
 {
+    if (skip && *skip) return;   // nothing was scored
     __shared__ double sh[kStMaxCands];
     __shared__ uint32_t sh_flag;
     const uint32_t tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
@@ -204,6 +206,16 @@ __global__ __launch_bounds__(kPkThreadsPick) void k_search_pick(const double *__
     if (wave != 0) return;
     const uint32_t bi = first_min_wave(sh, ncand, lane);
     if (lane == 0) write_search_result(ctl, sh, ncand, bi, n, scores_by_j, res, best);
+}
+
+hipError_t launch_search_pick(const double *partials, uint32_t nblocks, uint32_t count, uint64_t n, void *ws, double *scores_list,
+                              const uint32_t *skip, hipStream_t s)
+{
+    char *w = static_cast<char *>(ws);
+    hipLaunchKernelGGL(k_search_pick, dim3(count), dim3(kPkThreadsPick), 0, s, partials, nblocks, scores_list,
+                       reinterpret_cast<Ctl *>(w + kOffCtl), reinterpret_cast<qp_search_result_t *>(w + kOffResult),
+                       reinterpret_cast<qp_qparams_t *>(w + kOffQParams), n, reinterpret_cast<double *>(w + kOffScores), skip);
+    return hipGetLastError();
 }
 
 static uint32_t plan_max_count(const SearchPlan &plan)
@@ -264,10 +276,7 @@ static hipError_t launch_tile_sweep(const void *x, uint64_t n, int dtype, const 
     else hipLaunchKernelGGL(k_search_tile<QP_BF16>, dim3(blocks), dim3(kStThreads), 0, s, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_search_pick, dim3(count), dim3(kPkThreadsPick), 0, s, a.partials, blocks, scores_list, a.ctl,
-                       reinterpret_cast<qp_search_result_t *>(w + kOffResult),
-                       reinterpret_cast<qp_qparams_t *>(w + kOffQParams), n, a.scores_by_j);
-    return hipGetLastError();
+    return launch_search_pick(a.partials, blocks, count, n, ws, scores_list, nullptr, s);
 }
 
 hipError_t launch_tile_search(const void *x, uint64_t n, int dtype, const SearchPlan &plan, const qp_stats_t *st,

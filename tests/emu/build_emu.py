@@ -1,10 +1,10 @@
 """TEST INFRASTRUCTURE ONLY: compiles the library's kernel sources against the CPU stand-in for the HIP
 runtime (tests/emu/hip/hip_runtime.h) with AddressSanitizer and UBSan, into tests/emu/_build/<tag>/emu_driver.
 
-Four builds: "default" (the library's own size thresholds: small tensors take the tile search),
+Five builds: "default" (the library's own size thresholds: small tensors take the tile search),
 "streaming" (thresholds lowered so that tiny tensors take the streaming search, for bf16 the value
 table, and from 2048 elements on the large-tensor forms of quantize+pack and unpack+dequantize), "pairs" (the rule in element-candidate pairs lowered: bf16 sweeps of tiny tensors
-take a value table behind the streaming statistics) and "streaming_c2f" (as "streaming", plus the coarse-to-fine sweeps on the streaming kernel, which the
+take a value table behind the streaming statistics), "bucket" (tiny tensors are searched by value buckets) and "streaming_c2f" (as "streaming", plus the coarse-to-fine sweeps on the streaming kernel, which the
 library itself never launches).  Returns None when no host clang++ with C++20 is available."""
 from __future__ import annotations
 
@@ -23,6 +23,9 @@ VARIANTS = {
                   "-DQP_LARGE_FORMS_MIN_N=2048"],
     # bf16 sweeps below the value table's own size on a table that the search builds after two-pass statistics
     "pairs": ["-DQP_VALUE_TABLE_MIN_PAIRS=20000", "-DQP_VALUE_TABLE_SEARCH_MIN_N=1000"],
+    # the search by value buckets on tiny tensors, a few hundred buckets
+    "bucket": ["-DQP_TILE_SEARCH_MAX_N=0", "-DQP_BUCKET_MIN_N=1000", "-DQP_BUCKET_TILES=3", "-DQP_BUCKET_SUM_BLOCKS=2",
+               "-DQP_BUCKET_WIDTH=512", "-DQP_BUCKET_DEPTH=0x1p-3", "-DQP_BUCKET_SEGMENT=2500u", "-DQP_SEARCH_FILL_BLOCKS=8"],
     # as "streaming", and a coarse-to-fine search runs its two sweeps on the streaming kernel: the sequence that
     # the library refuses because its only GPU run faulted (the macro exists for this build alone)
     "streaming_c2f": ["-DQP_TILE_SEARCH_MAX_N=0", "-DQP_VALUE_TABLE_MIN_N=4096", "-DQP_SEARCH_FILL_BLOCKS=8",

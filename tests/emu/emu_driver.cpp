@@ -6,10 +6,11 @@
 
 #include <sys/mman.h>
 
+#include <algorithm>
 #include <string>
 #include <vector>
 
-#include "qp_common.hpp"
+#include "qp_bucket.hpp"
 
 namespace emu { extern int g_occupancy, g_cus; void *shared_alloc(size_t); }
 
@@ -128,6 +129,15 @@ int main(int argc, char **argv)
     // what the fused sender path left in its own workspace (its search may run a different kernel sequence)
     dump(out, "scores2.bin", (const char *)ws2 + qp_ws_offset(QP_WS_SCORES), ((size_t)cfg.t_steps + 1) * 8);
     dump(out, "result2.bin", (const char *)ws2 + qp_ws_offset(QP_WS_RESULT), sizeof res);
+    // what the search by value buckets made of the tensor: its plan, where the workspace holds one
+    {
+        const size_t cols = std::max(qp::search_blocks(n), qp::tile_search_blocks(n)), rows = std::max(cfg.t_steps + 1u, 128u);
+        const size_t least = qp::kOffSearchPart + cols * rows * sizeof(double);
+        qp::BucketPlan plan;
+        memset(&plan, 0xff, sizeof plan);
+        if (wsb > least) memcpy(&plan, (const char *)ws + qp::bucket_layout(n, least).plan, sizeof plan);
+        dump(out, "plan.bin", &plan, sizeof plan);
+    }
     dump(out, "packed.bin", packed, pkb);
     dump(out, "y.bin", y, n * 4);
     char line[256];

@@ -27,6 +27,18 @@ uint32_t exchange(uint32_t v, int src_lane, int ctrl, int xor_mask)
     return buf[from];
 }
 
+uint64_t ballot(bool p)
+{
+    const unsigned tid = t_threadIdx.x, wave = tid / 64, lane = tid % 64;
+    const unsigned par = (t_opcount++) & 1u;
+    uint32_t *buf = &g_ctx->xbuf[(wave * 2 + par) * 64];
+    buf[lane] = p ? 1u : 0u;
+    g_ctx->wave_bar[wave]->arrive_and_wait();
+    uint64_t m = 0;
+    for (unsigned l = 0; l < 64; ++l) m |= (uint64_t)buf[l] << l;
+    return m;
+}
+
 // One block: a thread per lane, barriers for the block and for each wave.
 static void run_block(unsigned bx, unsigned by, unsigned nthreads, const std::function<void()> &fn)
 {

@@ -23,6 +23,7 @@
 #define __global__
 #define __device__
 #define __host__
+#define __noinline__ __attribute__((noinline))
 #define __forceinline__ inline __attribute__((always_inline))
 #define __shared__ static
 #define __launch_bounds__(...)
@@ -69,6 +70,7 @@ void know(void *base, size_t bytes, hipMemoryType type, int device, bool unreach
 const Allocation *find(const void *p);
 hipError_t copy(void *d, const void *s, size_t n);
 uint32_t exchange(uint32_t v, int src_lane_or_minus1, int ctrl, int xor_mask);
+uint64_t ballot(bool p);
 }  // namespace emu
 
 #define threadIdx emu::t_threadIdx
@@ -118,6 +120,8 @@ static inline int __syncthreads_and(int p)
 }
 
 static inline uint32_t atomicAdd(uint32_t *p, uint32_t v) { return __atomic_fetch_add(p, v, __ATOMIC_SEQ_CST); }
+static inline unsigned long long atomicAdd(unsigned long long *p, unsigned long long v) { return __atomic_fetch_add(p, v, __ATOMIC_SEQ_CST); }
+static inline uint32_t atomicOr(uint32_t *p, uint32_t v) { return __atomic_fetch_or(p, v, __ATOMIC_SEQ_CST); }
 #define __builtin_amdgcn_fence(order, scope) ((void)0)
 
 static inline float __uint_as_float(uint32_t u) { float f; memcpy(&f, &u, 4); return f; }
@@ -146,6 +150,13 @@ static inline double __shfl_xor(double v, int m, int)
     return __hiloint2double((int)hi, (int)lo);
 }
 static inline uint32_t __shfl_xor(uint32_t v, int m, int) { return emu::exchange(v, -1, -1, m); }
+static inline uint32_t __shfl_up(uint32_t v, unsigned d, int)
+{
+    const unsigned lane = threadIdx.x % 64;
+    return emu::exchange(v, (int)(lane < d ? lane : lane - d), -1, 0);
+}
+static inline uint64_t __ballot(int p) { return emu::ballot(p != 0); }   /* every lane of the wave takes part where the kernels use it */
+static inline int __popcll(uint64_t v) { return __builtin_popcountll(v); }
 
 template <typename T> static inline T min(T a, T b) { return b < a ? b : a; }
 template <typename T> static inline T max(T a, T b) { return a < b ? b : a; }

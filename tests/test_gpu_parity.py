@@ -1719,3 +1719,95 @@ def test_low_bits_only_policy(qp):
             else:
                 check_variant(qp, xf, st, bits, {}, 100, ws, res, q)
                 assert np.array_equal(packed.cpu().numpy(), orc.pack(orc.quantize(xf, oracle_q_from(q)), bits))
+
+
+# ---- the search by value buckets (large fp32 tensors, at most 8 bit) --------------------------------------
+LEAST_WORKSPACE = 1_384_960     # with no more than this the same call takes the streaming kernel (t <= 127, n above 2^21)
+
+
+def bucket_values(kind, n, g):
+    lap = lambda: torch.empty(n, device="cuda").exponential_(generator=g) * (torch.rand(n, device="cuda", generator=g) - 0.5).sign()
+    normal = lambda: torch.randn(n, device="cuda", generator=g)
+    if kind == "laplace":
+        return lap() * 0.5
+    if kind == "relu":            # half of the elements are zero, of either sign
+        x = normal()
+        return torch.where(x > 0, x, x * 0.0)
+    if kind == "gelu":
+        return torch.nn.functional.gelu(normal() * 1.5)
+    if kind == "offset":          # all in two binades, far from zero
+        return normal() + 60.0
+    if kind == "negative":        # one-sided
+        return -lap().abs() - 0.01
+    if kind == "steps":           # few distinct values, thresholds among them
+        return (lap() * 8).round() / 8
+    if kind == "spike":           # a third of the elements on one value, sorted blocks of others
+        x = lap()
+        x[n // 3: 2 * n // 3] = 0.3712
+        x[:n // 8] = x[:n // 8].sort()[0]
+        return x
+    if kind == "tiny":            # the middle of the exponent range's lower end, still normal
+        return lap() * 1e-24
+    if kind == "wide":            # spread over more binades than the buckets have
+        return torch.exp(torch.empty(n, device="cuda").uniform_(-30.0, 30.0, generator=g)) * normal().sign()
+    if kind == "subnormal":
+        return lap() * 1e-41
+    if kind == "nan":
+        x = lap()
+        x[n // 2] = float("nan")
+        return x
+    x = lap()
+    x[12345] = float("inf")
+    return x
+
+
+# (values, elements, bits, variant, t): at the rule's line, at whole and just more than whole tiles per compute unit, over a
+# segment's size; every bitwidth; values that crowd buckets, lie on thresholds or leave the buckets' range
+BUCKET_CASES = [("laplace", (1 << 21) + 1, 2, {}, 100), ("laplace", 9_699_328, 8, {}, 100), ("laplace", 9_699_329, 3, {}, 100),
+                ("gelu", (1 << 24) + 5, 4, {}, 100), ("gelu", 2_600_011, 8, {}, 127), ("gelu", 3_000_000, 2, {}, 100),
+                ("relu", 2_500_002, 2, {}, 100), ("relu", 4_000_003, 6, dict(clip=True), 100), ("offset", 2_300_007, 4, {}, 100),
+                ("offset", 2_300_007, 8, {}, 100), ("negative", 2_222_223, 6, {}, 50), ("negative", 2_222_223, 3, dict(dist=1), 13),
+                ("steps", 5_000_001, 2, {}, 100), ("steps", 2_400_000, 8, {}, 100), ("spike", 6_000_001, 4, {}, 100),
+                ("spike", 2_100_001, 8, dict(dist=2), 100), ("tiny", 2_222_222, 4, {}, 100), ("wide", 2_222_222, 4, {}, 100),
+                ("subnormal", 2_222_222, 4, {}, 20), ("nan", 2_222_222, 2, {}, 20), ("inf", 2_222_222, 2, {}, 20)]
+
+
+@pytest.mark.parametrize("kind,n,bits,v,t", BUCKET_CASES, ids=[f"{c[0]}_{c[1]}_k{c[2]}_t{c[4]}" for c in BUCKET_CASES])
+def test_bucket_search_equals_the_streaming_search(qp, kind, n, bits, v, t):
+    """The same call with room for the buckets and without: every score, the winner and its grid.  Both add the same squares in 64
+    bits, grouped differently: a few thousand partial sums of relative error 2^-53 each at most, 1e-12 in all."""
+    print(f"[case] buckets {kind} n={n} bits={bits} t={t}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + bits)
+    xd = bucket_values(kind, n, g)
+    cfg = variant_cfg(qp, v, t)
+    out = []
+    for room in (True, False, True):
+        ws = qp.alloc_workspace(n, cfg)
+        ws.fill_(0x5A)
+        if not room:
+            ws = ws[:LEAST_WORKSPACE]
+        qp.qp_stats_async(xd, ws)
+        qp.qp_dsaciq_search_async(xd, bits, ws, cfg)
+        torch.cuda.synchronize()
+        off = qp.qp_ws_offset(qp.QP_WS_SCORES)
+        rec, grid = qp.qp_ws_offset(qp.QP_WS_RESULT), qp.qp_ws_offset(qp.QP_WS_QPARAMS)
+        out.append((ws[off:off + 8 * (t + 1)].cpu().numpy().view(np.float64).copy(),
+                    qp.qp_search_result_t.from_buffer_copy(ws[rec:rec + 56].cpu().numpy().tobytes()),
+                    ws[grid:grid + 32].cpu().numpy().copy(),
+                    int(ws[LEAST_WORKSPACE + 4:LEAST_WORKSPACE + 8].cpu().numpy().view(np.uint32)[0]) if room else None))
+    (a, ra, qa, left), (b, rb, qb, _), (c, rc, qc, _) = out
+    assert left == (1 if kind in ("wide", "subnormal", "nan", "inf") else 0)   # found unsuitable on the device, or not
+    assert np.array_equal(np.isnan(a), np.isnan(b))
+    fin = np.isfinite(b)
+    assert np.allclose(a[fin], b[fin], rtol=REL_SCORE_PAIRWISE, atol=0.0) and np.array_equal(a[~fin & ~np.isnan(b)], b[~fin & ~np.isnan(b)])
+    assert np.array_equal(a, c, equal_nan=True) and np.array_equal(qa, qc)      # whatever order the sort put the elements in
+    if ra.j_star != rb.j_star:
+        assert abs(b[ra.j_star] - b[rb.j_star]) <= 1e-12 * b[rb.j_star]
+    else:
+        assert np.array_equal(qa, qb)
+    if kind == "laplace" and bits == 2:      # and the sum itself, at both ends of the sweep
+        st = qp.qp_stats(xd, qp.alloc_workspace(n, cfg))
+        x = xd.cpu().numpy()
+        for j in (0, t):
+            assert a[j] == pytest.approx(pairwise_sq_error(x, orc.search_candidate(oracle_stats_from(st), bits, t, n, j)), rel=REL_SCORE_PAIRWISE)

@@ -125,6 +125,8 @@ def small_input(kind, n):
         g = np.random.default_rng(n)
         x = np.where(g.random(n) < 0.9, np.abs(g.laplace(0.0, 0.5, size=n)), 10.0 ** g.uniform(-3, 38.5, size=n))
         return si.f32_to_bf16_bits(np.minimum(x, 3.3e38).astype(np.float32)) | np.uint16(0x8000)
+    if kind == "offset":      # all values in two binades
+        return (np.random.default_rng(n).standard_normal(n) * 0.8 + 60.0).astype(np.float32)
     if kind == "subnormal":   # the grid's reciprocal is infinite: the search's full clamp sequence
         return (np.random.default_rng(n).laplace(0.0, 1.0, size=n) * 1e-41).astype(np.float32)
     return si.make_config(kind, n=n)
@@ -178,9 +180,13 @@ STREAM_C2F_CASES = [("streaming_c2f", ("C3", 10_011, 2, dict(stride=10), 100)),
 RECORD_CASES = [("default", ("C3", 4_301, 4, dict(record=r), 1)) for r in ("in_x", "in_packed", "on_itself", "host", "peer")]
 RECORD_CASES += [("default", ("bf16", 9_001, 3, dict(record="in_x", conc=2, seed=s), 1)) for s in (1,)]
 RECORD_REFUSED = ("default", ("C3", 3_001, 4, dict(record="short"), 1))
+# The search by value buckets: both signs; two segments, tiles and parts of buckets in any order; all values in two binades, many
+# thresholds to a bucket; a tensor that it leaves to the streaming kernel
+BUCKET_CASES = [("bucket", c) for c in (("C1", 1_301, 2, {}, 20), ("C2", 3_001, 3, dict(conc=3), 13), ("offset", 2_601, 4, {}, 20),
+                                        ("subnormal", 2_003, 4, {}, 13))]
 ALL_CASES = ([("default", c) for c in TILE_CASES] + [("streaming", c) for c in STREAM_CASES] + [("streaming", REFUSED)] + ACIQ_ONLY
              + CONCURRENT_CASES + STREAM_C2F_CASES + RECORD_CASES + [RECORD_REFUSED]
-             + TABLE_STATS_CASES + PAIRS_CASES)
+             + TABLE_STATS_CASES + PAIRS_CASES + BUCKET_CASES)
 
 
 def case_id(tag, c):
@@ -204,8 +210,8 @@ def runs(drivers, tmp_path_factory):
         return case_id(tag, item[1]), (p, out_dir, x)
 
     with ThreadPoolExecutor(max_workers=6) as ex:
-        # the longest first: those that may count values, a thread per lane of 1024-lane blocks
-        return dict(ex.map(go, sorted(ALL_CASES, key=lambda a: (a[0] != "streaming", small_input(a[1][0], a[1][1]).dtype != np.uint16))))
+        # the longest first: those that sort or count values, a thread per lane of 1024-lane blocks
+        return dict(ex.map(go, sorted(ALL_CASES, key=lambda a: (a[0] != "bucket", a[0] != "streaming", small_input(a[1][0], a[1][1]).dtype != np.uint16))))
 
 
 WHOLE = [a for a in ALL_CASES if a[1] is not REFUSED and a not in ACIQ_ONLY and a is not RECORD_REFUSED]
@@ -221,6 +227,14 @@ def test_whole_path_on_the_emulation(runs, tag, case):
     r = read_outputs(p, out_dir)
     check_against_oracle(r, x, bits, t=t, dist=v.get("dist", 0), clip=bool(v.get("clip")), stride=v.get("stride", 1),
                          nbins=v.get("nbins", 2048))
+
+
+@pytest.mark.parametrize("tag,case", BUCKET_CASES, ids=[case_id(*a) for a in BUCKET_CASES])
+def test_the_bucket_build_takes_the_buckets(runs, tag, case):
+    p, out_dir, x = runs[case_id(tag, case)]
+    assert p.returncode == 0
+    plan = np.fromfile(os.path.join(out_dir, "plan.bin"), np.uint32)
+    assert plan[1] == (1 if case[0] == "subnormal" else 0)     # 1: left to the streaming kernel
 
 
 def test_emulation_refuses_what_the_library_refuses(runs):
