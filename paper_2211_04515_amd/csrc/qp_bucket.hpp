@@ -24,8 +24,7 @@ constexpr uint32_t kBkCands = 128;           // most candidates of a sweep
 #define QP_BUCKET_SEGMENT (1u << 24)         // elements that are sorted at a time (bounds the workspace: 67 MB)
 #endif
 constexpr uint32_t kBkTiles = QP_BUCKET_TILES, kBkWidth = QP_BUCKET_WIDTH, kBkSumBlocks = QP_BUCKET_SUM_BLOCKS;
-constexpr uint32_t kBkOtherBlocks = kBkTiles;
-constexpr uint32_t kBkColumns = kBkSumBlocks + kBkOtherBlocks;   // partial sums of a candidate per segment
+constexpr uint32_t kBkColumns = kBkSumBlocks;                    // partial sums of a candidate per segment
 constexpr uint32_t kBkRounds = 10;                               // 16-byte loads of a lane of a sorting block
 constexpr uint32_t kBkTileMax = 37u * kBkThreads;                // elements of a tile: 148 KB of LDS
 constexpr uint32_t kBkKeys = 2u * kBkWidth;                      // buckets of both signs
@@ -42,10 +41,15 @@ struct BucketPlan {
     uint32_t width;       // buckets of a sign
     uint32_t centre;      // the bucket of the mean: every candidate has a threshold there, so its elements count as outside
 };
-constexpr uint32_t kBkDirect = 24;    // most sums of a bucket that are formed in registers
-// One of them: a class's r(x) - r(base) over the elements with |x - base| >= from.  As they are (mode 0); by adding and taking
-// away m, a whole multiple of 2^k that puts the sum's last place there (mode 1); in 64 bits (mode 2).
-struct BucketSum { float from, m, mr, unit; float frac; int k2; uint32_t mode, pad; };
+constexpr uint32_t kBkDirect = 12;    // most sums of a bucket that are formed in registers: each takes a share of the bucket 1 us, however small
+// How the elements of a bucket are rounded for some candidates: r(x) = x / 2^k - frac to the nearest whole number, ties to the
+// even (or to the odd) one.  With f = x - base, a whole multiple of the bucket's last place 2^a, 2^k (r(x) - r(base)) is
+// ((f + add) + m) - m in 32 bits: add is what base / 2^k - frac is off r(base), in 2^k; m = 1.5 * 2^23 * 2^k or the next
+// multiple of 2^k, so that the sum's last place is 2^k and ties go to r(x)'s parity.  Class 0 of every bucket leaves the elements as
+// they are: add = m = 0, k = a.
+struct BucketClass { float add, m, unit, pad; };     // unit = 2^-k
+// A sum: of a class, over the elements with |f| >= from.
+struct BucketSum { float from, add, m, unit; };
 struct BucketRec {
     uint32_t cut, cls, piece;         // where the bucket's cuts, classes and further pieces start
     uint32_t ncut, ncls;
@@ -53,14 +57,11 @@ struct BucketRec {
     uint32_t pad[2];
     BucketSum sum[kBkDirect];
 };
-// How the elements of a bucket are rounded for some candidates: r(x) = x / 2^k - frac to the nearest whole number, ties to the
-// even (odd: to the odd) one.  Class 0 of every bucket leaves them as they are (k: the bucket's last place).
-struct BucketClass { float frac; int k2; };          // k2 = 2 k + odd
 // A candidate's constant piece of a bucket: sum of 4^k (r(x) - r(base) + e)^2, k the bucket's last place + dk, over the elements
 // from cut `from` on and before cut `to` (0: the bucket's start; kBkNone: its end; cuts count from 1).  Where the sums are formed in
 // registers, from and to are places in BucketRec::sum.
 struct BucketPiece { double e; uint8_t cls, dk; uint16_t from, to, next; };
-static_assert(sizeof(BucketPiece) == 16 && sizeof(BucketRec) == 800 && sizeof(BucketClass) == 8, "layout");
+static_assert(sizeof(BucketPiece) == 16 && sizeof(BucketRec) == 224 && sizeof(BucketClass) == 16 && sizeof(BucketSum) == 16, "layout");
 constexpr uint32_t kBkNone = 0xffffu;
 
 struct BucketLayout {

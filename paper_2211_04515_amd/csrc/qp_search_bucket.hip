@@ -32,7 +32,7 @@ struct BucketArgs {
     float *sorted;
     const Cand *cands;
     BucketRec *recs;
-    uint32_t *shapes;           // of a bucket: 0 or the number of its classes, see k_bucket_sum
+    uint32_t *shapes;           // of a bucket: the weight of its sums; summed by interval: classes << 16 | cuts
     uint32_t *cuts;
     BucketClass *classes;
     BucketPiece *pieces;        // a candidate's first piece of a bucket
@@ -77,20 +77,51 @@ __device__ __forceinline__ float bucket_level(const Cand &c, float x)
     return rintf(d * c.inv_scale);   // the short sequence: candidate_grid has shown that it needs no upper clamp
 }
 
+// What the sums cost, in tenths of a microsecond of a block of k_bucket_sum per batch of 4096 elements, with four blocks on a
+// compute unit: measured as 3.5 to 4 us with one sum, 6.5 to 7 with five of class 0, 9.4 with five of four classes, 12 with nine;
+// a class by interval 8 to 20, most of it the LDS atomics and more where few intervals hold most elements.  A few hundred elements take two thirds of a batch's sums.
+__device__ __forceinline__ uint32_t sum_weight(const BucketSum &m)
+{
+    return m.m == 0.0f ? (m.from > 0.0f ? 9u : 7u) : m.from > 0.0f ? 14u : 11u;
+}
+// A bucket (one class of it) of n elements: what a share of it costs at least, and the whole.  shape: see BucketArgs.
+__device__ __forceinline__ uint32_t bucket_least(uint32_t shape)
+{
+    const uint32_t low = shape & 0xffffu;
+    return shape >> 16 ? 70u + low / 4u : 30u + low * 2u / 3u;
+}
+__device__ __forceinline__ uint32_t bucket_cost(uint32_t n, uint32_t shape)
+{
+    const uint32_t low = shape & 0xffffu, batches = n / 64u;   // in 1/64
+    return shape >> 16 ? bucket_least(shape) + batches * 130u / 64u : max(bucket_least(shape), 30u + batches * (28u + low) / 64u);
+}
+
 // A bucket's lists while 128 lanes, one a candidate, fill them.
 constexpr uint32_t kBkKeyed = 128;    // classes that candidates share: place - a < 32, parity, frac 0 or a half
 constexpr uint32_t kBkAsIs = 255u;    // class 0
 static_assert(kBkKeyed + kBkOwnCap < kBkAsIs, "a class is a byte");
+struct BucketRounding { float frac; int k2; };   // k2 = 2 k + odd
 struct alignas(16) BucketLists {
-    uint32_t ncut, nown, npiece, over, ncls, need[2], pad;
+    uint32_t ncut, nown, npiece, over, ncls, need[2], weight;
     uint32_t cut[kBkCutCap];          // its place in the bucket << 9 | number, so that no two are equal
     uint16_t order[kBkCutCap];        // a cut's place among the sorted ones
     uint16_t keyed[kBkKeyed];         // 1: wanted; then its number
-    BucketClass own[kBkOwnCap];
+    BucketRounding own[kBkOwnCap];
     BucketPiece piece[kBkPieceCap];
 };
 
 __device__ inline double class_round(double x, double inv, double frac, double magic) { return (fma(x, inv, -frac) + magic) - magic; }
+
+// A class from how it rounds; f + add needs at most 2 + max(19, k - a) + 1 <= 24 bits.
+constexpr int kBkFurthest = 20;   // most of k - a
+__device__ inline BucketClass bucket_class(const BucketAt &t, const BucketRounding &c)
+{
+    const int k = c.k2 >> 1;
+    const double odd = (double)(c.k2 & 1), inv = pow2(-k), frac = (double)c.frac;
+    const double base = (double)t.value(0), r = class_round(base, inv, frac, 0x1.8p52 + odd);   // r(base)
+    const double parity = (r != 2.0 * floor(0.5 * r)) != (odd != 0.0) ? 1.0 : 0.0;
+    return BucketClass{(float)((fma(base, inv, -r) - frac) * pow2(k)), (float)((0x1.8p23 + parity) * pow2(k)), (float)inv, 0.0f};
+}
 
 // All pieces of one candidate in one bucket.
 __device__ inline void candidate_pieces(const BucketAt &t, const Cand &c, uint32_t j, BucketLists &l)
@@ -189,15 +220,15 @@ __device__ inline void candidate_pieces(const BucketAt &t, const Cand &c, uint32
                     cls = ((uint32_t)(k - t.a) * 2u + odd) * 2u + (frac == 0.5 ? 1u : 0u);
                     l.keyed[cls] = 1u;
                 } else {
-                    // x has at most 24 places below 2^k: what lies further down in frac only breaks ties
-                    const double f26 = floor(frac * 0x1p26);
-                    frac = f26 * 0x1p-26 + (frac * 0x1p26 != f26 ? 0x1p-27 : 0.0);
+                    // its digits below the bucket's last place only say on which side of a multiple of half of that it lies
+                    const double q = frac * pow2(k - t.a), below = floor(q), rest = q - below;
+                    frac = (below + (rest == 0.0 ? 0.0 : rest < 0.5 ? 0.25 : rest == 0.5 ? 0.5 : 0.75)) * pow2(t.a - k);   // a float up to kBkFurthest
                     const uint32_t i = atomicAdd(&l.nown, 1u);
                     if (i >= kBkOwnCap) over = true;
-                    else l.own[i] = BucketClass{(float)frac, 2 * k + (int)odd};
+                    else l.own[i] = BucketRounding{(float)frac, 2 * k + (int)odd};
                     cls = kBkKeyed + i;
                 }
-                if (k - t.a > 24) over = true;
+                if (k - t.a > kBkFurthest) over = true;
                 emit(class_round(base, pow2(-k), (double)(float)frac, magic) - fl, cls, k - t.a, from, end);
             }
             from = end;
@@ -222,12 +253,13 @@ __device__ inline void bucket_lists(const BucketArgs &a, const BucketPlan &p, Bu
         const uint32_t b = first + g * blocks;
         const bool live = b < 2u * p.width && b != p.centre;
         if (j == 0u) {
-            l.ncut = l.nown = l.npiece = l.over = l.need[0] = l.need[1] = 0u;
+            l.ncut = l.nown = l.npiece = l.over = l.need[0] = l.need[1] = l.weight = 0u;
             l.ncls = 1u;   // class 0
         }
         l.keyed[j] = 0u;
         __syncthreads();
         const BucketAt t = bucket_at(p, live ? b : 0u);
+        auto keyed_class = [&](uint32_t i) { return BucketRounding{(i & 1u) ? 0.5f : 0.0f, 2 * (t.a + (int)(i >> 2)) + (int)((i >> 1) & 1u)}; };
         if (live && has) candidate_pieces(t, c, j, l);
         __syncthreads();
         const uint32_t nc = min(l.ncut, kBkCutCap), nown = min(l.nown, kBkOwnCap), np = min(l.npiece, kBkPieceCap - kBkCands);
@@ -263,9 +295,9 @@ __device__ inline void bucket_lists(const BucketArgs &a, const BucketPlan &p, Bu
         if (live && !l.over) {
             for (uint32_t i = j; i < nc; i += kBkCands) a.cuts[at_cut + l.order[i]] = l.cut[i] >> 9;
             BucketClass *cls = a.classes + at_cls;
-            if (j == 0u) cls[0] = BucketClass{0.0f, 2 * t.a};
-            if (want) cls[number] = BucketClass{(j & 1u) ? 0.5f : 0.0f, 2 * (t.a + (int)(j >> 2)) + (int)((j >> 1) & 1u)};
-            for (uint32_t i = j; i < nown; i += kBkCands) cls[shared + i] = l.own[i];
+            if (j == 0u) cls[0] = BucketClass{0.0f, 0.0f, __uint_as_float((uint32_t)(127 - t.a) << 23), 0.0f};
+            if (want) cls[number] = bucket_class(t, keyed_class(j));
+            for (uint32_t i = j; i < nown; i += kBkCands) cls[shared + i] = bucket_class(t, l.own[i]);
             for (uint32_t i = j; i < kBkCands + np; i += kBkCands) {
                 if (i < kBkCands && !has) continue;
                 BucketPiece &q = l.piece[i];
@@ -284,7 +316,8 @@ __device__ inline void bucket_lists(const BucketArgs &a, const BucketPlan &p, Bu
         }
         __syncthreads();
         const uint64_t need = (uint64_t)l.need[0] | ((uint64_t)l.need[1] << 32);
-        const uint32_t nsum = few && __popcll(need) <= (int)kBkDirect ? (uint32_t)__popcll(need) : 0u;
+        // a sum in registers costs 5 to 20, a class by interval 100 (bucket_cost)
+        const uint32_t nsum = few && __popcll(need) <= (int)min(kBkDirect, 8u * ncls) ? (uint32_t)__popcll(need) : 0u;
         if (live && !l.over) {
             auto place = [&](uint32_t s) { return (uint16_t)__popcll(need & ((1ull << s) - 1ull)); };
             for (uint32_t i = j; i < kBkCands + np; i += kBkCands) {
@@ -300,30 +333,22 @@ __device__ inline void bucket_lists(const BucketArgs &a, const BucketPlan &p, Bu
             BucketRec &r = a.recs[b];
             if (nsum && j < 64u && (need >> j & 1ull)) {
                 const uint32_t k = j / (nc + 1u), cut = j % (nc + 1u);
-                BucketSum m{0.0f, 0.0f, 0.0f, __uint_as_float((uint32_t)(127 - t.a) << 23), 0.0f, 2 * t.a, 0u, 0u};
+                BucketSum m{0.0f, 0.0f, 0.0f, __uint_as_float((uint32_t)(127 - t.a) << 23)};
                 for (uint32_t i = 0; i < nc; ++i)
                     if (cut == (uint32_t)l.order[i] + 1u) m.from = fabsf(t.value(l.cut[i] >> 9) - t.value(0));   // exact: one binade
                 if (k) {
-                    BucketClass c{0.0f, 0};
-                    if (k >= shared) c = l.own[k - shared];
+                    BucketRounding how{0.0f, 0};
+                    if (k >= shared) how = l.own[k - shared];
                     else
                         for (uint32_t i = 0; i < kBkKeyed; ++i)
-                            if (l.keyed[i] == k) c = BucketClass{(i & 1u) ? 0.5f : 0.0f, 2 * (t.a + (int)(i >> 2)) + (int)((i >> 1) & 1u)};
-                    const int e = c.k2 >> 1;
-                    m.frac = c.frac;
-                    m.k2 = c.k2;
-                    m.mode = 2u;
-                    m.unit = (float)pow2(-e);
-                    if (c.frac == 0.0f && e <= 90) {
-                        const double b = rint((double)t.value(0) * pow2(-e));   // the base in whole 2^e
-                        double w = ((t.base >> 31) ? -0x1.8p23 : 0x1.8p23) - b;
-                        if ((w != 2.0 * floor(0.5 * w)) != ((c.k2 & 1) != 0)) w += 1.0;   // ties go to its parity
-                        m.m = (float)(w * pow2(e));
-                        m.mr = t.value(0) + m.m;
-                        m.mode = 1u;
-                    }
+                            if (l.keyed[i] == k) how = keyed_class(i);
+                    const BucketClass c = bucket_class(t, how);
+                    m.add = c.add;
+                    m.m = c.m;
+                    m.unit = c.unit;
                 }
                 r.sum[place(j)] = m;
+                atomicAdd(&l.weight, sum_weight(m));
             }
             if (j == 0u) {
                 r.cut = at_cut;
@@ -332,10 +357,10 @@ __device__ inline void bucket_lists(const BucketArgs &a, const BucketPlan &p, Bu
                 r.ncut = nc;
                 r.ncls = ncls;
                 r.nsum = nsum;
-                a.shapes[b] = nsum ? 0u : ncls;
             }
         }
         __syncthreads();   // the lists are reused
+        if (live && j == 0u && !l.over) a.shapes[b] = nsum ? l.weight : ncls << 16 | nc;
     }
 }
 
@@ -482,7 +507,7 @@ constexpr int kBsThreads = 256;
 constexpr uint32_t kBsTiles = 512;         // most tiles of a segment
 constexpr uint32_t kBsQuads = 4;           // 4-element loads of a lane per batch
 constexpr uint32_t kBsPerLane = 4u * kBsQuads;
-constexpr uint32_t kBsPart = 3584;         // elements of a work item, about: a batch
+constexpr uint32_t kBsLoads = 1u << 18;    // most loads that are summed by interval at a time: n < 2^24, sum |f| < 2^40
 constexpr uint32_t kBsBatch = kBsThreads * kBsQuads;   // loads of a batch
 constexpr uint32_t kBsItems = 128;         // most work items that a block lists at a time
 
@@ -499,19 +524,6 @@ struct BucketSums {
     uint16_t start[257];                             // cuts at or below the start of each 1/256 of the bucket
 };
 
-struct ClassArgs {
-    double inv, frac, magic, ref;
-    __device__ ClassArgs(const BucketClass &c, float base)
-    {
-        const int k = c.k2 >> 1;
-        inv = pow2(-k);
-        frac = (double)c.frac;
-        magic = 0x1.8p52 + (double)(c.k2 & 1);
-        ref = class_round((double)base, inv, frac, magic);
-    }
-    __device__ __forceinline__ double offset(float x) const { return (fma((double)x, inv, -frac) + magic) - (magic + ref); }
-};
-
 // Values that the compiler must take as new: what it would otherwise work out once for all sums (64-bit copies) costs the
 // registers of a wave.
 __device__ __forceinline__ void opaque(float (&v)[kBsPerLane])
@@ -522,15 +534,21 @@ __device__ __forceinline__ void opaque(float (&v)[kBsPerLane])
 #endif
 }
 
+__device__ __forceinline__ void opaque(uint32_t &v)
+{
+#if defined(__AMDGCN__)
+    asm volatile("" : "+v"(v));
+#endif
+}
+
 // The sums that a bucket's pieces refer to, a batch of 4 NQ elements a lane, `valid` of the wave's.
 template <int NQ>
-__device__ __forceinline__ void bucket_batch(float (&f0)[kBsPerLane], uint32_t valid, float base, uint32_t nsum, BucketSums &sh,
+__device__ __forceinline__ void bucket_batch(float (&f0)[kBsPerLane], uint32_t valid, uint32_t nsum, BucketSums &sh,
                                              uint32_t lane)
 {
     for (uint32_t s = 0; s < nsum; ++s) {
         opaque(f0);
-        const float from = wave_uniform(sh.sum[s].from), unit = wave_uniform(sh.sum[s].unit);
-        const uint32_t mode = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.sum[s].mode);
+        const float from = wave_uniform(sh.sum[s].from), unit = wave_uniform(sh.sum[s].unit), m = wave_uniform(sh.sum[s].m);
         uint32_t n = valid;
         float fs = 0.0f;   // at most 2^10 elements below 2^20
         double q0 = 0.0, q1 = 0.0;
@@ -550,20 +568,16 @@ __device__ __forceinline__ void bucket_batch(float (&f0)[kBsPerLane], uint32_t v
 #pragma unroll
             for (int i = 0; i < 4 * NQ; ++i) n += (uint32_t)__popcll(__ballot(fabsf(f0[i]) >= from));
         }
-        if (mode == 0u) {
+        if (m == 0.0f) {
             if (from > 0.0f) sums([&](int i) { return fabsf(f0[i]) >= from ? f0[i] : 0.0f; });
             else sums([&](int i) { return f0[i]; });
-        } else if (mode == 1u) {
-            const float m = wave_uniform(sh.sum[s].m), mr = wave_uniform(sh.sum[s].mr);
-            if (from > 0.0f) sums([&](int i) { return fabsf(f0[i]) >= from ? ((base + f0[i]) + m) - mr : 0.0f; });
-            else sums([&](int i) { return ((base + f0[i]) + m) - mr; });
         } else {
-            const ClassArgs cl(BucketClass{sh.sum[s].frac, sh.sum[s].k2}, base);
-            sums([&](int i) { return fabsf(f0[i]) >= from ? (float)cl.offset(base + f0[i]) : 0.0f; });   // whole numbers
+            const float add = wave_uniform(sh.sum[s].add);
+            if (from > 0.0f) sums([&](int i) { return fabsf(f0[i]) >= from ? ((f0[i] + add) + m) - m : 0.0f; });
+            else sums([&](int i) { return ((f0[i] + add) + m) - m; });
         }
-        const float u = mode == 2u ? 1.0f : unit;
-        const int fi = (int)wave_sum_u32((uint32_t)(int)(fs * u));
-        const double qs = wave_sum(q0 + q1) * ((double)u * (double)u);
+        const int fi = (int)wave_sum_u32((uint32_t)(int)(fs * unit));
+        const double qs = wave_sum(q0 + q1) * ((double)unit * (double)unit);
         if (lane == 0) {
             atomicAdd(reinterpret_cast<unsigned long long *>(&sh.f[s]), (unsigned long long)(long long)fi);
             atomicAdd(reinterpret_cast<unsigned long long *>(&sh.q[s]), (unsigned long long)qs);
@@ -590,16 +604,15 @@ __device__ inline double piece_sum(double n, double f, double q, double e)
 
 __global__ __launch_bounds__(kBsThreads, 4) void k_bucket_sum(BucketArgs a)
 {
-    // the sums; before them, the work items' bounds
-    __shared__ __align__(16) uint32_t buffer[sizeof(BucketSums) / 4u > 2u * kBkKeys + 1u ? sizeof(BucketSums) / 4u : 2u * kBkKeys + 1u];
-    BucketSums &sh = *reinterpret_cast<BucketSums *>(buffer);
+    __shared__ BucketSums sh;
     const uint32_t tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
     const BucketPlan p = *a.plan;
     if (p.fallback) return;
     const uint32_t nbuckets = 2u * p.width;
-    double total = 0.0;   // of the lane's candidate
+    __shared__ double sh_total[kBkCands];   // of a candidate: kept here, not in registers
 
-    if (blockIdx.x < kBkOtherBlocks) {   // elements outside the buckets: one candidate a lane, two lanes a candidate
+    // ---- elements outside the buckets, a quarter of a tile's at a time: one candidate a lane, two lanes a candidate ----
+    {
         float *sh_v = reinterpret_cast<float *>(&sh);
         double *sh_half = reinterpret_cast<double *>(sh_v + 1024);
         static_assert(sizeof(BucketSums) >= 4096 + kBkCands * sizeof(double), "their place");
@@ -607,18 +620,19 @@ __global__ __launch_bounds__(kBsThreads, 4) void k_bucket_sum(BucketArgs a)
         Cand g{0.0f, 0.0f, 0.0f, 0.0f};
         if (c < a.ncand) g = a.cands[c];
         auto score = [&](float x) { return (double)(x - dequant_level(bucket_level(g, x), g.scale, g.lo)); };
-        double acc[2] = {0.0, 0.0};
+        double acc[2] = {0.0, 0.0}, total = 0.0;
         if (blockIdx.x == 0u && half == 0u) {   // all zeros have one value
             const double e = score(0.0f);
             total = (double)*a.zeros * e * e;
         }
-        for (uint32_t t = blockIdx.x; t < a.tiles; t += kBkOtherBlocks) {
-            const uint16_t *row = a.table + (uint64_t)t * kBkRow;
-            const uint32_t from = row[nbuckets], to = row[nbuckets + 1u];
+        for (uint32_t t = blockIdx.x; t < 4u * a.tiles; t += kBkSumBlocks) {
+            const uint16_t *row = a.table + (uint64_t)(t / 4u) * kBkRow;
+            const uint32_t start = row[nbuckets], len = row[nbuckets + 1u] - start;
+            const uint32_t from = start + len * (t % 4u) / 4u, to = start + len * (t % 4u + 1u) / 4u;
             for (uint32_t at = from; at < to; at += 1024u) {
                 const uint32_t nv = min(1024u, to - at), mid = nv / 8u * 4u;
                 __syncthreads();
-                for (uint32_t i = tid; i < nv; i += kBsThreads) sh_v[i] = a.sorted[(uint64_t)t * a.tile + at + i];
+                for (uint32_t i = tid; i < nv; i += kBsThreads) sh_v[i] = a.sorted[(uint64_t)(t / 4u) * a.tile + at + i];
                 __syncthreads();
                 const uint32_t end = half ? nv : mid;
                 uint32_t i = half ? mid : 0u;
@@ -638,309 +652,342 @@ __global__ __launch_bounds__(kBsThreads, 4) void k_bucket_sum(BucketArgs a)
         __syncthreads();
         if (half) sh_half[c] = total;
         __syncthreads();
-        if (!half && c < a.ncand) a.partials[(uint64_t)c * a.columns + blockIdx.x] = total + sh_half[c];
-        return;
+        if (!half) sh_total[c] = total + sh_half[c];
+        __syncthreads();   // their place is used again
     }
 
-    // ---- work items: a bucket is cut into parts by tile, and where it is summed by interval, by class as well ----
-    struct Item { uint16_t bucket, part, parts, cls; };
+    // ---- the block's share: the buckets lie end to end by what they cost, and a block takes a stretch of that.  A bucket, or a
+    // class of one that is summed by interval, is an item; of one that the stretch cuts the block takes a share of the tiles ----
+    struct Item { uint16_t bucket, cls, from, to; };   // tiles
     __shared__ Item sh_items[kBsItems];
-    __shared__ uint32_t sh_wave[kBsThreads / kWave][2];
+    __shared__ uint32_t sh_wave[kBsThreads / kWave][2], sh_first, sh_count;
+    __shared__ BucketPiece sh_piece[kBkCands];
     __shared__ uint32_t runs[kBsTiles], first_load[kBsTiles], loads[kBsBatch];
-    static_assert((kBkKeys & (kBkKeys - 1u)) == 0u && kBsItems <= (uint32_t)kBsThreads, "an item a lane");
     constexpr uint32_t per = (kBkKeys + kBsThreads - 1) / kBsThreads;
-    const uint32_t me = blockIdx.x - kBkOtherBlocks;
-    for (uint32_t first = me, items = first + 1u; first < items; first += kBsItems * kBkSumBlocks) {
-        // the block's items first, first + kBkSumBlocks, ...
+    static_assert(per * kBsThreads == kBkKeys && per % 4u == 0u, "16-byte loads");
+    uint32_t *sizes = reinterpret_cast<uint32_t *>(&sh);   // of a bucket or of each of its classes, where the sums will be
+    uint8_t *classes_of = reinterpret_cast<uint8_t *>(sizes + kBkKeys);
+    static_assert(sizeof(BucketSums) >= 5u * kBkKeys, "their place");
+    const uint32_t me = blockIdx.x;
+    for (uint32_t first = 0u, count = 1u; first < count; first += kBsItems) {
         {
-            uint32_t parts[per], s1 = 0u, s2 = 0u;   // of the lane's buckets; classes << 16 | parts
-            static_assert(per % 4u == 0u, "16-byte loads");
+            uint32_t s1 = 0u, s2 = 0u;   // of the lane's buckets: what they cost, items
+            uint32_t mine = tid * per;
+            opaque(mine);   // (else the addresses are kept from the kernel's start on, in registers that it does not have)
 #pragma unroll
             for (uint32_t k = 0; k < per; k += 4u) {
-                const uint4 u = reinterpret_cast<const uint4 *>(a.totals)[(tid * per + k) / 4u], v = reinterpret_cast<const uint4 *>(a.shapes)[(tid * per + k) / 4u];
+                const uint4 u = reinterpret_cast<const uint4 *>(a.totals)[(mine + k) / 4u], v = reinterpret_cast<const uint4 *>(a.shapes)[(mine + k) / 4u];
                 const uint32_t n[4] = {u.x, u.y, u.z, u.w}, shape[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
                 for (uint32_t i = 0; i < 4u; ++i) {
-                    const uint32_t b = tid * per + k + i;
+                    const uint32_t b = mine + k + i;
                     const bool used = b < nbuckets && b != p.centre;   // (the others have no shape)
-                    const uint32_t p1 = used ? min(n[i] / kBsPart + 1u, a.tiles) : 0u, c = used ? shape[i] : 0u;
-                    parts[k + i] = p1 | c << 16;
-                    if (c) s1 += p1 * c;
-                    else s2 += p1;
+                    const uint32_t ncls = used ? max(shape[i] >> 16, 1u) : 0u, size = used ? bucket_cost(n[i], shape[i]) : 0u;
+                    sizes[b] = size;
+                    classes_of[b] = (uint8_t)ncls;
+                    s1 += ncls * size;
+                    s2 += ncls;
                 }
             }
-            uint32_t p1 = s1, p2 = s2;
+            uint32_t c = s1, i0 = s2;
 #pragma unroll
             for (uint32_t o = 1; o < (uint32_t)kWave; o <<= 1) {
-                const uint32_t u1 = __shfl_up(p1, o, kWave), u2 = __shfl_up(p2, o, kWave);
+                const uint32_t u1 = __shfl_up(c, o, kWave), u2 = __shfl_up(i0, o, kWave);
                 if (lane >= o) {
-                    p1 += u1;
-                    p2 += u2;
+                    c += u1;
+                    i0 += u2;
                 }
             }
             if (lane == (uint32_t)kWave - 1u) {
-                sh_wave[wave][0] = p1;
-                sh_wave[wave][1] = p2;
+                sh_wave[wave][0] = c;
+                sh_wave[wave][1] = i0;
             }
+            if (tid == 0) sh_first = sh_count = 0u;
             __syncthreads();
-            uint32_t all1 = 0u, all2 = 0u;
+            uint32_t all = 0u;
+            c -= s1;
+            i0 -= s2;
             for (uint32_t w = 0; w < kBsThreads / kWave; ++w) {
                 if (w < wave) {
-                    p1 += sh_wave[w][0];
-                    p2 += sh_wave[w][1];
+                    c += sh_wave[w][0];
+                    i0 += sh_wave[w][1];
                 }
-                all1 += sh_wave[w][0];
-                all2 += sh_wave[w][1];
+                all += sh_wave[w][0];
             }
-            uint32_t i1 = p1 - s1, i2 = all1 + p2 - s2;   // the costly ones first
-            items = all1 + all2;
-            uint32_t *first_item = buffer;
-#pragma unroll
-            for (uint32_t k = 0; k < per; ++k) {
-                const uint32_t b = tid * per + k, c = parts[k] >> 16, n = parts[k] & 0xffffu;
-                if (b < kBkKeys) {
-                    first_item[b] = i1;
-                    first_item[kBkKeys + b] = i2;
+            const uint32_t begin = (uint32_t)((uint64_t)all * me / kBkSumBlocks), end = (uint32_t)((uint64_t)all * (me + 1u) / kBkSumBlocks);
+            // the item in which the stretch begins
+            if (c <= begin && begin < c + s1) {
+                uint32_t c1 = c, i1 = i0;
+#pragma unroll 1
+                for (uint32_t b = mine; b < mine + per; ++b) {
+                    const uint32_t ncls = classes_of[b], size = sizes[b];
+                    if (c1 <= begin && begin < c1 + ncls * size) sh_first = i1 + (begin - c1) / size;
+                    c1 += ncls * size;
+                    i1 += ncls;
                 }
-                if (c) i1 += n * c;
-                else i2 += n;
             }
-            if (tid == kBsThreads - 1u) first_item[2u * kBkKeys] = i2;
             __syncthreads();
-            const uint32_t i = first + tid * kBkSumBlocks;
-            if (tid < kBsItems && i < items) {
-                uint32_t lo = 0u, hi = 2u * kBkKeys;   // first_item[lo] <= i < first_item[hi]
-                while (hi - lo > 1u) {
-                    const uint32_t mid = (lo + hi) / 2u;
-                    if (first_item[mid] <= i) lo = mid;
-                    else hi = mid;
+            if (c < end && begin < c + s1) {
+#pragma unroll 1
+                for (uint32_t b = mine; b < mine + per && c < end; ++b) {
+                    const uint32_t ncls = classes_of[b], size = sizes[b];
+                    if (begin < c + ncls * size) {
+                        const uint32_t scrap = min(bucket_least(a.shapes[b]) / 2u, size / 2u);
+                        // a place in the stretch to a tile of the item that it lies in; no scraps
+                        auto tile_at = [&](uint32_t at, uint32_t from) -> uint32_t {
+                            if (at < from + scrap + 1u) return 0u;
+                            if (at + scrap >= from + size) return a.tiles;
+                            return (uint32_t)((double)a.tiles * (double)(at - from) / (double)size);
+                        };
+                        for (uint32_t cls = begin > c ? (begin - c) / size : 0u; cls < ncls && c + cls * size < end; ++cls) {
+                            const uint32_t at = c + cls * size, number = i0 + cls - sh_first, slot = number - first;   // (before this turn: wraps around)
+                            if (slot < kBsItems) sh_items[slot] = Item{(uint16_t)b, (uint16_t)cls, (uint16_t)tile_at(begin, at), (uint16_t)tile_at(end, at)};
+                            if (end <= at + size) sh_count = number + 1u;   // the last one
+                        }
+                    }
+                    c += ncls * size;
+                    i0 += ncls;
                 }
-                const uint32_t b = lo & (kBkKeys - 1u), ncls = lo < kBkKeys ? a.shapes[b] : 1u;
-                const uint32_t n = (first_item[lo + 1u] - first_item[lo]) / ncls, at = i - first_item[lo], cls = at / n;
-                sh_items[tid] = Item{(uint16_t)b, (uint16_t)(at - cls * n), (uint16_t)n, (uint16_t)cls};
             }
         }
         __syncthreads();
-        for (uint32_t item = 0; item < kBsItems && first + item * kBkSumBlocks < items; ++item) {
+        count = sh_count;
+        for (uint32_t item = 0; item < kBsItems && first + item < count; ++item) {
             auto uniform = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); };
-            const uint32_t b = uniform(sh_items[item].bucket), part = uniform(sh_items[item].part), parts = uniform(sh_items[item].parts);
-            const uint32_t cls = uniform(sh_items[item].cls);
-            const uint32_t t0 = a.tiles * part / parts, nruns = a.tiles * (part + 1u) / parts - t0;   // tiles <= 512
+            const uint32_t b = uniform(sh_items[item].bucket), cls = uniform(sh_items[item].cls);
+            const uint32_t last = uniform(sh_items[item].to);
             const BucketRec *rec = a.recs + b;
-            const uint32_t nsum = uniform(rec->nsum), ncut = uniform(rec->ncut), cuts1 = ncut + 1u;
-            const uint32_t further = uniform(rec->piece);
-            const bool direct = nsum != 0u;
-            const uint32_t *cuts = a.cuts + uniform(rec->cut);
-            const BucketClass *classes = a.classes + uniform(rec->cls);
-            if (tid < kBkDirect) sh.sum[tid] = rec->sum[tid];   // (what lies past nsum is not used)
-            const BucketAt at = bucket_at(p, b);
-            const float base = at.value(0);
-            BucketPiece pc{};
-            if (tid < a.ncand) pc = a.pieces[(uint64_t)b * kBkCands + tid];
-            // the runs, two a lane, and where their loads come in the item's list of loads
-            uint32_t nl[2], sum = 0u;
+            uint32_t t0 = uniform(sh_items[item].from), nruns = last - t0;   // tiles <= 512
+            while (t0 < last) {
+                const uint32_t nsum = uniform(rec->nsum), ncut = uniform(rec->ncut), cuts1 = ncut + 1u;
+                const uint32_t further = uniform(rec->piece);
+                const bool direct = nsum != 0u;
+                const uint32_t *cuts = a.cuts + uniform(rec->cut);
+                const BucketClass *classes = a.classes + uniform(rec->cls);
+                if (tid < kBkDirect) sh.sum[tid] = rec->sum[tid];   // (what lies past nsum is not used)
+                const BucketAt at = bucket_at(p, b);
+                const float base = at.value(0);
+                if (tid < a.ncand) sh_piece[tid] = a.pieces[(uint64_t)b * kBkCands + tid];   // (kept in LDS, not in registers)
+                // the runs, two a lane, and where their loads come in the item's list of loads
+                uint32_t nl[2], sum = 0u;
 #pragma unroll
-            for (uint32_t i = 0; i < 2u; ++i) {
-                const uint32_t t = 2u * tid + i;
-                nl[i] = 0u;
-                if (t < nruns) {
-                    const uint16_t *row = a.table + (uint64_t)(t0 + t) * kBkRow + b;
-                    const uint32_t from = row[0], len = (uint32_t)row[1] - from;
-                    runs[t] = from | (len << 16);
-                    nl[i] = (len + 3u) / 4u;
-                }
-                sum += nl[i];
-            }
-            static_assert(kBsTiles <= 2u * kBsThreads, "two runs a lane");
-            uint32_t up = sum;
-#pragma unroll
-            for (uint32_t o = 1; o < (uint32_t)kWave; o <<= 1) {
-                const uint32_t v = __shfl_up(up, o, kWave);
-                if (lane >= o) up += v;
-            }
-            if (lane == (uint32_t)kWave - 1u) sh_wave[wave][0] = up;
-            if (direct) {
-                if (tid < kBkDirect) {
-                    sh.n[tid] = 0u;
-                    sh.f[tid] = sh.q[tid] = 0u;
-                }
-            } else {
-                for (uint32_t i = tid; i < ncut; i += kBsThreads) sh.cut[i] = cuts[i];
-                for (uint32_t i = tid; i < cuts1; i += kBsThreads) sh.nf[i] = sh.iq[i] = 0u;
-            }
-            __syncthreads();
-            uint32_t total_loads = 0u;
-            for (uint32_t w = 0; w < kBsThreads / kWave; ++w) {
-                if (w < wave) up += sh_wave[w][0];
-                total_loads += sh_wave[w][0];
-            }
-            up -= sum;
-            if (2u * tid < nruns) first_load[2u * tid] = up;
-            if (2u * tid + 1u < nruns) first_load[2u * tid + 1u] = up + nl[0];
-            if (!direct) {
-                // by interval between cuts: first the cuts at or below each 1/256 of the bucket, a few steps on from there
-                for (uint32_t i = tid; i <= 256u; i += kBsThreads) {
-                    const uint32_t d = i << (p.shift - 8u);
-                    uint32_t l0 = 0u, h0 = ncut;   // cuts below l0 are <= d, cuts from h0 on are > d
-                    while (l0 < h0) {
-                        const uint32_t mid = (l0 + h0) / 2u;
-                        if (sh.cut[mid] <= d) l0 = mid + 1u;
-                        else h0 = mid;
+                for (uint32_t i = 0; i < 2u; ++i) {
+                    const uint32_t t = 2u * tid + i;
+                    nl[i] = 0u;
+                    if (t < nruns) {
+                        const uint16_t *row = a.table + (uint64_t)(t0 + t) * kBkRow + b;
+                        const uint32_t from = row[0], len = (uint32_t)row[1] - from;
+                        runs[t] = from | (len << 16);
+                        nl[i] = (len + 3u) / 4u;
                     }
-                    sh.start[i] = (uint16_t)l0;
+                    sum += nl[i];
                 }
-            }
-            uint32_t share = 0u;   // 2^share lanes list a run's loads
-            while (share < 6u && (nruns << (share + 1u)) <= (uint32_t)kBsThreads) ++share;
-            for (uint32_t batch = 0; batch < total_loads; batch += kBsBatch) {
-                __syncthreads();   // runs and their places are there; the last batch's list has been read
-                for (uint32_t r = tid >> share; r < nruns; r += (uint32_t)kBsThreads >> share) {
-                    const uint32_t run = runs[r], at0 = first_load[r], len = run >> 16, n4 = (len + 3u) / 4u;
-                    if (at0 + n4 <= batch || at0 >= batch + kBsBatch) continue;
-                    const uint32_t where = r * a.tile + (run & 0xffffu);
-                    uint32_t q = tid & ((1u << share) - 1u);
-                    if (at0 + q < batch) q += ((batch - at0 - q + (1u << share) - 1u) >> share) << share;
-                    for (; q < n4 && at0 + q < batch + kBsBatch; q += 1u << share)
-                        loads[at0 + q - batch] = (where + 4u * q) << 2 | min(len - 4u * q - 1u, 3u);   // where < 2^25
-                }
-                __syncthreads();
-                const uint32_t left = min(total_loads - batch, kBsBatch);
-                const float *sorted = a.sorted + (uint64_t)t0 * a.tile;
-                float f0[kBsPerLane];
-                uint32_t have[kBsQuads], valid = 0u;
-                Float4U x[kBsQuads];
-#pragma unroll
-                for (uint32_t k = 0; k < kBsQuads; ++k) {
-                    const uint32_t i = k * kBsThreads + tid;
-                    x[k] = Float4U{base, base, base, base};
-                    have[k] = 0u;
-                    if (i < left) {
-                        const uint32_t l = loads[i];
-                        x[k] = *reinterpret_cast<const Float4U *>(sorted + (l >> 2));
-                        have[k] = (l & 3u) + 1u;
-                    }
-                }
-#pragma unroll
-                for (uint32_t k = 0; k < kBsQuads; ++k) {
-                    f0[4 * k] = x[k].x - base;
-                    f0[4 * k + 1] = have[k] > 1u ? x[k].y - base : 0.0f;
-                    f0[4 * k + 2] = have[k] > 2u ? x[k].z - base : 0.0f;
-                    f0[4 * k + 3] = have[k] > 3u ? x[k].w - base : 0.0f;
-                    valid += have[k];
-                }
-                if (direct) {
-                    const uint32_t all = wave_sum_u32(valid);
-                    if (left <= kBsThreads) bucket_batch<1>(f0, all, base, nsum, sh, lane);
-                    else bucket_batch<4>(f0, all, base, nsum, sh, lane);
-                } else {
-                    const float unit = __uint_as_float((uint32_t)(127 - at.a) << 23);
-                    const ClassArgs cl(classes[cls], base);
-#pragma unroll
-                    for (uint32_t k = 0; k < kBsQuads; ++k) {
-                        uint32_t d[4], v[4];
-#pragma unroll
-                        for (uint32_t e = 0; e < 4u; ++e) {
-                            d[e] = (uint32_t)(fabsf(f0[4u * k + e]) * unit);
-                            v[e] = sh.start[d[e] >> (p.shift - 8u)];
-                        }
-#pragma unroll
-                        for (uint32_t e = 0; e < 4u; ++e) {
-                            if (e < have[k]) {
-                                while (v[e] < ncut && sh.cut[v[e]] <= d[e]) ++v[e];
-                                const uint32_t r = cls == 0u ? d[e] : (uint32_t)fabs(cl.offset(base + f0[4u * k + e]));
-                                atomicAdd(reinterpret_cast<unsigned long long *>(&sh.nf[v[e]]), (1ull << 40) + r);
-                                atomicAdd(reinterpret_cast<unsigned long long *>(&sh.iq[v[e]]), (unsigned long long)r * r);
-                            }
-                        }
-                        asm volatile("" ::: "memory");   // a load at a time: registers
-                    }
-                }
-            }
-            __syncthreads();
-            if (!direct) {
-                // sums from each cut on: a suffix scan, three intervals a lane, from the last interval down
-                constexpr uint32_t pl = (kBkCutCap + 1 + kBsThreads - 1) / kBsThreads;
-                uint64_t nf[pl], iq[pl], snf = 0u, sq = 0u;
-#pragma unroll
-                for (uint32_t i = 0; i < pl; ++i) {
-                    const uint32_t v = tid * pl + i;   // counted from the end
-                    nf[i] = v < cuts1 ? sh.nf[ncut - v] : 0u;
-                    iq[i] = v < cuts1 ? sh.iq[ncut - v] : 0u;
-                    snf += nf[i];
-                    sq += iq[i];
-                }
-                uint64_t anf = snf, aq = sq;
+                static_assert(kBsTiles <= 2u * kBsThreads, "two runs a lane");
+                uint32_t up = sum;
 #pragma unroll
                 for (uint32_t o = 1; o < (uint32_t)kWave; o <<= 1) {
-                    const uint64_t unf = shfl_up_u64(anf, o), uq = shfl_up_u64(aq, o);
-                    if (lane >= o) {
-                        anf += unf;
-                        aq += uq;
-                    }
+                    const uint32_t v = __shfl_up(up, o, kWave);
+                    if (lane >= o) up += v;
                 }
-                if (lane == (uint32_t)kWave - 1u) {
-                    sh.wave_nf[wave] = anf;
-                    sh.wave_q[wave] = aq;
+                if (lane == (uint32_t)kWave - 1u) sh_wave[wave][0] = up;
+                if (direct) {
+                    if (tid < kBkDirect) {
+                        sh.n[tid] = 0u;
+                        sh.f[tid] = sh.q[tid] = 0u;
+                    }
+                } else {
+                    for (uint32_t i = tid; i < ncut; i += kBsThreads) sh.cut[i] = cuts[i];
+                    for (uint32_t i = tid; i < cuts1; i += kBsThreads) sh.nf[i] = sh.iq[i] = 0u;
                 }
                 __syncthreads();
-                anf -= snf;
-                aq -= sq;
-                for (uint32_t w = 0; w < wave; ++w) {
-                    anf += sh.wave_nf[w];
-                    aq += sh.wave_q[w];
+                uint32_t total_loads = 0u;
+                for (uint32_t w = 0; w < kBsThreads / kWave; ++w) {
+                    if (w < wave) up += sh_wave[w][0];
+                    total_loads += sh_wave[w][0];
                 }
-#pragma unroll
-                for (uint32_t i = 0; i < pl; ++i) {
-                    const uint32_t v = tid * pl + i;
-                    anf += nf[i];
-                    aq += iq[i];
-                    if (v < cuts1) {
-                        sh.nf[ncut - v] = anf;
-                        sh.iq[ncut - v] = aq;
-                    }
+                if (!direct && total_loads > kBsLoads && nruns > 1u) {   // fewer tiles at a time
+                    nruns /= 2u;
+                    __syncthreads();
+                    continue;
                 }
-                __syncthreads();
-            }
-            // the candidate's pieces (of the item's class)
-            if (tid < a.ncand) {
-                const double sgn = (at.base >> 31) ? -1.0 : 1.0;
-                double mine = 0.0;
-                for (;;) {
-                    if (direct || pc.cls == cls) {
-                        double n, f, q;
-                        if (direct) {
-                            uint32_t ni = sh.n[pc.from];
-                            uint64_t fi = sh.f[pc.from], qi = sh.q[pc.from];
-                            if (pc.to != kBkNone) {
-                                ni -= sh.n[pc.to];
-                                fi -= sh.f[pc.to];
-                                qi -= sh.q[pc.to];
-                            }
-                            n = (double)ni;
-                            f = (double)(long long)fi;
-                            q = (double)qi;
-                        } else {
-                            uint64_t nfi = sh.nf[pc.from], qi = sh.iq[pc.from];
-                            if (pc.to != kBkNone) {
-                                nfi -= sh.nf[pc.to];
-                                qi -= sh.iq[pc.to];
-                            }
-                            n = (double)(nfi >> 40);
-                            f = sgn * (double)(nfi & ((1ull << 40) - 1ull));
-                            q = (double)qi;
+                up -= sum;
+                if (2u * tid < nruns) first_load[2u * tid] = up;
+                if (2u * tid + 1u < nruns) first_load[2u * tid + 1u] = up + nl[0];
+                if (!direct) {
+                    // by interval between cuts: first the cuts at or below each 1/256 of the bucket, a few steps on from there
+                    for (uint32_t i = tid; i <= 256u; i += kBsThreads) {
+                        const uint32_t d = i << (p.shift - 8u);
+                        uint32_t l0 = 0u, h0 = ncut;   // cuts below l0 are <= d, cuts from h0 on are > d
+                        while (l0 < h0) {
+                            const uint32_t mid = (l0 + h0) / 2u;
+                            if (sh.cut[mid] <= d) l0 = mid + 1u;
+                            else h0 = mid;
                         }
-                        mine += piece_sum(n, f, q, pc.e) * pow2(2 * (at.a + (int)pc.dk));
+                        sh.start[i] = (uint16_t)l0;
                     }
-                    if (pc.next == kBkNone) break;
-                    pc = a.further[further + pc.next - kBkCands];
                 }
-                total += mine;
+                uint32_t share = 0u;   // 2^share lanes list a run's loads
+                while (share < 6u && (nruns << (share + 1u)) <= (uint32_t)kBsThreads) ++share;
+                // a batch's loads are listed and requested before the sums of the batch before it
+                const float *sorted = a.sorted + (uint64_t)t0 * a.tile;
+                Float4U x[kBsQuads];
+                uint32_t have = 0u;   // elements of each, a byte
+                auto request = [&](uint32_t batch) {
+                    __syncthreads();   // runs and their places are there; the last batch's list has been read
+                    for (uint32_t r = tid >> share; r < nruns; r += (uint32_t)kBsThreads >> share) {
+                        const uint32_t run = runs[r], at0 = first_load[r], len = run >> 16, n4 = (len + 3u) / 4u;
+                        if (at0 + n4 <= batch || at0 >= batch + kBsBatch) continue;
+                        const uint32_t where = r * a.tile + (run & 0xffffu);
+                        uint32_t q = tid & ((1u << share) - 1u);
+                        if (at0 + q < batch) q += ((batch - at0 - q + (1u << share) - 1u) >> share) << share;
+                        for (; q < n4 && at0 + q < batch + kBsBatch; q += 1u << share)
+                            loads[at0 + q - batch] = (where + 4u * q) << 2 | min(len - 4u * q - 1u, 3u);   // where < 2^25
+                    }
+                    __syncthreads();
+                    have = 0u;
+#pragma unroll
+                    for (uint32_t k = 0; k < kBsQuads; ++k) {
+                        const uint32_t i = batch + k * kBsThreads + tid;
+                        x[k] = Float4U{base, base, base, base};
+                        if (i < total_loads) {
+                            const uint32_t l = loads[i - batch];
+                            x[k] = *reinterpret_cast<const Float4U *>(sorted + (l >> 2));
+                            have |= ((l & 3u) + 1u) << (8u * k);
+                        }
+                    }
+                };
+                for (uint32_t batch = 0; batch < total_loads; batch += kBsBatch) {
+                    request(batch);
+                    const uint32_t left = min(total_loads - batch, kBsBatch);
+                    float f0[kBsPerLane];
+                    uint32_t had[kBsQuads], valid = 0u;
+#pragma unroll
+                    for (uint32_t k = 0; k < kBsQuads; ++k) {
+                        had[k] = have >> (8u * k) & 0xffu;
+                        f0[4 * k] = x[k].x - base;
+                        f0[4 * k + 1] = had[k] > 1u ? x[k].y - base : 0.0f;
+                        f0[4 * k + 2] = had[k] > 2u ? x[k].z - base : 0.0f;
+                        f0[4 * k + 3] = had[k] > 3u ? x[k].w - base : 0.0f;
+                        valid += had[k];
+                    }
+                    if (direct) {
+                        const uint32_t all_valid = wave_sum_u32(valid);
+                        if (left <= kBsThreads) bucket_batch<1>(f0, all_valid, nsum, sh, lane);
+                        else bucket_batch<4>(f0, all_valid, nsum, sh, lane);
+                    } else {
+                        const float unit = __uint_as_float((uint32_t)(127 - at.a) << 23);
+                        const BucketClass &cl = classes[cls];
+                        const float add = wave_uniform(cl.add), m = wave_uniform(cl.m), per = wave_uniform(cl.unit);
+#pragma unroll
+                        for (uint32_t k = 0; k < kBsQuads; ++k) {
+                            uint32_t d[4], v[4];
+#pragma unroll
+                            for (uint32_t e = 0; e < 4u; ++e) {
+                                d[e] = (uint32_t)(fabsf(f0[4u * k + e]) * unit);
+                                v[e] = sh.start[d[e] >> (p.shift - 8u)];
+                            }
+#pragma unroll
+                            for (uint32_t e = 0; e < 4u; ++e) {
+                                if (e < had[k]) {
+                                    while (v[e] < ncut && sh.cut[v[e]] <= d[e]) ++v[e];
+                                    const uint32_t r = (uint32_t)(fabsf(((f0[4u * k + e] + add) + m) - m) * per);
+                                    atomicAdd(reinterpret_cast<unsigned long long *>(&sh.nf[v[e]]), (1ull << 40) + r);
+                                    atomicAdd(reinterpret_cast<unsigned long long *>(&sh.iq[v[e]]), (unsigned long long)r * r);
+                                }
+                            }
+                            asm volatile("" ::: "memory");   // a load at a time: registers
+                        }
+                    }
+                }
+                __syncthreads();
+                if (!direct) {
+                    // sums from each cut on: a suffix scan, three intervals a lane, from the last interval down
+                    constexpr uint32_t pl = (kBkCutCap + 1 + kBsThreads - 1) / kBsThreads;
+                    uint64_t nf[pl], iq[pl], snf = 0u, sq = 0u;
+#pragma unroll
+                    for (uint32_t i = 0; i < pl; ++i) {
+                        const uint32_t v = tid * pl + i;   // counted from the end
+                        nf[i] = v < cuts1 ? sh.nf[ncut - v] : 0u;
+                        iq[i] = v < cuts1 ? sh.iq[ncut - v] : 0u;
+                        snf += nf[i];
+                        sq += iq[i];
+                    }
+                    uint64_t anf = snf, aq = sq;
+#pragma unroll
+                    for (uint32_t o = 1; o < (uint32_t)kWave; o <<= 1) {
+                        const uint64_t unf = shfl_up_u64(anf, o), uq = shfl_up_u64(aq, o);
+                        if (lane >= o) {
+                            anf += unf;
+                            aq += uq;
+                        }
+                    }
+                    if (lane == (uint32_t)kWave - 1u) {
+                        sh.wave_nf[wave] = anf;
+                        sh.wave_q[wave] = aq;
+                    }
+                    __syncthreads();
+                    anf -= snf;
+                    aq -= sq;
+                    for (uint32_t w = 0; w < wave; ++w) {
+                        anf += sh.wave_nf[w];
+                        aq += sh.wave_q[w];
+                    }
+#pragma unroll
+                    for (uint32_t i = 0; i < pl; ++i) {
+                        const uint32_t v = tid * pl + i;
+                        anf += nf[i];
+                        aq += iq[i];
+                        if (v < cuts1) {
+                            sh.nf[ncut - v] = anf;
+                            sh.iq[ncut - v] = aq;
+                        }
+                    }
+                    __syncthreads();
+                }
+                // the candidate's pieces (of the item's class)
+                if (tid < a.ncand) {
+                    const double sgn = (at.base >> 31) ? -1.0 : 1.0;
+                    double mine = 0.0;
+                    BucketPiece pc = sh_piece[tid];
+                    for (;;) {
+                        if (direct || pc.cls == cls) {
+                            double n, f, q;
+                            if (direct) {
+                                uint32_t ni = sh.n[pc.from];
+                                uint64_t fi = sh.f[pc.from], qi = sh.q[pc.from];
+                                if (pc.to != kBkNone) {
+                                    ni -= sh.n[pc.to];
+                                    fi -= sh.f[pc.to];
+                                    qi -= sh.q[pc.to];
+                                }
+                                n = (double)ni;
+                                f = (double)(long long)fi;
+                                q = (double)qi;
+                            } else {
+                                uint64_t nfi = sh.nf[pc.from], qi = sh.iq[pc.from];
+                                if (pc.to != kBkNone) {
+                                    nfi -= sh.nf[pc.to];
+                                    qi -= sh.iq[pc.to];
+                                }
+                                n = (double)(nfi >> 40);
+                                f = sgn * (double)(nfi & ((1ull << 40) - 1ull));
+                                q = (double)qi;
+                            }
+                            mine += piece_sum(n, f, q, pc.e) * pow2(2 * (at.a + (int)pc.dk));
+                        }
+                        if (pc.next == kBkNone) break;
+                        pc = a.further[further + pc.next - kBkCands];
+                    }
+                    sh_total[tid] += mine;
+                }
+                __syncthreads();   // runs and sums are reused
+                t0 += nruns;
+                nruns = last - t0;
             }
-            __syncthreads();   // runs and sums are reused
         }
         __syncthreads();
     }
-    if (tid < a.ncand) a.partials[(uint64_t)tid * a.columns + blockIdx.x] = total;
+    if (tid < a.ncand) a.partials[(uint64_t)tid * a.columns + blockIdx.x] = sh_total[tid];
 }
 
 // ---- launch -----------------------------------------------------------------------------------------

@@ -1746,6 +1746,10 @@ def bucket_values(kind, n, g):
         x[n // 3: 2 * n // 3] = 0.3712
         x[:n // 8] = x[:n // 8].sort()[0]
         return x
+    if kind == "uneven":          # two values crowd three tiles of four, but not those that the buckets' sizes are taken from
+        at = torch.arange(n, device="cuda")
+        heavy = at // 31_252 % 4 != 0
+        return torch.where(heavy, torch.where(at % 2 == 0, 0.71, -1.9), lap())
     if kind == "tiny":            # the middle of the exponent range's lower end, still normal
         return lap() * 1e-24
     if kind == "wide":            # spread over more binades than the buckets have
@@ -1767,7 +1771,7 @@ BUCKET_CASES = [("laplace", (1 << 21) + 1, 2, {}, 100), ("laplace", 9_699_328, 8
                 ("gelu", (1 << 24) + 5, 4, {}, 100), ("gelu", 2_600_011, 8, {}, 127), ("gelu", 3_000_000, 2, {}, 100),
                 ("relu", 2_500_002, 2, {}, 100), ("relu", 4_000_003, 6, dict(clip=True), 100), ("offset", 2_300_007, 4, {}, 100),
                 ("offset", 2_300_007, 8, {}, 100), ("negative", 2_222_223, 6, {}, 50), ("negative", 2_222_223, 3, dict(dist=1), 13),
-                ("steps", 5_000_001, 2, {}, 100), ("steps", 2_400_000, 8, {}, 100), ("spike", 6_000_001, 4, {}, 100),
+                ("uneven", 256 * 31_252, 8, {}, 100), ("steps", 5_000_001, 2, {}, 100), ("steps", 2_400_000, 8, {}, 100), ("spike", 6_000_001, 4, {}, 100),
                 ("spike", 2_100_001, 8, dict(dist=2), 100), ("tiny", 2_222_222, 4, {}, 100), ("wide", 2_222_222, 4, {}, 100),
                 ("subnormal", 2_222_222, 4, {}, 20), ("nan", 2_222_222, 2, {}, 20), ("inf", 2_222_222, 2, {}, 20)]
 
