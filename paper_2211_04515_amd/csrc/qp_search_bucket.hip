@@ -237,17 +237,15 @@ __device__ inline void candidate_pieces(const BucketAt &t, const Cand &c, uint32
     if (over) l.over = 1u;
 }
 
-// The block's share of the buckets, eight at a time (128 lanes each).  Its lists go to stretches of its own.
-__device__ inline void bucket_lists(const BucketArgs &a, const BucketPlan &p, BucketLists *lists, uint32_t *used /* [3], shared */)
+// The block's share of the buckets, eight at a time (128 lanes each, c the lane's candidate).  Its lists go to stretches of its own.
+__device__ inline void bucket_lists(const BucketArgs &a, const BucketPlan &p, const Cand &c, BucketLists *lists, uint32_t *used /* [3], shared */)
 {
     const uint32_t tid = threadIdx.x, g = tid / kBkCands, j = tid % kBkCands;
     constexpr uint32_t groups = kBkThreads / kBkCands;
     static_assert(kBkKeyed == kBkCands, "a keyed class a lane");
     const uint32_t blocks = min(gridDim.x, kBkTiles);
     BucketLists &l = lists[g];
-    Cand c{0.0f, 0.0f, 0.0f, 0.0f};
     const bool has = j < a.ncand;
-    if (has) c = a.cands[j];
     if (tid < 3u) used[tid] = 0u;
     for (uint32_t first = blockIdx.x; first < 2u * p.width; first += blocks * groups) {
         const uint32_t b = first + g * blocks;
@@ -366,6 +364,8 @@ __device__ inline void bucket_lists(const BucketArgs &a, const BucketPlan &p, Bu
 
 // ---- sort -------------------------------------------------------------------------------------------
 
+constexpr uint32_t kBkEarly = 7u;   // loads of a lane before the lists: their registers are held meanwhile
+
 __global__ __launch_bounds__(kBkThreads) void k_bucket_sort(BucketArgs a)
 {
     __shared__ __align__(16) float sx[kBkTileMax];
@@ -380,10 +380,12 @@ __global__ __launch_bounds__(kBkThreads) void k_bucket_sort(BucketArgs a)
     const uint32_t m = (uint32_t)min((uint64_t)a.tile, a.n - e0);   // elements of this tile
     const uint32_t quads = (m + 3u) / 4u;
 
-    // the whole tile is requested before anything else
+    // much of the tile is requested before anything else but the candidates, and the lists are made while it is on its way
+    const bool listing = a.first_segment && blockIdx.x < kBkTiles;
+    Cand c{0.0f, 0.0f, 0.0f, 0.0f};
+    if (listing && tid % kBkCands < a.ncand) c = a.cands[tid % kBkCands];
     float v[kBkRounds][4];
-#pragma unroll
-    for (uint32_t i = 0; i < kBkRounds; ++i) {
+    auto request = [&](uint32_t i) {
         const uint32_t q = i * kBkThreads + tid;
         if (4u * q + 4u <= m) {
             Vec4<QP_F32>::load(a.x + e0, q, v[i]);
@@ -391,7 +393,12 @@ __global__ __launch_bounds__(kBkThreads) void k_bucket_sort(BucketArgs a)
 #pragma unroll
             for (uint32_t k = 0; k < 4; ++k) v[i][k] = 4u * q + k < m ? a.x[e0 + 4u * q + k] : 0.0f;   // zeros are not kept
         }
-    }
+    };
+#pragma unroll
+    for (uint32_t i = 0; i < kBkEarly; ++i) request(i);
+    if (listing) bucket_lists(a, p, c, reinterpret_cast<BucketLists *>(sx), sh_wave);
+#pragma unroll
+    for (uint32_t i = kBkEarly; i < kBkRounds; ++i) request(i);
     for (uint32_t i = tid; i < kBkKeys; i += kBkThreads) cnt[i] = 0u;
     if (tid == 0) sh_bad = 0u;
     __syncthreads();
@@ -496,9 +503,6 @@ __global__ __launch_bounds__(kBkThreads) void k_bucket_sort(BucketArgs a)
         if (c0) atomicAdd(&a.totals[2u * tid], 4u * c0);
         if (c1) atomicAdd(&a.totals[2u * tid + 1u], 4u * c1);
     }
-    if (!a.first_segment || blockIdx.x >= kBkTiles) return;
-    __syncthreads();
-    bucket_lists(a, p, reinterpret_cast<BucketLists *>(sx), sh_wave);
 }
 
 // ---- sum --------------------------------------------------------------------------------------------
