@@ -997,13 +997,16 @@ __global__ __launch_bounds__(kBsThreads, 4) void k_bucket_sum(BucketArgs a)
 // ---- launch -----------------------------------------------------------------------------------------
 
 #ifndef QP_BUCKET_MIN_N
-#define QP_BUCKET_MIN_N ((1ull << 21) + 1ull)
+#define QP_BUCKET_MIN_N ((1ull << 21) + 1ull)   // from here on a workspace has room for it; see bucket_search_eligible
 #endif
 
 bool bucket_search_eligible(uint64_t n, int dtype, const SearchPlan &plan)
 {
-    return plan.bucket_room && dtype == QP_F32 && n >= QP_BUCKET_MIN_N && plan.bits <= 8u && plan.stride <= 1u &&
-           plan.t_steps + 1u <= kBkCands;
+    // Sorting and listing take 50 us whatever the size, the streaming search 17 us a million elements.  Sender path by streaming /
+    // by buckets: 2 bit 65 / 71 us at 2.2 M elements, 81 / 73 at 3 M; 4 bit after GELU 80 / 90 at 3 M, 97 / 100 at 4 M, 115 / 105
+    // at 5 M; 8 bit 80 / 92, 97 / 96, 115 / 102.
+    const bool pays = plan.bits <= 3u ? 4u * n >= 5u * QP_BUCKET_MIN_N : n >= 2u * QP_BUCKET_MIN_N;
+    return plan.bucket_room && dtype == QP_F32 && pays && plan.bits <= 8u && plan.stride <= 1u && plan.t_steps + 1u <= kBkCands;
 }
 
 size_t bucket_search_end(uint64_t n, size_t at) { return n >= QP_BUCKET_MIN_N ? bucket_layout(n, at).end : at; }
