@@ -473,6 +473,10 @@ __global__ __launch_bounds__(kBkThreads) void k_bucket_sort(BucketArgs a)
         cnt[2u * tid] = start0;
         cnt[2u * tid + 1u] = start1;
         if (tid < p.width) reinterpret_cast<uint32_t *>(row)[tid] = start0 | (start1 << 16);
+        // how much work a bucket is: of every tile, since a crowd may lie in any of them.  Two counts at a time, neither reaches
+        // 2^32; on their way while the tile is written.
+        if ((c0 | c1) != 0u)
+            atomicAdd(reinterpret_cast<unsigned long long *>(a.totals) + tid, (unsigned long long)c0 | ((unsigned long long)c1 << 32));
     }
     if (tid == 0) {
         reinterpret_cast<uint32_t *>(row)[p.width] = kept | ((kept + others) << 16);
@@ -498,11 +502,6 @@ __global__ __launch_bounds__(kBkThreads) void k_bucket_sort(BucketArgs a)
     float4 *out = reinterpret_cast<float4 *>(a.sorted + (uint64_t)blockIdx.x * a.tile);
     const uint32_t oq = (kept + others + 3u) / 4u;   // at most tile / 4
     for (uint32_t q = tid; q < oq; q += kBkThreads) out[q] = reinterpret_cast<const float4 *>(sx)[q];
-    // how much work a bucket is: every fourth tile's count
-    if (two && blockIdx.x % 4u == 0u) {
-        if (c0) atomicAdd(&a.totals[2u * tid], 4u * c0);
-        if (c1) atomicAdd(&a.totals[2u * tid + 1u], 4u * c1);
-    }
 }
 
 // ---- sum --------------------------------------------------------------------------------------------
@@ -661,10 +660,11 @@ __global__ __launch_bounds__(kBsThreads, 4) void k_bucket_sum(BucketArgs a)
     }
 
     // ---- the block's share: the buckets lie end to end by what they cost, and a block takes a stretch of that.  A bucket, or a
-    // class of one that is summed by interval, is an item; of one that the stretch cuts the block takes a share of the tiles ----
-    struct Item { uint16_t bucket, cls, from, to; };   // tiles
+    // class of one that is summed by interval, is an item; of one that the stretch cuts the block takes the tiles that hold that
+    // share of its elements (whole tiles: which elements of a bucket come first in one is the sort's chance) ----
+    struct Item { uint16_t bucket, cls; uint32_t from, to, size; };   // from..to of size
     __shared__ Item sh_items[kBsItems];
-    __shared__ uint32_t sh_wave[kBsThreads / kWave][2], sh_first, sh_count;
+    __shared__ uint32_t sh_wave[kBsThreads / kWave][2], sh_first, sh_count, sh_run[2][2];
     __shared__ BucketPiece sh_piece[kBkCands];
     __shared__ uint32_t runs[kBsTiles], first_load[kBsTiles], loads[kBsBatch];
     constexpr uint32_t per = (kBkKeys + kBsThreads - 1) / kBsThreads;
@@ -737,15 +737,15 @@ __global__ __launch_bounds__(kBsThreads, 4) void k_bucket_sum(BucketArgs a)
                     const uint32_t ncls = classes_of[b], size = sizes[b];
                     if (begin < c + ncls * size) {
                         const uint32_t scrap = min(bucket_least(a.shapes[b]) / 2u, size / 2u);
-                        // a place in the stretch to a tile of the item that it lies in; no scraps
-                        auto tile_at = [&](uint32_t at, uint32_t from) -> uint32_t {
+                        // a place in the stretch to one in the item that it lies in; no scraps
+                        auto place_at = [&](uint32_t at, uint32_t from) -> uint32_t {
                             if (at < from + scrap + 1u) return 0u;
-                            if (at + scrap >= from + size) return a.tiles;
-                            return (uint32_t)((double)a.tiles * (double)(at - from) / (double)size);
+                            if (at + scrap >= from + size) return size;
+                            return at - from;
                         };
                         for (uint32_t cls = begin > c ? (begin - c) / size : 0u; cls < ncls && c + cls * size < end; ++cls) {
                             const uint32_t at = c + cls * size, number = i0 + cls - sh_first, slot = number - first;   // (before this turn: wraps around)
-                            if (slot < kBsItems) sh_items[slot] = Item{(uint16_t)b, (uint16_t)cls, (uint16_t)tile_at(begin, at), (uint16_t)tile_at(end, at)};
+                            if (slot < kBsItems) sh_items[slot] = Item{(uint16_t)b, (uint16_t)cls, place_at(begin, at), place_at(end, at), size};
                             if (end <= at + size) sh_count = number + 1u;   // the last one
                         }
                     }
@@ -759,86 +759,105 @@ __global__ __launch_bounds__(kBsThreads, 4) void k_bucket_sum(BucketArgs a)
         for (uint32_t item = 0; item < kBsItems && first + item < count; ++item) {
             auto uniform = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); };
             const uint32_t b = uniform(sh_items[item].bucket), cls = uniform(sh_items[item].cls);
-            const uint32_t last = uniform(sh_items[item].to);
+            const uint32_t part0 = uniform(sh_items[item].from), part1 = uniform(sh_items[item].to), whole = uniform(sh_items[item].size);
+            if (part0 == part1) continue;
             const BucketRec *rec = a.recs + b;
-            uint32_t t0 = uniform(sh_items[item].from), nruns = last - t0;   // tiles <= 512
-            while (t0 < last) {
-                const uint32_t nsum = uniform(rec->nsum), ncut = uniform(rec->ncut), cuts1 = ncut + 1u;
-                const uint32_t further = uniform(rec->piece);
-                const bool direct = nsum != 0u;
-                const uint32_t *cuts = a.cuts + uniform(rec->cut);
-                const BucketClass *classes = a.classes + uniform(rec->cls);
-                if (tid < kBkDirect) sh.sum[tid] = rec->sum[tid];   // (what lies past nsum is not used)
-                const BucketAt at = bucket_at(p, b);
-                const float base = at.value(0);
-                if (tid < a.ncand) sh_piece[tid] = a.pieces[(uint64_t)b * kBkCands + tid];   // (kept in LDS, not in registers)
-                // the runs, two a lane, and where their loads come in the item's list of loads
-                uint32_t nl[2], sum = 0u;
+            const uint32_t nsum = uniform(rec->nsum), ncut = uniform(rec->ncut), cuts1 = ncut + 1u;
+            const uint32_t further = uniform(rec->piece);
+            const bool direct = nsum != 0u;
+            const uint32_t *cuts = a.cuts + uniform(rec->cut);
+            const BucketClass *classes = a.classes + uniform(rec->cls);
+            if (tid < kBkDirect) sh.sum[tid] = rec->sum[tid];   // (what lies past nsum is not used)
+            const BucketAt at = bucket_at(p, b);
+            const float base = at.value(0);
+            if (tid < a.ncand) sh_piece[tid] = a.pieces[(uint64_t)b * kBkCands + tid];   // (kept in LDS, not in registers)
+            // the runs, two a lane, and where their loads come in the item's list of loads
+            uint32_t nl[2], sum = 0u;
 #pragma unroll
-                for (uint32_t i = 0; i < 2u; ++i) {
-                    const uint32_t t = 2u * tid + i;
-                    nl[i] = 0u;
-                    if (t < nruns) {
-                        const uint16_t *row = a.table + (uint64_t)(t0 + t) * kBkRow + b;
-                        const uint32_t from = row[0], len = (uint32_t)row[1] - from;
-                        runs[t] = from | (len << 16);
-                        nl[i] = (len + 3u) / 4u;
+            for (uint32_t i = 0; i < 2u; ++i) {
+                const uint32_t t = 2u * tid + i;
+                nl[i] = 0u;
+                if (t < a.tiles) {
+                    const uint16_t *row = a.table + (uint64_t)t * kBkRow + b;
+                    const uint32_t from = row[0], len = (uint32_t)row[1] - from;
+                    runs[t] = from | (len << 16);
+                    nl[i] = (len + 3u) / 4u;
+                }
+                sum += nl[i];
+            }
+            static_assert(kBsTiles <= 2u * kBsThreads, "two runs a lane");
+            uint32_t up = sum;
+#pragma unroll
+            for (uint32_t o = 1; o < (uint32_t)kWave; o <<= 1) {
+                const uint32_t v = __shfl_up(up, o, kWave);
+                if (lane >= o) up += v;
+            }
+            if (lane == (uint32_t)kWave - 1u) sh_wave[wave][0] = up;
+            if (!direct)
+                for (uint32_t i = tid; i < ncut; i += kBsThreads) sh.cut[i] = cuts[i];
+            __syncthreads();
+            uint32_t total_loads = 0u;
+            for (uint32_t w = 0; w < kBsThreads / kWave; ++w) {
+                if (w < wave) up += sh_wave[w][0];
+                total_loads += sh_wave[w][0];
+            }
+            // the block's share: from one run's start on and to another's (the blocks next to it work out the same ones)
+            auto load_at = [&](uint32_t part) { return uniform((uint32_t)((double)total_loads * (double)part / (double)whole)); };
+            const uint32_t at0 = load_at(part0), at1 = load_at(part1);
+            up -= sum;
+#pragma unroll
+            for (uint32_t i = 0; i < 2u; ++i) {
+                const uint32_t t = 2u * tid + i;
+                if (t < a.tiles) {
+                    first_load[t] = up;
+                    auto nearest = [&](uint32_t load, uint32_t (&run)[2]) {
+                        if (up < load && load <= up + nl[i]) {
+                            const uint32_t behind = 2u * (load - up) >= nl[i] ? 1u : 0u;
+                            run[0] = t + behind;
+                            run[1] = up + behind * nl[i];
+                        }
+                    };
+                    nearest(at0, sh_run[0]);
+                    nearest(at1, sh_run[1]);
+                }
+                up += nl[i];
+            }
+            if (!direct) {
+                // by interval between cuts: first the cuts at or below each 1/256 of the bucket, a few steps on from there
+                for (uint32_t i = tid; i <= 256u; i += kBsThreads) {
+                    const uint32_t d = i << (p.shift - 8u);
+                    uint32_t l0 = 0u, h0 = ncut;   // cuts below l0 are <= d, cuts from h0 on are > d
+                    while (l0 < h0) {
+                        const uint32_t mid = (l0 + h0) / 2u;
+                        if (sh.cut[mid] <= d) l0 = mid + 1u;
+                        else h0 = mid;
                     }
-                    sum += nl[i];
+                    sh.start[i] = (uint16_t)l0;
                 }
-                static_assert(kBsTiles <= 2u * kBsThreads, "two runs a lane");
-                uint32_t up = sum;
-#pragma unroll
-                for (uint32_t o = 1; o < (uint32_t)kWave; o <<= 1) {
-                    const uint32_t v = __shfl_up(up, o, kWave);
-                    if (lane >= o) up += v;
-                }
-                if (lane == (uint32_t)kWave - 1u) sh_wave[wave][0] = up;
+            }
+            __syncthreads();
+            // (no run holds load 0's end)
+            const uint32_t run0 = at0 ? uniform(sh_run[0][0]) : 0u, run1 = at1 ? uniform(sh_run[1][0]) : 0u;
+            uint32_t load0 = at0 ? uniform(sh_run[0][1]) : 0u;
+            const uint32_t load1 = at1 ? uniform(sh_run[1][1]) : 0u;
+            while (load0 < load1) {
+                const uint32_t load_end = direct ? load1 : min(load1, load0 + kBsLoads);
                 if (direct) {
                     if (tid < kBkDirect) {
                         sh.n[tid] = 0u;
                         sh.f[tid] = sh.q[tid] = 0u;
                     }
                 } else {
-                    for (uint32_t i = tid; i < ncut; i += kBsThreads) sh.cut[i] = cuts[i];
                     for (uint32_t i = tid; i < cuts1; i += kBsThreads) sh.nf[i] = sh.iq[i] = 0u;
                 }
-                __syncthreads();
-                uint32_t total_loads = 0u;
-                for (uint32_t w = 0; w < kBsThreads / kWave; ++w) {
-                    if (w < wave) up += sh_wave[w][0];
-                    total_loads += sh_wave[w][0];
-                }
-                if (!direct && total_loads > kBsLoads && nruns > 1u) {   // fewer tiles at a time
-                    nruns /= 2u;
-                    __syncthreads();
-                    continue;
-                }
-                up -= sum;
-                if (2u * tid < nruns) first_load[2u * tid] = up;
-                if (2u * tid + 1u < nruns) first_load[2u * tid + 1u] = up + nl[0];
-                if (!direct) {
-                    // by interval between cuts: first the cuts at or below each 1/256 of the bucket, a few steps on from there
-                    for (uint32_t i = tid; i <= 256u; i += kBsThreads) {
-                        const uint32_t d = i << (p.shift - 8u);
-                        uint32_t l0 = 0u, h0 = ncut;   // cuts below l0 are <= d, cuts from h0 on are > d
-                        while (l0 < h0) {
-                            const uint32_t mid = (l0 + h0) / 2u;
-                            if (sh.cut[mid] <= d) l0 = mid + 1u;
-                            else h0 = mid;
-                        }
-                        sh.start[i] = (uint16_t)l0;
-                    }
-                }
                 uint32_t share = 0u;   // 2^share lanes list a run's loads
-                while (share < 6u && (nruns << (share + 1u)) <= (uint32_t)kBsThreads) ++share;
+                while (share < 6u && ((run1 - run0) << (share + 1u)) <= (uint32_t)kBsThreads) ++share;
                 // a batch's loads are listed and requested before the sums of the batch before it
-                const float *sorted = a.sorted + (uint64_t)t0 * a.tile;
                 Float4U x[kBsQuads];
                 uint32_t have = 0u;   // elements of each, a byte
                 auto request = [&](uint32_t batch) {
                     __syncthreads();   // runs and their places are there; the last batch's list has been read
-                    for (uint32_t r = tid >> share; r < nruns; r += (uint32_t)kBsThreads >> share) {
+                    for (uint32_t r = run0 + (tid >> share); r < run1; r += (uint32_t)kBsThreads >> share) {
                         const uint32_t run = runs[r], at0 = first_load[r], len = run >> 16, n4 = (len + 3u) / 4u;
                         if (at0 + n4 <= batch || at0 >= batch + kBsBatch) continue;
                         const uint32_t where = r * a.tile + (run & 0xffffu);
@@ -853,16 +872,16 @@ __global__ __launch_bounds__(kBsThreads, 4) void k_bucket_sum(BucketArgs a)
                     for (uint32_t k = 0; k < kBsQuads; ++k) {
                         const uint32_t i = batch + k * kBsThreads + tid;
                         x[k] = Float4U{base, base, base, base};
-                        if (i < total_loads) {
+                        if (i < load_end) {
                             const uint32_t l = loads[i - batch];
-                            x[k] = *reinterpret_cast<const Float4U *>(sorted + (l >> 2));
+                            x[k] = *reinterpret_cast<const Float4U *>(a.sorted + (l >> 2));
                             have |= ((l & 3u) + 1u) << (8u * k);
                         }
                     }
                 };
-                for (uint32_t batch = 0; batch < total_loads; batch += kBsBatch) {
+                for (uint32_t batch = load0; batch < load_end; batch += kBsBatch) {
                     request(batch);
-                    const uint32_t left = min(total_loads - batch, kBsBatch);
+                    const uint32_t left = min(load_end - batch, kBsBatch);
                     float f0[kBsPerLane];
                     uint32_t had[kBsQuads], valid = 0u;
 #pragma unroll
@@ -985,8 +1004,7 @@ __global__ __launch_bounds__(kBsThreads, 4) void k_bucket_sum(BucketArgs a)
                     sh_total[tid] += mine;
                 }
                 __syncthreads();   // runs and sums are reused
-                t0 += nruns;
-                nruns = last - t0;
+                load0 = load_end;
             }
         }
         __syncthreads();

@@ -129,14 +129,19 @@ int main(int argc, char **argv)
     // what the fused sender path left in its own workspace (its search may run a different kernel sequence)
     dump(out, "scores2.bin", (const char *)ws2 + qp_ws_offset(QP_WS_SCORES), ((size_t)cfg.t_steps + 1) * 8);
     dump(out, "result2.bin", (const char *)ws2 + qp_ws_offset(QP_WS_RESULT), sizeof res);
-    // what the search by value buckets made of the tensor: its plan, where the workspace holds one
+    // what the search by value buckets made of the tensor, where the workspace holds such: its plan
     {
         const size_t cols = std::max(qp::search_blocks(n), qp::tile_search_blocks(n)), rows = std::max(cfg.t_steps + 1u, 128u);
         const size_t least = qp::kOffSearchPart + cols * rows * sizeof(double);
         qp::BucketPlan plan;
         memset(&plan, 0xff, sizeof plan);
-        if (wsb > least) memcpy(&plan, (const char *)ws + qp::bucket_layout(n, least).plan, sizeof plan);
+        const qp::BucketLayout l = qp::bucket_layout(n, least);
+        if (wsb > least) memcpy(&plan, (const char *)ws + l.plan, sizeof plan);
         dump(out, "plan.bin", &plan, sizeof plan);
+        // ... and how many elements it counted in each bucket, segment by segment
+        const uint32_t parts[2] = {l.segments, l.tile * l.tiles};
+        dump(out, "segments.bin", parts, sizeof parts);
+        if (wsb > least) dump(out, "totals.bin", (const char *)ws + l.totals, (size_t)l.segments * qp::kBkKeys * 4);
     }
     dump(out, "packed.bin", packed, pkb);
     dump(out, "y.bin", y, n * 4);

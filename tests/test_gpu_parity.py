@@ -1,6 +1,7 @@
 """GPU parity: the HIP library (through its C ABI) against the CPU oracle, element by element,
 on the same seeded inputs.  Needs a real MI355X: run with -m gpu."""
 import ctypes as C
+import math
 from concurrent.futures import ThreadPoolExecutor
 
 import numpy as np
@@ -1815,3 +1816,33 @@ def test_bucket_search_equals_the_streaming_search(qp, kind, n, bits, v, t):
         x = xd.cpu().numpy()
         for j in (0, t):
             assert a[j] == pytest.approx(pairwise_sq_error(x, orc.search_candidate(oracle_stats_from(st), bits, t, n, j)), rel=REL_SCORE_PAIRWISE)
+
+
+def sender_us(qp, xd, bits, cfg, room):
+    """Microseconds of a sender path among others, with room for the buckets or without."""
+    n = xd.numel()
+    ws = qp.alloc_workspace(n, cfg)
+    ws = ws if room else ws[:LEAST_WORKSPACE]
+    packed, grid = qp.alloc_packed(n, bits), torch.empty(32, dtype=torch.uint8, device="cuda")
+    best = math.inf
+    for _ in range(4):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(8):
+            qp.qp_compress_async(xd, bits, ws, packed, grid.data_ptr(), cfg)
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) / 8 * 1000)
+    return best
+
+
+@pytest.mark.parametrize("kind,n,bits", [("uneven", 256 * 31_252, 8), ("uneven", 256 * 31_252, 2), ("spike", 6_000_001, 4)])
+def test_a_crowd_of_equal_values_is_shared_by_the_blocks(qp, kind, n, bits):
+    """Values that crowd a few buckets in some of the tiles: the blocks share their elements, wherever they lie.  Atomics on one
+    address make such tensors slower than others; left to one block they took 270 times the streaming search."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    xd, cfg = bucket_values(kind, n, g), variant_cfg(qp, {}, 100)
+    took, streaming = sender_us(qp, xd, bits, cfg, True), sender_us(qp, xd, bits, cfg, False)
+    print(f"[case] {kind} {n} {bits} bit: {took:.1f} / {streaming:.1f} us", flush=True)
+    assert took <= 3.0 * streaming

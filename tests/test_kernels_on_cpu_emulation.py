@@ -237,6 +237,24 @@ def test_the_bucket_build_takes_the_buckets(runs, tag, case):
     assert plan[1] == (1 if case[0] == "subnormal" else 0)     # 1: left to the streaming kernel
 
 
+@pytest.mark.parametrize("tag,case", BUCKET_CASES[:3], ids=[case_id(*a) for a in BUCKET_CASES[:3]])
+def test_a_buckets_size_counts_every_tile(runs, tag, case):
+    """The summing blocks share the work by the buckets' sizes: a crowd that they do not show falls to one block."""
+    p, out_dir, x = runs[case_id(tag, case)]
+    assert p.returncode == 0
+    rd = lambda name: np.fromfile(os.path.join(out_dir, name), np.uint32)
+    _, _, shift, first, width, centre = (int(v) for v in rd("plan.bin"))
+    segments, step = (int(v) for v in rd("segments.bin"))
+    totals = rd("totals.bin").reshape(segments, -1)
+    w = x.view(np.uint32)
+    u = ((w & 0x7fffffff) >> shift).astype(np.int64) - first
+    key = np.where((u >= 0) & (u < width), u + (w >> 31) * width, -1)
+    for s in range(segments):
+        k = key[s * step:(s + 1) * step]
+        k = k[(k >= 0) & (k != centre)]
+        assert np.array_equal(totals[s], np.bincount(k, minlength=totals.shape[1]))
+
+
 def test_emulation_refuses_what_the_library_refuses(runs):
     """Coarse-to-fine is not offered for bf16 tensors that go through their value table: QP_EINVAL, nothing more runs."""
     p, out_dir, x = runs[case_id("streaming", REFUSED)]
