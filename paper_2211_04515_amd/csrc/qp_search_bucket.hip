@@ -96,16 +96,27 @@ __device__ __forceinline__ uint32_t bucket_cost(uint32_t n, uint32_t shape)
     return shape >> 16 ? bucket_least(shape) + batches * 130u / 64u : max(bucket_least(shape), 30u + batches * (28u + low) / 64u);
 }
 
+// A value that the compiler must take as new: what it would otherwise work out early or once for all (addresses, 64-bit copies)
+// costs the registers of a wave.
+__device__ __forceinline__ void opaque(uint32_t &v)
+{
+#if defined(__AMDGCN__)
+    asm volatile("" : "+v"(v));
+#endif
+}
+
 // A bucket's lists while 128 lanes, one a candidate, fill them.
 constexpr uint32_t kBkKeyed = 128;    // classes that candidates share: place - a < 32, parity, frac 0 or a half
 constexpr uint32_t kBkAsIs = 255u;    // class 0
 static_assert(kBkKeyed + kBkOwnCap < kBkAsIs, "a class is a byte");
 struct BucketRounding { float frac; int k2; };   // k2 = 2 k + odd
 struct alignas(16) BucketLists {
-    uint32_t ncut, nown, npiece, over, ncls, need[2], weight;
+    uint32_t ncut, nown, npiece, over, wanted[kBkKeyed / kWave], need[2], weight;
     uint32_t cut[kBkCutCap];          // its place in the bucket << 9 | number, so that no two are equal
     uint16_t order[kBkCutCap];        // a cut's place among the sorted ones
     uint16_t keyed[kBkKeyed];         // 1: wanted; then its number
+    uint32_t owner[kBkOwnCap];        // candidate << 20 | where in the bucket
+    uint8_t own_place[kBkOwnCap], own_at[kBkOwnCap];   // by owner; and which one lies there
     BucketRounding own[kBkOwnCap];
     BucketPiece piece[kBkPieceCap];
 };
@@ -224,8 +235,12 @@ __device__ inline void candidate_pieces(const BucketAt &t, const Cand &c, uint32
                     const double q = frac * pow2(k - t.a), below = floor(q), rest = q - below;
                     frac = (below + (rest == 0.0 ? 0.0 : rest < 0.5 ? 0.25 : rest == 0.5 ? 0.5 : 0.75)) * pow2(t.a - k);   // a float up to kBkFurthest
                     const uint32_t i = atomicAdd(&l.nown, 1u);
-                    if (i >= kBkOwnCap) over = true;
-                    else l.own[i] = BucketRounding{(float)frac, 2 * k + (int)odd};
+                    if (i >= kBkOwnCap) {
+                        over = true;
+                    } else {
+                        l.own[i] = BucketRounding{(float)frac, 2 * k + (int)odd};
+                        l.owner[i] = j << 20 | from;
+                    }
                     cls = kBkKeyed + i;
                 }
                 if (k - t.a > kBkFurthest) over = true;
@@ -238,6 +253,8 @@ __device__ inline void candidate_pieces(const BucketAt &t, const Cand &c, uint32
 }
 
 // The block's share of the buckets, eight at a time (128 lanes each, c the lane's candidate).  Its lists go to stretches of its own.
+// The classes' order is that of the candidates, not of the atomics: where a bucket is summed by interval, a class's number says
+// which block's sum takes it, and with that how the score is rounded.
 __device__ inline void bucket_lists(const BucketArgs &a, const BucketPlan &p, const Cand &c, BucketLists *lists, uint32_t *used /* [3], shared */)
 {
     const uint32_t tid = threadIdx.x, g = tid / kBkCands, j = tid % kBkCands;
@@ -252,7 +269,6 @@ __device__ inline void bucket_lists(const BucketArgs &a, const BucketPlan &p, co
         const bool live = b < 2u * p.width && b != p.centre;
         if (j == 0u) {
             l.ncut = l.nown = l.npiece = l.over = l.need[0] = l.need[1] = l.weight = 0u;
-            l.ncls = 1u;   // class 0
         }
         l.keyed[j] = 0u;
         __syncthreads();
@@ -261,9 +277,12 @@ __device__ inline void bucket_lists(const BucketArgs &a, const BucketPlan &p, co
         if (live && has) candidate_pieces(t, c, j, l);
         __syncthreads();
         const uint32_t nc = min(l.ncut, kBkCutCap), nown = min(l.nown, kBkOwnCap), np = min(l.npiece, kBkPieceCap - kBkCands);
-        const bool want = l.keyed[j] != 0u;
-        uint32_t number = 0u;
-        if (want) number = atomicAdd(&l.ncls, 1u);
+        {   // the keyed classes' numbers: behind class 0, so far of each wave's lanes (kept in LDS, not in registers)
+            const bool want = l.keyed[j] != 0u;
+            const uint64_t wanted = __ballot(want);
+            if (want) l.keyed[j] = (uint16_t)(1u + (uint32_t)__popcll(wanted & ((1ull << (j % kWave)) - 1ull)));
+            if (j % kWave == 0u) l.wanted[j / kWave] = (uint32_t)__popcll(wanted);
+        }
         if (j < 8u && nc + j < kBkCutCap) l.cut[nc + j] = 0xffffffffu;
         __syncthreads();
         // the cuts' order
@@ -277,9 +296,19 @@ __device__ inline void bucket_lists(const BucketArgs &a, const BucketPlan &p, co
             }
             l.order[i] = (uint16_t)below;
         }
+        for (uint32_t i = j; i < nown; i += kBkCands) {
+            uint32_t me = i;
+            opaque(me);
+            const uint32_t o = l.owner[me];
+            uint32_t below = 0u;
+#pragma unroll 1
+            for (uint32_t k = 0; k < nown; ++k) below += l.owner[k] < o ? 1u : 0u;
+            l.own_place[me] = (uint8_t)below;
+            l.own_at[below] = (uint8_t)me;
+        }
+        if (j >= (uint32_t)kWave && l.keyed[j]) l.keyed[j] += (uint16_t)l.wanted[0];
+        const uint32_t shared = 1u + l.wanted[0] + l.wanted[1], ncls = shared + nown;
         __syncthreads();
-        if (want) l.keyed[j] = (uint16_t)number;
-        const uint32_t shared = l.ncls, ncls = shared + nown;
         if (j == 0u) {   // (a dead group has a class and nothing else)
             l.ncut = atomicAdd(&used[0], nc);
             l.nown = atomicAdd(&used[1], ncls);
@@ -294,12 +323,12 @@ __device__ inline void bucket_lists(const BucketArgs &a, const BucketPlan &p, co
             for (uint32_t i = j; i < nc; i += kBkCands) a.cuts[at_cut + l.order[i]] = l.cut[i] >> 9;
             BucketClass *cls = a.classes + at_cls;
             if (j == 0u) cls[0] = BucketClass{0.0f, 0.0f, __uint_as_float((uint32_t)(127 - t.a) << 23), 0.0f};
-            if (want) cls[number] = bucket_class(t, keyed_class(j));
-            for (uint32_t i = j; i < nown; i += kBkCands) cls[shared + i] = bucket_class(t, l.own[i]);
+            if (l.keyed[j]) cls[l.keyed[j]] = bucket_class(t, keyed_class(j));
+            for (uint32_t i = j; i < nown; i += kBkCands) cls[shared + l.own_place[i]] = bucket_class(t, l.own[i]);
             for (uint32_t i = j; i < kBkCands + np; i += kBkCands) {
                 if (i < kBkCands && !has) continue;
                 BucketPiece &q = l.piece[i];
-                q.cls = (uint8_t)(q.cls == kBkAsIs ? 0u : q.cls < kBkKeyed ? l.keyed[q.cls] : shared + q.cls - kBkKeyed);
+                q.cls = (uint8_t)(q.cls == kBkAsIs ? 0u : q.cls < kBkKeyed ? l.keyed[q.cls] : shared + l.own_place[q.cls - kBkKeyed]);
                 if (q.from) q.from = (uint16_t)(l.order[q.from - 1u] + 1u);
                 if (q.to != kBkNone) q.to = (uint16_t)(l.order[q.to - 1u] + 1u);
                 if (few) {
@@ -336,7 +365,7 @@ __device__ inline void bucket_lists(const BucketArgs &a, const BucketPlan &p, co
                     if (cut == (uint32_t)l.order[i] + 1u) m.from = fabsf(t.value(l.cut[i] >> 9) - t.value(0));   // exact: one binade
                 if (k) {
                     BucketRounding how{0.0f, 0};
-                    if (k >= shared) how = l.own[k - shared];
+                    if (k >= shared) how = l.own[l.own_at[k - shared]];
                     else
                         for (uint32_t i = 0; i < kBkKeyed; ++i)
                             if (l.keyed[i] == k) how = keyed_class(i);
@@ -527,20 +556,11 @@ struct BucketSums {
     uint16_t start[257];                             // cuts at or below the start of each 1/256 of the bucket
 };
 
-// Values that the compiler must take as new: what it would otherwise work out once for all sums (64-bit copies) costs the
-// registers of a wave.
 __device__ __forceinline__ void opaque(float (&v)[kBsPerLane])
 {
 #if defined(__AMDGCN__)
 #pragma unroll
     for (uint32_t i = 0; i < kBsPerLane; ++i) asm volatile("" : "+v"(v[i]));
-#endif
-}
-
-__device__ __forceinline__ void opaque(uint32_t &v)
-{
-#if defined(__AMDGCN__)
-    asm volatile("" : "+v"(v));
 #endif
 }
 

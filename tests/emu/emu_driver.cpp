@@ -142,6 +142,19 @@ int main(int argc, char **argv)
         const uint32_t parts[2] = {l.segments, l.tile * l.tiles};
         dump(out, "segments.bin", parts, sizeof parts);
         if (wsb > least) dump(out, "totals.bin", (const char *)ws + l.totals, (size_t)l.segments * qp::kBkKeys * 4);
+        // ... and the classes of each bucket, in their order
+        if (wsb > least && plan.fallback == 0) {
+            std::vector<float> list;
+            const char *p = (const char *)ws;
+            for (uint32_t b = 0; b < 2 * plan.width; ++b) {
+                if (b == plan.centre) continue;
+                const qp::BucketRec &r = reinterpret_cast<const qp::BucketRec *>(p + l.recs)[b];
+                const qp::BucketClass *c = reinterpret_cast<const qp::BucketClass *>(p + l.classes) + r.cls;
+                list.push_back((float)r.ncls);
+                for (uint32_t i = 0; i < r.ncls; ++i) list.insert(list.end(), {c[i].add, c[i].m, c[i].unit});
+            }
+            dump(out, "classes.bin", list.data(), list.size() * 4);
+        }
     }
     dump(out, "packed.bin", packed, pkb);
     dump(out, "y.bin", y, n * 4);

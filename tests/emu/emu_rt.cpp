@@ -39,6 +39,35 @@ uint64_t ballot(bool p)
     return m;
 }
 
+// EMU_LATE_WAVES=0 or 1: between two barriers of a block its even (odd) waves run only once the others have reached the second one,
+// so that what the waves do in turn (atomics that hand out places) happens in that order and in no other.
+static int late_waves()
+{
+    static const int late = [] { const char *e = getenv("EMU_LATE_WAVES"); return e ? atoi(e) : -1; }();
+    return late;
+}
+static thread_local uint64_t t_barriers = 0;
+static bool late_lane() { return late_waves() >= 0 && (int)(t_threadIdx.x / 64 % 2) == late_waves(); }
+static void wait_for_the_others()
+{
+    if (!late_lane()) return;
+    const uint64_t need = (t_barriers + 1) * g_ctx->early_lanes;
+    for (uint64_t v; (v = g_ctx->early_arrivals.load()) < need;) g_ctx->early_arrivals.wait(v);
+}
+static void early_arrival(uint64_t count)
+{
+    if (late_waves() < 0 || late_lane()) return;
+    const uint64_t v = g_ctx->early_arrivals.fetch_add(count) + count;
+    if (count > 1 || v % g_ctx->early_lanes == 0) g_ctx->early_arrivals.notify_all();
+}
+void block_barrier()
+{
+    early_arrival(1);
+    g_ctx->block_bar->arrive_and_wait();
+    ++t_barriers;
+    wait_for_the_others();
+}
+
 // One block: a thread per lane, barriers for the block and for each wave.
 static void run_block(unsigned bx, unsigned by, unsigned nthreads, const std::function<void()> &fn)
 {
@@ -48,6 +77,7 @@ static void run_block(unsigned bx, unsigned by, unsigned nthreads, const std::fu
     for (unsigned w = 0; w < nwaves; ++w)
         ctx.wave_bar.push_back(std::make_unique<std::barrier<>>(std::min(64u, nthreads - 64 * w)));
     ctx.xbuf.assign(nwaves * 2 * 64, 0u);
+    for (unsigned t = 0; t < nthreads; ++t) ctx.early_lanes += late_waves() >= 0 && (int)(t / 64 % 2) != late_waves() ? 1u : 0u;
     g_ctx = &ctx;
     std::vector<std::thread> th;
     th.reserve(nthreads);
@@ -56,7 +86,10 @@ static void run_block(unsigned bx, unsigned by, unsigned nthreads, const std::fu
             t_threadIdx = dim3(t, 0, 0);
             t_blockIdx = dim3(bx, by, 0);
             t_opcount = 0;
+            t_barriers = 0;
+            wait_for_the_others();
             fn();
+            early_arrival(1ull << 40);   // nothing to wait for any more
             ctx.block_bar->arrive_and_drop();
             ctx.wave_bar[t / 64]->arrive_and_drop();
         });

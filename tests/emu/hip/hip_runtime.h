@@ -59,6 +59,8 @@ struct BlockCtx {
     std::vector<std::unique_ptr<std::barrier<>>> wave_bar;
     std::vector<uint32_t> xbuf;   // [wave][2][64]
     std::atomic<int> and_flag{1};
+    uint64_t early_lanes = 0;                  // see EMU_LATE_WAVES
+    std::atomic<uint64_t> early_arrivals{0};   // of those lanes, at barriers
 };
 extern BlockCtx *g_ctx;
 extern thread_local unsigned t_opcount;
@@ -71,6 +73,7 @@ const Allocation *find(const void *p);
 hipError_t copy(void *d, const void *s, size_t n);
 uint32_t exchange(uint32_t v, int src_lane_or_minus1, int ctrl, int xor_mask);
 uint64_t ballot(bool p);
+void block_barrier();
 }  // namespace emu
 
 #define threadIdx emu::t_threadIdx
@@ -106,7 +109,7 @@ static inline hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
 static inline hipError_t hipDeviceGetAttribute(int *v, int, int) { *v = emu::g_cus; return hipSuccess; }
 template <typename K> static inline hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, K, int, size_t) { *n = emu::g_occupancy; return hipSuccess; }
 
-static inline void __syncthreads() { emu::g_ctx->block_bar->arrive_and_wait(); }
+static inline void __syncthreads() { emu::block_barrier(); }
 static inline int __syncthreads_and(int p)
 {
     __syncthreads();

@@ -54,13 +54,15 @@ def drivers():
 
 
 def start_driver(exe, out_dir, x, bits, t=100, dist=0, flags=0, stride=0, nbins=2048, cus=4, cpr=None, concurrent=0, seed=1,
-                 record=None):
+                 record=None, late=None):
     os.makedirs(out_dir, exist_ok=True)
     inp = os.path.join(out_dir, "in.bin")
     x.tofile(inp)
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:abort_on_error=0", UBSAN_OPTIONS="print_stacktrace=1")
     if record:
         env["EMU_RECORD"] = record
+    if late is not None:
+        env["EMU_LATE_WAVES"] = str(late)
     if concurrent:
         env.update(EMU_CONCURRENT_BLOCKS=str(concurrent), EMU_SEED=str(seed))
     return subprocess.run([exe, inp, str(x.size), "1" if x.dtype == np.uint16 else "0", str(bits), str(t), str(dist),
@@ -184,9 +186,11 @@ RECORD_REFUSED = ("default", ("C3", 3_001, 4, dict(record="short"), 1))
 # thresholds to a bucket; a tensor that it leaves to the streaming kernel
 BUCKET_CASES = [("bucket", c) for c in (("C1", 1_301, 2, {}, 20), ("C2", 3_001, 3, dict(conc=3), 13), ("offset", 2_601, 4, {}, 20),
                                         ("subnormal", 2_003, 4, {}, 13))]
+# The waves of a block in either order (candidates of two waves, so that both hand out classes)
+WAVE_CASES = [("bucket", ("offset", 1_301, 3, dict(late=w), 68)) for w in (0, 1)]
 ALL_CASES = ([("default", c) for c in TILE_CASES] + [("streaming", c) for c in STREAM_CASES] + [("streaming", REFUSED)] + ACIQ_ONLY
              + CONCURRENT_CASES + STREAM_C2F_CASES + RECORD_CASES + [RECORD_REFUSED]
-             + TABLE_STATS_CASES + PAIRS_CASES + BUCKET_CASES)
+             + TABLE_STATS_CASES + PAIRS_CASES + BUCKET_CASES + WAVE_CASES)
 
 
 def case_id(tag, c):
@@ -206,7 +210,7 @@ def runs(drivers, tmp_path_factory):
         out_dir = os.path.join(base, case_id(tag, item[1]))
         p = start_driver(drivers[tag], out_dir, x, bits, t=t, dist=v.get("dist", 0), flags=flags,
                          stride=v.get("stride", 0) if flags & 2 else 0, cus=4 if tag == "default" else 2, cpr=v.get("cpr"), nbins=v.get("nbins", 2048),
-                         concurrent=v.get("conc", 0), seed=v.get("seed", 1), record=v.get("record"))
+                         concurrent=v.get("conc", 0), seed=v.get("seed", 1), record=v.get("record"), late=v.get("late"))
         return case_id(tag, item[1]), (p, out_dir, x)
 
     with ThreadPoolExecutor(max_workers=6) as ex:
@@ -253,6 +257,18 @@ def test_a_buckets_size_counts_every_tile(runs, tag, case):
         k = key[s * step:(s + 1) * step]
         k = k[(k >= 0) & (k != centre)]
         assert np.array_equal(totals[s], np.bincount(k, minlength=totals.shape[1]))
+
+
+def test_a_buckets_classes_do_not_depend_on_the_waves_order(runs):
+    """Where a bucket is summed by interval, a class's number says which block's partial sum takes it: an order left to atomics is one
+    of the scores' last bits."""
+    seen = []
+    for tag, case in WAVE_CASES:
+        p, out_dir, x = runs[case_id(tag, case)]
+        assert p.returncode == 0
+        seen.append((np.fromfile(os.path.join(out_dir, "classes.bin"), np.float32), read_outputs(p, out_dir)["scores"]))
+    (a, sa), (b, sb) = seen
+    assert np.array_equal(a, b) and np.array_equal(sa, sb)
 
 
 def test_emulation_refuses_what_the_library_refuses(runs):
