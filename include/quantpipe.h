@@ -162,10 +162,14 @@ size_t qp_packed_bytes(uint64_t n, uint32_t bits);
 /* Bytes of device workspace needed by qp_stats / qp_dsaciq_search for an n-element
  * tensor under cfg (NULL = defaults: t_steps 100, cands_per_round 13).  0 on bad arguments.
  * (Sec. 3, Eq. 1: what the statistics and the t+1 candidates of the directed search need between kernels:
- * per-block partial sums, the histogram D_R, the candidate grids and their scores.)
- * About 1.4 MB for the default t_steps; above 2^21 elements also room for up to 2^24 elements of the tensor sorted by value
- * and the tables of that sort (29 MB in all at 2^21 elements, 59 MB at 9.7 M, 89 MB at 2^24 and hardly more beyond).  A call
- * whose workspace holds the first part only is not refused: its search goes over the tensor as it lies, with the same result. */
+ * per-block partial sums, the histogram D_R, the candidate grids and their scores.
+ * About 1.4 MB for the default t_steps.  Where a search of an fp32 tensor under cfg may go by value buckets (from 2.6 M elements on for
+ * the default t_steps, from more for a shorter sweep, never for QP_SEARCH_COARSE_TO_FINE) also room for up to 2^24 elements of the
+ * tensor sorted by value and the tables of that sort: 30 MB in all at 2.6 M elements, 58 MB at 9.7 M, 88 MB at 2^24, and 1.1 MB for
+ * each 2^24 elements beyond that (357 MB at 2^32 - 1).  The dtype and the bitwidth are not known here: bf16 tensors and 16 bit never
+ * use that room.  A call whose workspace holds the first part only is not refused: its search goes over the tensor as it lies.  Both
+ * ways add the same squared errors in 64 bits, in another order: scores agree to about 1e-15 of their value, so that candidates which
+ * tie to that may change places.) */
 size_t qp_workspace_bytes(uint64_t n, const qp_search_cfg_t *cfg);
 
 /* Byte offset of a region inside the workspace; (size_t)-1 for an unknown region. */
@@ -333,8 +337,8 @@ qp_status qp_compress_many_async(const qp_job_t *jobs, uint32_t count, const qp_
 
 /* ---- the same sender path for callers that cannot allocate -----------------------
  * For code under HIP graph capture, tight serving loops and harnesses that forbid hipMalloc: the
- * callers that cannot bring a workspace.  Same results as qp_compress_async (the search of a large fp32
- * tensor goes over the tensor as it lies, see qp_workspace_bytes), with the workspace in a static device array
+ * callers that cannot bring a workspace.  Same results as qp_compress_async with a workspace that
+ * holds no room for value buckets (see qp_workspace_bytes: the search of a large fp32 tensor goes over the tensor as it lies), with the workspace in a static device array
  * inside the library (1,384,960 bytes per GPU, held until the process ends; its device address is looked up on the first call on each device, so a caller
  * that captures into a HIP graph makes one call outside the capture first).  Calls no allocating routine.  The caller still owns x_dev, packed_dev and qparams_out_dev (required:
  * 32 bytes of device memory that receive the winner's qp_qparams_t; the statistics and the search

@@ -87,6 +87,11 @@ qp_status check_ws(uint64_t n, const qp_search_cfg_t *cfg, const void *ws, size_
     return QP_OK;
 }
 
+uint32_t stride_of(const qp_search_cfg_t *cfg)
+{
+    return cfg && (cfg->flags & QP_SEARCH_COARSE_TO_FINE) ? (cfg->coarse_stride ? cfg->coarse_stride : 10u) : 1u;
+}
+
 // The host's decisions about one search (cfg already checked).
 SearchPlan make_plan(uint32_t bits, const qp_search_cfg_t *cfg)
 {
@@ -98,10 +103,9 @@ SearchPlan make_plan(uint32_t bits, const qp_search_cfg_t *cfg)
     p.C = p.dist == QP_GAUSS ? gauss_constant(bits) : laplace_constant(bits);
     p.C_alt = p.dist == QP_DIST_AUTO ? gauss_constant(bits) : 0.0;
     p.clip = (cfg && (cfg->flags & QP_SEARCH_CLIP_TO_DATA)) ? 1u : 0u;
-    p.stride = 1u;
+    p.stride = stride_of(cfg);
     p.bucket_room = 0u;
     p.bucket_at = 0u;
-    if (cfg && (cfg->flags & QP_SEARCH_COARSE_TO_FINE)) p.stride = cfg->coarse_stride ? cfg->coarse_stride : 10u;
     p.aciq_only = (cfg && (cfg->flags & QP_SEARCH_LOW_BITS_ONLY) && bits > 4u) ? 1u : 0u;
     return p;
 }
@@ -157,7 +161,8 @@ void qp_default_search_cfg(qp_search_cfg_t *cfg)
 size_t qp_workspace_bytes(uint64_t n, const qp_search_cfg_t *cfg)
 {
     const size_t least = least_workspace(n, cfg);
-    return least == 0 ? 0 : bucket_search_end(n, least);   // (whatever t_steps: a longer sweep asks for no less)
+    if (least == 0 || !bucket_search_wanted(n, cfg ? cfg->t_steps : 100u, stride_of(cfg))) return least;
+    return bucket_search_end(n, least);
 }
 
 size_t qp_ws_offset(qp_ws_region region)

@@ -135,6 +135,8 @@ __device__ inline void bucket_plan(const BucketSetup &b, const GridModel &g, int
 
 // Whether such a search takes this call, given room in the workspace (the caller's business).
 bool bucket_search_eligible(uint64_t n, int dtype, const SearchPlan &plan);
+// Whether the search takes some bitwidth's call of these settings: whether a workspace should hold its part.
+bool bucket_search_wanted(uint64_t n, uint32_t t_steps, uint32_t stride);
 size_t bucket_search_end(uint64_t n, size_t at);   // bytes of a workspace with the search's part behind `at`
 BucketSetup bucket_setup_args(uint64_t n, const SearchPlan &plan, void *ws);
 // Behind the set-up: sort, sum, pick.  *fallback (device) is 1 afterwards if nothing was scored.

@@ -1035,19 +1035,42 @@ __global__ __launch_bounds__(kBsThreads, 4) void k_bucket_sum(BucketArgs a)
 // ---- launch -----------------------------------------------------------------------------------------
 
 #ifndef QP_BUCKET_MIN_N
-#define QP_BUCKET_MIN_N ((1ull << 21) + 1ull)   // from here on a workspace has room for it; see bucket_search_eligible
+#define QP_BUCKET_MIN_N ((1ull << 21) + 1ull)   // the tile search is there below
 #endif
+#ifndef QP_BUCKET_LEAST_SAVING
+#define QP_BUCKET_LEAST_SAVING 0.0
+#endif
+
+// What the buckets save a call against the streaming search, in microseconds.  That one's time goes with the pairs (0.16 us a
+// million); sorting, listing and summing hardly know how many candidates there are.  Sender path by streaming / by buckets, Laplace
+// data at 2 bit: 9.7 M elements 81 / 106 us at t = 20, 117 / 109 at 42, 207 / 110 at 100; 4.3 M 81 / 81 at 55, 113 / 82 at 100;
+// 30 M 227 / 258 at 30, 349 / 262 at 55; 2.7 M 75 / 72 at 85.  At 8 bit 9.7 M 140 / 135 at 55, 4.3 M 90 / 99 at 70, 113 / 103 at 100.
+static double bucket_saving(uint64_t n, uint32_t bits, uint32_t ncand)
+{
+    const double m = 1e-6 * (double)n, segments = (double)ceil_div_u64(n, QP_BUCKET_SEGMENT);
+    const double fixed = bits <= 3u ? 31.0 : bits <= 4u ? 30.0 : bits <= 6u ? 32.0 : 36.0;
+    const double each = bits <= 3u ? 3.75 : bits <= 6u ? 5.25 : 6.0;
+    return 0.16 * m * (double)ncand - fixed - each * m - 15.0 * (segments - 1.0);
+}
+static bool bucket_search_pays(uint64_t n, uint32_t bits, uint32_t ncand)
+{
+    if (bits > 3u ? n < 2u * QP_BUCKET_MIN_N : 4u * n < 5u * QP_BUCKET_MIN_N) return false;
+    return bucket_saving(n, bits, ncand) >= QP_BUCKET_LEAST_SAVING;
+}
 
 bool bucket_search_eligible(uint64_t n, int dtype, const SearchPlan &plan)
 {
-    // Sorting and listing take 50 us whatever the size, the streaming search 17 us a million elements.  Sender path by streaming /
-    // by buckets: 2 bit 65 / 71 us at 2.2 M elements, 81 / 73 at 3 M; 4 bit after GELU 80 / 90 at 3 M, 97 / 100 at 4 M, 115 / 105
-    // at 5 M; 8 bit 80 / 92, 97 / 96, 115 / 102.
-    const bool pays = plan.bits <= 3u ? 4u * n >= 5u * QP_BUCKET_MIN_N : n >= 2u * QP_BUCKET_MIN_N;
-    return plan.bucket_room && dtype == QP_F32 && pays && plan.bits <= 8u && plan.stride <= 1u && plan.t_steps + 1u <= kBkCands;
+    return plan.bucket_room && dtype == QP_F32 && plan.bits <= 8u && plan.stride <= 1u && plan.t_steps + 1u <= kBkCands &&
+           bucket_search_pays(n, plan.bits, plan.t_steps + 1u);
 }
 
-size_t bucket_search_end(uint64_t n, size_t at) { return n >= QP_BUCKET_MIN_N ? bucket_layout(n, at).end : at; }
+// (2 bit is what it takes first; a longer sweep than it can take asks for no less than the longest that it can)
+bool bucket_search_wanted(uint64_t n, uint32_t t_steps, uint32_t stride)
+{
+    return stride <= 1u && bucket_search_pays(n, 2u, min(t_steps + 1u, kBkCands));
+}
+
+size_t bucket_search_end(uint64_t n, size_t at) { return bucket_layout(n, at).end; }
 
 BucketSetup bucket_setup_args(uint64_t n, const SearchPlan &plan, void *ws)
 {

@@ -24,7 +24,7 @@ VARIANTS = {
     # bf16 sweeps below the value table's own size on a table that the search builds after two-pass statistics
     "pairs": ["-DQP_VALUE_TABLE_MIN_PAIRS=20000", "-DQP_VALUE_TABLE_SEARCH_MIN_N=1000"],
     # the search by value buckets on tiny tensors, a few hundred buckets
-    "bucket": ["-DQP_TILE_SEARCH_MAX_N=0", "-DQP_BUCKET_MIN_N=1000", "-DQP_BUCKET_TILES=3", "-DQP_BUCKET_SUM_BLOCKS=2",
+    "bucket": ["-DQP_TILE_SEARCH_MAX_N=0", "-DQP_BUCKET_MIN_N=1000", "-DQP_BUCKET_LEAST_SAVING=-1e9", "-DQP_BUCKET_TILES=3", "-DQP_BUCKET_SUM_BLOCKS=2",
                "-DQP_BUCKET_WIDTH=512", "-DQP_BUCKET_DEPTH=0x1p-3", "-DQP_BUCKET_SEGMENT=2500u", "-DQP_SEARCH_FILL_BLOCKS=8"],
     # as "streaming", and a coarse-to-fine search runs its two sweeps on the streaming kernel: the sequence that
     # the library refuses because its only GPU run faulted (the macro exists for this build alone)

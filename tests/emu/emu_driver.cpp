@@ -1,6 +1,7 @@
 // TEST INFRASTRUCTURE ONLY: drives the library's C ABI on the CPU emulation (host memory stands in
 // for device memory) and writes everything it produced to files, for comparison with the oracle.
-//   emu_driver route <n> <dtype 0|1> <t_steps> <stride>: only names the search that such a tensor takes
+//   emu_driver route <n> <dtype 0|1> <t_steps> <stride> [<bits>]: only names the search that such a tensor takes (of 16 bits; the
+//   caller's rounds of 13); with bits also whether a workspace of such a call has room for value buckets
 //   emu_driver <in.bin> <n> <dtype 0|1> <bits> <t_steps> <dist> <flags> <stride> <nbins> <cus> <outdir> [cands_per_round]
 #include <hip/hip_runtime.h>
 
@@ -45,12 +46,30 @@ static void release(void *p)
 
 int main(int argc, char **argv)
 {
-    if (argc == 6 && std::string(argv[1]) == "route") {
+    if ((argc == 6 || argc == 7) && std::string(argv[1]) == "route") {
         const uint64_t n = strtoull(argv[2], nullptr, 10);
         qp::SearchPlan plan{};
         plan.t_steps = (uint32_t)atoi(argv[4]);
         plan.stride = (uint32_t)atoi(argv[5]);
-        puts(qp::searches_value_table(n, atoi(argv[3]), plan) ? "table" : qp::tile_search_eligible(n, plan) ? "tile" : "streaming");
+        plan.bits = argc == 7 ? (uint32_t)atoi(argv[6]) : 16u;
+        plan.bucket_room = 1u;
+        const bool streams = !qp::searches_value_table(n, atoi(argv[3]), plan) && !qp::tile_search_eligible(n, plan);
+        const bool tile = plan.stride > 1u || (argc == 7 && plan.t_steps + 1u <= 13u);
+        if (streams && !tile && qp::bucket_search_eligible(n, atoi(argv[3]), plan)) {
+            puts("buckets");
+        } else {
+            puts(qp::searches_value_table(n, atoi(argv[3]), plan) ? "table" : !streams || (argc == 7 && tile) ? "tile" : "streaming");
+        }
+        if (argc == 7) {
+            qp_search_cfg_t cfg;
+            qp_default_search_cfg(&cfg);
+            cfg.t_steps = plan.t_steps;
+            if (plan.stride > 1u) {
+                cfg.flags = QP_SEARCH_COARSE_TO_FINE;
+                cfg.coarse_stride = plan.stride;
+            }
+            puts(qp_workspace_bytes(n, &cfg) > (4u << 20) ? "room" : "no room");
+        }
         return 0;
     }
     if (argc != 12 && argc != 13) { fprintf(stderr, "usage: see source\n"); return 2; }

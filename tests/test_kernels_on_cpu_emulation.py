@@ -286,6 +286,28 @@ ROUTES = [((594_059, 1, 100, 1), "tile"), ((594_060, 1, 100, 1), "table"), ((594
           ((117_188, 1, 511, 1), "table"), ((234_374, 1, 255, 1), "tile"), ((234_375, 1, 255, 1), "table")]
 
 
+# (n, t, stride, bits) -> the search of an fp32 tensor and whether its workspace has room for value buckets: their cost hardly goes with
+# the candidates, the streaming search's does
+BUCKET_ROUTES = [((9_682_944, 100, 1, 2), "buckets", "room"), ((9_682_944, 100, 1, 8), "buckets", "room"),
+                 ((9_682_944, 20, 1, 2), "streaming", "no room"), ((9_682_944, 42, 1, 2), "streaming", "no room"),
+                 ((9_682_944, 43, 1, 2), "buckets", "room"), ((9_682_944, 55, 1, 8), "streaming", "room"),
+                 ((9_682_944, 63, 1, 8), "buckets", "room"), ((9_682_944, 100, 1, 16), "streaming", "room"),
+                 ((9_682_944, 12, 1, 2), "tile", "no room"), ((9_682_944, 100, 10, 2), "tile", "no room"),
+                 ((9_682_944, 127, 1, 8), "buckets", "room"), ((9_682_944, 128, 1, 8), "streaming", "room"),
+                 ((2_621_441, 100, 1, 3), "streaming", "no room"), ((2_621_442, 100, 1, 3), "buckets", "room"),
+                 ((3_222_223, 13, 1, 3), "streaming", "no room"), ((4_194_305, 100, 1, 4), "streaming", "room"),
+                 ((4_194_306, 100, 1, 4), "buckets", "room"), ((4_194_306, 100, 1, 8), "buckets", "room"),
+                 ((16_777_216, 36, 1, 2), "buckets", "room"), ((16_777_216, 33, 1, 2), "streaming", "no room"),
+                 ((2_097_152, 127, 1, 2), "tile", "no room"), ((30_000_000, 30, 1, 2), "streaming", "no room")]
+
+
+@pytest.mark.parametrize("call,search,room", BUCKET_ROUTES, ids=["_".join(map(str, c)) for c, _, _ in BUCKET_ROUTES])
+def test_which_fp32_searches_go_by_buckets(drivers, call, search, room):
+    n, t, stride, bits = call
+    p = subprocess.run([drivers["default"], "route", str(n), "0", str(t), str(stride), str(bits)], capture_output=True, timeout=60)
+    assert p.returncode == 0 and p.stdout.decode().split("\n")[:2] == [search, room]
+
+
 def test_the_pairs_build_takes_the_table(drivers):
     for n, t, search in ((7_001, 3, "table"), (3_001, 6, "table"), (999, 100, "tile"), (5_001, 2, "tile")):
         p = subprocess.run([drivers["pairs"], "route", str(n), "1", str(t), "1"], capture_output=True, timeout=60)
