@@ -20,6 +20,9 @@ constexpr uint32_t kBkCands = 128;           // most candidates of a sweep
 #ifndef QP_BUCKET_DEPTH
 #define QP_BUCKET_DEPTH 0x1p-10              // smallest element that has a bucket, as a share of |mean| + s_E
 #endif
+#ifndef QP_BUCKET_DENSE
+#define QP_BUCKET_DENSE 5.0                  // one end of a dense sweep over the other: thresholds as many as at twice the coarser end
+#endif
 #ifndef QP_BUCKET_SEGMENT
 #define QP_BUCKET_SEGMENT (1u << 24)         // elements that are sorted at a time (bounds the workspace: 67 MB)
 #endif
@@ -97,7 +100,8 @@ struct BucketSetup {
     BucketPlan *plan;       // null: no such search follows
     uint32_t *totals;
     uint32_t words;         // of totals
-    uint32_t width;         // most buckets of a sign
+    uint32_t width;         // most buckets of a sign ...
+    uint32_t dense_width;   // ... of a dense sweep (see bucket_plan); 0: such a sweep is left to the streaming kernel
 };
 
 // One block, behind setup_candidates: where the buckets lie, and whether this tensor suits them.
@@ -112,18 +116,21 @@ __device__ inline void bucket_plan(const BucketSetup &b, const GridModel &g, int
     if (tid % kWave == 0) sh_inv[tid / kWave] = inv;
     __syncthreads();
     if (tid != 0) return;
-    for (uint32_t w = 1; w < blockDim.x / kWave; ++w) inv += sh_inv[w];
+    for (uint32_t w = 1; w < (ncand + kWave - 1) / kWave; ++w) inv += sh_inv[w];
+    // b_R far below b_E (after ReLU or GELU, by 10 to 20): most candidates' thresholds lie much closer than the first one's
+    const bool dense = fmax(g.s_e, g.s_r) > QP_BUCKET_DENSE * fmin(g.s_e, g.s_r);
+    const uint32_t width = dense && b.dense_width ? b.dense_width : b.width;
     const double am = fabs(g.mean) + g.s_e, reach = 16.0 * g.s_e;
     const double lo = fmax(am * QP_BUCKET_DEPTH, fabs(g.mean) - reach), hi = fabs(g.mean) + reach;
     const uint32_t plo = __float_as_uint((float)lo), phi = __float_as_uint((float)hi);
     const bool ok = g.s_e > 0.0 && hi >= lo && plo >= (27u << 23) && phi <= (227u << 23);
     uint32_t shift = 8u;
     if (ok)
-        while ((phi >> shift) - (plo >> shift) + 1u > b.width) ++shift;
+        while ((phi >> shift) - (plo >> shift) + 1u > width) ++shift;
     // thresholds that a typical bucket holds, all candidates together
     const double cell = (double)__uint_as_float(__float_as_uint((float)am) & 0x7f800000u) * (double)(1u << shift) * 0x1p-23;
     BucketPlan p{};
-    p.unsuited = (!ok || !safe || shift > 19u || !(inv * cell <= 250.0)) ? 1u : 0u;
+    p.unsuited = (!ok || !safe || (dense && b.dense_width == 0u) || shift > 19u || !(inv * cell <= 250.0)) ? 1u : 0u;
     p.fallback = p.unsuited;
     p.shift = shift;
     p.first = plo >> shift;

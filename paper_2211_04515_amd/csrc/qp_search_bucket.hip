@@ -1045,29 +1045,32 @@ __global__ __launch_bounds__(kBsThreads, 4) void k_bucket_sum(BucketArgs a)
 // million); sorting, listing and summing hardly know how many candidates there are.  Sender path by streaming / by buckets, Laplace
 // data at 2 bit: 9.7 M elements 81 / 106 us at t = 20, 117 / 109 at 42, 207 / 110 at 100; 4.3 M 81 / 81 at 55, 113 / 82 at 100;
 // 30 M 227 / 258 at 30, 349 / 262 at 55; 2.7 M 75 / 72 at 85.  At 8 bit 9.7 M 140 / 135 at 55, 4.3 M 90 / 99 at 70, 113 / 103 at 100.
-static double bucket_saving(uint64_t n, uint32_t bits, uint32_t ncand)
+// A dense sweep (see bucket_plan) has several times the pieces.  Post-GELU data, 2 bit: 9.7 M 134 / 133 at 55, 204 / 141 at 100; 3.5 M
+// 98 / 98 at 100; 8 bit: 4.3 M 113 / 125, 5 M 126 / 123 at 100.
+static double bucket_saving(uint64_t n, uint32_t bits, uint32_t ncand, bool dense)
 {
     const double m = 1e-6 * (double)n, segments = (double)ceil_div_u64(n, QP_BUCKET_SEGMENT);
     const double fixed = bits <= 3u ? 31.0 : bits <= 4u ? 30.0 : bits <= 6u ? 32.0 : 36.0;
     const double each = bits <= 3u ? 3.75 : bits <= 6u ? 5.25 : 6.0;
-    return 0.16 * m * (double)ncand - fixed - each * m - 15.0 * (segments - 1.0);
+    const double more = !dense ? 0.0 : (bits <= 3u ? 10.0 : 4.0) + 2.0 * m;
+    return 0.16 * m * (double)ncand - fixed - each * m - 15.0 * (segments - 1.0) - more;
 }
-static bool bucket_search_pays(uint64_t n, uint32_t bits, uint32_t ncand)
+static bool bucket_search_pays(uint64_t n, uint32_t bits, uint32_t ncand, bool dense)
 {
     if (bits > 3u ? n < 2u * QP_BUCKET_MIN_N : 4u * n < 5u * QP_BUCKET_MIN_N) return false;
-    return bucket_saving(n, bits, ncand) >= QP_BUCKET_LEAST_SAVING;
+    return bucket_saving(n, bits, ncand, dense) >= QP_BUCKET_LEAST_SAVING;
 }
 
 bool bucket_search_eligible(uint64_t n, int dtype, const SearchPlan &plan)
 {
     return plan.bucket_room && dtype == QP_F32 && plan.bits <= 8u && plan.stride <= 1u && plan.t_steps + 1u <= kBkCands &&
-           bucket_search_pays(n, plan.bits, plan.t_steps + 1u);
+           bucket_search_pays(n, plan.bits, plan.t_steps + 1u, false);
 }
 
 // (2 bit is what it takes first; a longer sweep than it can take asks for no less than the longest that it can)
 bool bucket_search_wanted(uint64_t n, uint32_t t_steps, uint32_t stride)
 {
-    return stride <= 1u && bucket_search_pays(n, 2u, min(t_steps + 1u, kBkCands));
+    return stride <= 1u && bucket_search_pays(n, 2u, min(t_steps + 1u, kBkCands), false);
 }
 
 size_t bucket_search_end(uint64_t n, size_t at) { return bucket_layout(n, at).end; }
@@ -1076,8 +1079,15 @@ BucketSetup bucket_setup_args(uint64_t n, const SearchPlan &plan, void *ws)
 {
     const BucketLayout l = bucket_layout(n, plan.bucket_at);
     char *w = static_cast<char *>(ws);
+    // Few wide buckets cost the least to list, narrow ones keep their sums in registers.  Sender path with 256 / 512 / 1024 of a sign,
+    // 9.7 M elements, t = 100: Laplace data at 2 bit 110 / 113 / 125 us, 4 bit 121 / 117 / 120, 6 bit 119 / 123 / 130, 8 bit 258 (lists
+    // too long) / 147 / 143; Gauss and Laplace mixed, 6 bit 125 / 119 / 124, 8 bit 258 / 144 / 134; after GELU at 2 bit 241 / 151 / 142
+    // (4.3 M elements 120 / 104 / 112), 3 bit 174 / 142 / 139, 6 bit 161 / 153 / 158.
+    const uint32_t width = plan.bits <= 3u ? kBkWidth / 4u : plan.bits <= 6u ? kBkWidth / 2u : kBkWidth;
+    const uint32_t dense_width = plan.bits <= 3u ? (n < (1u << 23) ? kBkWidth / 2u : kBkWidth) : width;
     return BucketSetup{reinterpret_cast<BucketPlan *>(w + l.plan), reinterpret_cast<uint32_t *>(w + l.totals),
-                       l.segments * (kBkKeys + 1u), plan.bits <= 3u ? kBkWidth / 4u : plan.bits <= 4u ? kBkWidth / 2u : kBkWidth};
+                       l.segments * (kBkKeys + 1u), width,
+                       bucket_search_pays(n, plan.bits, plan.t_steps + 1u, true) ? dense_width : 0u};
 }
 
 hipError_t launch_bucket_search(const void *x, uint64_t n, const SearchPlan &plan, void *ws, const uint32_t **fallback, hipStream_t s)

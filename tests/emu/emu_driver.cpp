@@ -56,7 +56,8 @@ int main(int argc, char **argv)
         const bool streams = !qp::searches_value_table(n, atoi(argv[3]), plan) && !qp::tile_search_eligible(n, plan);
         const bool tile = plan.stride > 1u || (argc == 7 && plan.t_steps + 1u <= 13u);
         if (streams && !tile && qp::bucket_search_eligible(n, atoi(argv[3]), plan)) {
-            puts("buckets");
+            plan.bucket_at = 0u;
+            puts(qp::bucket_setup_args(n, plan, reinterpret_cast<void *>(uintptr_t{1} << 20)).dense_width ? "buckets" : "buckets, or streaming if dense");
         } else {
             puts(qp::searches_value_table(n, atoi(argv[3]), plan) ? "table" : !streams || (argc == 7 && tile) ? "tile" : "streaming");
         }

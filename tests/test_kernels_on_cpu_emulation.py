@@ -290,14 +290,14 @@ ROUTES = [((594_059, 1, 100, 1), "tile"), ((594_060, 1, 100, 1), "table"), ((594
 # the candidates, the streaming search's does
 BUCKET_ROUTES = [((9_682_944, 100, 1, 2), "buckets", "room"), ((9_682_944, 100, 1, 8), "buckets", "room"),
                  ((9_682_944, 20, 1, 2), "streaming", "no room"), ((9_682_944, 42, 1, 2), "streaming", "no room"),
-                 ((9_682_944, 43, 1, 2), "buckets", "room"), ((9_682_944, 55, 1, 8), "streaming", "room"),
-                 ((9_682_944, 63, 1, 8), "buckets", "room"), ((9_682_944, 100, 1, 16), "streaming", "room"),
+                 ((9_682_944, 43, 1, 2), "buckets, or streaming if dense", "room"), ((9_682_944, 55, 1, 8), "streaming", "room"),
+                 ((9_682_944, 63, 1, 8), "buckets, or streaming if dense", "room"), ((9_682_944, 100, 1, 16), "streaming", "room"),
                  ((9_682_944, 12, 1, 2), "tile", "no room"), ((9_682_944, 100, 10, 2), "tile", "no room"),
                  ((9_682_944, 127, 1, 8), "buckets", "room"), ((9_682_944, 128, 1, 8), "streaming", "room"),
-                 ((2_621_441, 100, 1, 3), "streaming", "no room"), ((2_621_442, 100, 1, 3), "buckets", "room"),
+                 ((2_621_441, 100, 1, 3), "streaming", "no room"), ((2_621_442, 100, 1, 3), "buckets, or streaming if dense", "room"),
                  ((3_222_223, 13, 1, 3), "streaming", "no room"), ((4_194_305, 100, 1, 4), "streaming", "room"),
-                 ((4_194_306, 100, 1, 4), "buckets", "room"), ((4_194_306, 100, 1, 8), "buckets", "room"),
-                 ((16_777_216, 36, 1, 2), "buckets", "room"), ((16_777_216, 33, 1, 2), "streaming", "no room"),
+                 ((4_194_306, 100, 1, 4), "buckets", "room"), ((4_194_306, 100, 1, 8), "buckets, or streaming if dense", "room"),
+                 ((16_777_216, 36, 1, 2), "buckets, or streaming if dense", "room"), ((16_777_216, 33, 1, 2), "streaming", "no room"),
                  ((2_097_152, 127, 1, 2), "tile", "no room"), ((30_000_000, 30, 1, 2), "streaming", "no room")]
 
 
