@@ -10,12 +10,13 @@ outliers), resident in HBM before the timed region; passes rotate over 16 distin
 input/output buffer sets (> 600 MB) so that the tensor is not served from the 256 MB
 Infinity Cache left warm by the previous pass.  The six passes are independent jobs and are
 issued round-robin over `--streams` HIP streams (default 3, default priority, a workspace
-each), so that the HBM-bound steps of one pass run beside the ALU-bound search of another;
+each), so that the HBM-bound steps of one pass run beside the search of another;
 `one_stream` repeats the timed steps with everything on one stream.
 
 Prints ONE JSON line.  `value` is activation bytes entering the path per second.
-`roofline` describes the kernel that dominates the step (the directed-search kernel, bound by
-plain vector ALU work); `roofline_pack` / `roofline_unpack` / `roofline_stats` describe the
+`roofline` describes the kernels that dominate the step (the directed search by value buckets of the
+passes at up to 8 bit, against the one read of the tensor that any search needs; `roofline_search_16_bit` the
+element-by-element search of the pass at 16 bit, bound by plain vector ALU work); `roofline_pack` / `roofline_unpack` / `roofline_stats` describe the
 HBM-bound kernels.  The other configurations ride in the same line, each with roofline-shaped
 entries of its own: `c3_vit_large_fp32` (64x197x1024 post-GELU, cands_per_round 32),
 `large_tensor_bf16` (C5: 256x577x1024 bf16, the largest, HBM-honest by itself),
@@ -99,6 +100,11 @@ def alu_entry(kernel, n, ncand, us, traffic, timed):
     return {"kernel": kernel, "bound": "alu", "achieved": a, "peak": VALU_PEAK_TLANEOPS, "unit": "Tlaneop/s",
             "frac": a / VALU_PEAK_TLANEOPS, "algorithmic_laneops": ops, "traffic": traffic, "us_per_launch": us,
             "timed": timed}
+
+
+def bucket_entry(n, us, timed):
+    """A search by value buckets: of its work only the tensor's one read is the same whatever the way it goes."""
+    return hbm_entry("k_bucket_sort + k_bucket_sum (+ k_search_setup, k_search_pick)", 4 * n, us, None, None, timed)
 
 
 def main() -> int:
@@ -290,10 +296,16 @@ def c2_leg(qp, si, torch, x_host, args, timed_reps, side_streams):
         for k, s in enumerate(("stats", "search", "pack", "unpack")):
             stage[s].append(e[k].elapsed_time(e[k + 1]) * 1e3)
     mean = lambda v: float(sum(v) / len(v))
-    search_us = mean(stage["search"])       # setup kernel (a few microseconds) + search kernel
-    roofline = alu_entry("k_search_mse<fp32,13> (+ k_search_setup)", n, 101, search_us, TRAFFIC_RATIO["c2_search_bytes"],
-                         "HIP events around every search launch in an instrumented repetition of the timed steps")
-    roofline["traffic_source"] = TRAFFIC_SOURCE["c2"]
+    search_us = mean(stage["search"])       # every kernel of the search, all six bitwidths
+    by_bits = {b: mean([e[1].elapsed_time(e[2]) * 1e3 for bits, e in timers if bits == b]) for b in bits_set}
+    events = "HIP events around every search in an instrumented repetition of the timed steps"
+    roofline = bucket_entry(n, mean([by_bits[b] for b in bits_set if b <= 8]), events + ", the passes at up to 8 bit")
+    roofline["us_per_launch_by_bitwidth"] = {str(b): by_bits[b] for b in bits_set}
+    roofline_16 = None
+    if 16 in by_bits:
+        roofline_16 = alu_entry("k_search_mse<fp32,13> (+ k_search_setup)", n, 101, by_bits[16], TRAFFIC_RATIO["c2_search_bytes"],
+                                events + ", the passes at 16 bit")
+        roofline_16["traffic_source"] = TRAFFIC_SOURCE["c2"]
 
     rot = (f"{args.kernel_reps} back-to-back launches between two HIP events, every stream rotating over at least {NBUF} distinct "
            f"buffers and {COLD_BYTES / 1e6:.0f} MB")
@@ -394,7 +406,7 @@ def c2_leg(qp, si, torch, x_host, args, timed_reps, side_streams):
         "dsaciq_histogram_fit_us_per_tensor": th,
         "dsaciq_coarse_to_fine_us_per_tensor": tc,
         "step_with_search_at_2_to_4_bit_only": policy,
-        "roofline": roofline, "roofline_pack": r_pack, "roofline_unpack": r_unpack, "roofline_stats": r_stats,
+        "roofline": roofline, "roofline_search_16_bit": roofline_16, "roofline_pack": r_pack, "roofline_unpack": r_unpack, "roofline_stats": r_stats,
         "hbm_copy_reference": copy_ref, "hbm_fill_reference": fill_ref,
         "per_bitwidth": per_bits,
         "size_sweep_4bit": sweep,
@@ -464,8 +476,7 @@ def c3_leg(qp, si, torch, timed_reps, reps):
         out["per_bitwidth"][str(b)] = {
             "j_star": res.j_star, "mse_star_over_mse_aciq": res.mse_star / res.mse_aciq,
             "sender_path_us_per_tensor": tsend,
-            "roofline_search": alu_entry("k_search_mse<fp32,13> (+ k_search_setup)", n, 101, tsr, None,
-                                         "24 back-to-back searches over rotating inputs between two HIP events"),
+            "roofline_search": bucket_entry(n, tsr, "24 back-to-back searches over rotating inputs between two HIP events"),
             "roofline_pack": hbm_entry(f"k_quant_pack<{b},fp32>", byts, tp, None, None, rot),
             "roofline_unpack": hbm_entry(f"k_unpack_dequant<{b}>", byts, tu, None, None, rot)}
         del packs
