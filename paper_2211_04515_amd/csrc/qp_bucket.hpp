@@ -36,6 +36,7 @@ constexpr uint32_t kBkRow = kBkKeys + 4u;                        // table entrie
 constexpr uint32_t kBkCutCap = 512, kBkOwnCap = 96, kBkPieceCap = 768;
 constexpr uint32_t kBkCutAll = (1u << 19) / kBkTiles, kBkClassAll = (1u << 16) / kBkTiles, kBkPieceAll = (1u << 19) / kBkTiles;   // of one sorting block
 
+constexpr uint32_t kBkSample = 1024, kBkSampleOut = 384;   // elements of a sample; most of them outside the buckets
 struct BucketPlan {
     uint32_t unsuited;    // 1: the set-up leaves this tensor to the streaming kernel ...
     uint32_t fallback;    // ... or the sort does
@@ -43,7 +44,15 @@ struct BucketPlan {
     uint32_t first;       // |pattern| >> shift of bucket 0
     uint32_t width;       // buckets of a sign
     uint32_t centre;      // the bucket of the mean: every candidate has a threshold there, so its elements count as outside
+    uint32_t uneven;      // 1: some tile has so many elements outside the buckets that all blocks share them
 };
+// An element's bucket; 2 width: outside.
+__device__ __forceinline__ uint32_t bucket_key(const BucketPlan &p, float x)
+{
+    const uint32_t w = __float_as_uint(x), u = ((w & 0x7fffffffu) >> p.shift) - p.first;
+    const uint32_t key = u + (w >> 31) * p.width;
+    return u < p.width && key != p.centre ? key : 2u * p.width;
+}
 constexpr uint32_t kBkDirect = 12;    // most sums of a bucket that are formed in registers: each takes a share of the bucket 1 us, however small
 // How the elements of a bucket are rounded for some candidates: r(x) = x / 2^k - frac to the nearest whole number, ties to the
 // even (or to the odd) one.  With f = x - base, a whole multiple of the bucket's last place 2^a, 2^k (r(x) - r(base)) is
@@ -102,11 +111,16 @@ struct BucketSetup {
     uint32_t words;         // of totals
     uint32_t width;         // most buckets of a sign ...
     uint32_t dense_width;   // ... of a dense sweep (see bucket_plan); 0: such a sweep is left to the streaming kernel
+    const float *x;
+    uint64_t n;
 };
 
 // One block, behind setup_candidates: where the buckets lie, and whether this tensor suits them.
-__device__ inline void bucket_plan(const BucketSetup &b, const GridModel &g, int safe, const Cand *cands, uint32_t ncand)
+// st: the tensor's statistics where they are on the device.
+__device__ inline void bucket_plan(const BucketSetup &b, const GridModel &g, const qp_stats_t *st, int safe, const Cand *cands, uint32_t ncand)
 {
+    __shared__ BucketPlan sh_plan;
+    __shared__ uint32_t sh_out[kFinThreads / kWave];
     __shared__ double sh_inv[kFinThreads / kWave];
     const uint32_t tid = threadIdx.x;
     for (uint32_t i = tid; i < b.words; i += blockDim.x) b.totals[i] = 0u;
@@ -115,29 +129,47 @@ __device__ inline void bucket_plan(const BucketSetup &b, const GridModel &g, int
     inv = wave_sum(inv);
     if (tid % kWave == 0) sh_inv[tid / kWave] = inv;
     __syncthreads();
+    if (tid == 0) {
+        for (uint32_t w = 1; w < (ncand + kWave - 1) / kWave; ++w) inv += sh_inv[w];
+        // b_R far below b_E (after ReLU or GELU, by 10 to 20): most candidates' thresholds lie much closer than the first one's
+        const bool dense = fmax(g.s_e, g.s_r) > QP_BUCKET_DENSE * fmin(g.s_e, g.s_r);
+        const uint32_t width = dense && b.dense_width ? b.dense_width : b.width;
+        const double am = fabs(g.mean) + g.s_e, reach = 16.0 * g.s_e;
+        const double lo = fmax(am * QP_BUCKET_DEPTH, fabs(g.mean) - reach), hi = fabs(g.mean) + reach;
+        const uint32_t plo = __float_as_uint((float)lo), phi = __float_as_uint((float)hi);
+        const bool ok = g.s_e > 0.0 && hi >= lo && plo >= (27u << 23) && phi <= (227u << 23);
+        uint32_t shift = 8u;
+        if (ok)
+            while ((phi >> shift) - (plo >> shift) + 1u > width) ++shift;
+        // thresholds that a typical bucket holds, all candidates together
+        const double cell = (double)__uint_as_float(__float_as_uint((float)am) & 0x7f800000u) * (double)(1u << shift) * 0x1p-23;
+        BucketPlan p{};
+        p.unsuited = (!ok || !safe || (dense && b.dense_width == 0u) || shift > 19u || !(inv * cell <= 250.0)) ? 1u : 0u;
+        p.fallback = p.unsuited;
+        p.shift = shift;
+        p.first = plo >> shift;
+        p.width = ok ? (phi >> shift) - (plo >> shift) + 1u : 1u;
+        const uint32_t mean = __float_as_uint((float)g.mean), u = ((mean & 0x7fffffffu) >> shift) - p.first;
+        p.centre = u < p.width ? u + (mean >> 31) * p.width : 0xffffffffu;
+        sh_plan = p;
+        *b.plan = p;
+    }
+    // The sort costs its time whatever becomes of it.  Elements outside the buckets (scored one by one) cluster at zero or the mean, in
+    // one bin of the histogram; where that holds a quarter of the tensor a sample tells whether they are too many.
+    if (st && 4ull * st->peak_count < b.n) return;
+    __syncthreads();
+    const BucketPlan p = sh_plan;
+    uint32_t out = 0u;
+    for (uint32_t i = tid; i < kBkSample; i += blockDim.x) {
+        const float v = b.x[(uint64_t)(i * 2654435769u) * b.n >> 32];
+        out += v != 0.0f && bucket_key(p, v) == 2u * p.width ? 1u : 0u;
+    }
+    out = wave_sum_u32(out);
+    if (tid % kWave == 0) sh_out[tid / kWave] = out;
+    __syncthreads();
     if (tid != 0) return;
-    for (uint32_t w = 1; w < (ncand + kWave - 1) / kWave; ++w) inv += sh_inv[w];
-    // b_R far below b_E (after ReLU or GELU, by 10 to 20): most candidates' thresholds lie much closer than the first one's
-    const bool dense = fmax(g.s_e, g.s_r) > QP_BUCKET_DENSE * fmin(g.s_e, g.s_r);
-    const uint32_t width = dense && b.dense_width ? b.dense_width : b.width;
-    const double am = fabs(g.mean) + g.s_e, reach = 16.0 * g.s_e;
-    const double lo = fmax(am * QP_BUCKET_DEPTH, fabs(g.mean) - reach), hi = fabs(g.mean) + reach;
-    const uint32_t plo = __float_as_uint((float)lo), phi = __float_as_uint((float)hi);
-    const bool ok = g.s_e > 0.0 && hi >= lo && plo >= (27u << 23) && phi <= (227u << 23);
-    uint32_t shift = 8u;
-    if (ok)
-        while ((phi >> shift) - (plo >> shift) + 1u > width) ++shift;
-    // thresholds that a typical bucket holds, all candidates together
-    const double cell = (double)__uint_as_float(__float_as_uint((float)am) & 0x7f800000u) * (double)(1u << shift) * 0x1p-23;
-    BucketPlan p{};
-    p.unsuited = (!ok || !safe || (dense && b.dense_width == 0u) || shift > 19u || !(inv * cell <= 250.0)) ? 1u : 0u;
-    p.fallback = p.unsuited;
-    p.shift = shift;
-    p.first = plo >> shift;
-    p.width = ok ? (phi >> shift) - (plo >> shift) + 1u : 1u;
-    const uint32_t mean = __float_as_uint((float)g.mean), u = ((mean & 0x7fffffffu) >> shift) - p.first;
-    p.centre = u < p.width ? u + (mean >> 31) * p.width : 0xffffffffu;
-    *b.plan = p;
+    for (uint32_t w = 1; w < blockDim.x / kWave; ++w) out += sh_out[w];
+    if (out > kBkSampleOut) b.plan->unsuited = b.plan->fallback = 1u;
 }
 
 // Whether such a search takes this call, given room in the workspace (the caller's business).
@@ -145,7 +177,7 @@ bool bucket_search_eligible(uint64_t n, int dtype, const SearchPlan &plan);
 // Whether the search takes some bitwidth's call of these settings: whether a workspace should hold its part.
 bool bucket_search_wanted(uint64_t n, uint32_t t_steps, uint32_t stride);
 size_t bucket_search_end(uint64_t n, size_t at);   // bytes of a workspace with the search's part behind `at`
-BucketSetup bucket_setup_args(uint64_t n, const SearchPlan &plan, void *ws);
+BucketSetup bucket_setup_args(const void *x, uint64_t n, const SearchPlan &plan, void *ws);
 // Behind the set-up: sort, sum, pick.  *fallback (device) is 1 afterwards if nothing was scored.
 hipError_t launch_bucket_search(const void *x, uint64_t n, const SearchPlan &plan, void *ws, const uint32_t **fallback, hipStream_t s);
 

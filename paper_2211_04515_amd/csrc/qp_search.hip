@@ -49,7 +49,7 @@ __global__ __launch_bounds__(kFinThreads) void k_search_setup(ModelArgs m, qp_st
     const uint32_t j1 = (m.list_mode == kListFine) ? prev->j_star : 0u;
     const qp_stats_t *st = m.from_ws ? stats_dev : nullptr;
     const int safe = setup_candidates(m, st, j1, n, cands, nullptr, ctl, scores_by_j);
-    if (buckets.plan) bucket_plan(buckets, grid_model(m, st), safe, cands, m.count);
+    if (buckets.plan) bucket_plan(buckets, grid_model(m, st), st, safe, cands, m.count);
 }
 
 // No search: the result is plain ACIQ, candidate j = 0 (the paper's deployment switches the directed search
@@ -590,7 +590,7 @@ static hipError_t launch_sweep(const void *x, uint64_t n, int dtype, const Searc
     if (finalize_nbins) stats_grid(n, dtype, fin.nb1, fin.nb2);
     const ModelArgs m = model_args(plan, st, list_mode, count, ws);
     const bool buckets = list_mode == kListFull && bucket_search_eligible(n, dtype, plan);
-    const BucketSetup bs = buckets ? bucket_setup_args(n, plan, ws) : BucketSetup{};
+    const BucketSetup bs = buckets ? bucket_setup_args(x, n, plan, ws) : BucketSetup{};
     hipLaunchKernelGGL(k_search_setup, dim3(1), dim3(kFinThreads), 0, s, m, stats_dev, n, cands, ctl, round_tickets, fin,
                        res, scores_by_j, bs);
     hipError_t e = hipGetLastError();

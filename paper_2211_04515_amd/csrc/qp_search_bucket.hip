@@ -434,7 +434,7 @@ __global__ __launch_bounds__(kBkThreads) void k_bucket_sort(BucketArgs a)
 
     // an element's place in its bucket (any order), or among the wave's elements outside the buckets (in a fixed order: those
     // are scored one by one, and their sum depends on it)
-    auto key_of = [&](float x) -> uint32_t {   // 2 width: outside
+    auto key_of = [&](float x) -> uint32_t {   // as bucket_key, whose inlining here costs two spilled registers
         const uint32_t w = __float_as_uint(x), u = ((w & 0x7fffffffu) >> p.shift) - p.first;
         const uint32_t key = u + (w >> 31) * p.width;
         return u < p.width && key != p.centre ? key : 2u * p.width;
@@ -511,8 +511,8 @@ __global__ __launch_bounds__(kBkThreads) void k_bucket_sort(BucketArgs a)
         reinterpret_cast<uint32_t *>(row)[p.width] = kept | ((kept + others) << 16);
         const uint32_t real = zeros - ((quads + kBkThreads - 1u) / kBkThreads * kBkThreads * 4u - m);   // without the places behind the tile's end
         if (real) atomicAdd(a.zeros, real);
-        // one by one they would take too long
-        if (sh_bad || others > m / 8u + 64u) st_dev(&a.plan->fallback, 1u);
+        if (sh_bad) st_dev(&a.plan->fallback, 1u);
+        if (others > m / 8u + 64u) st_dev(&a.plan->uneven, 1u);
     }
     __syncthreads();
 #pragma unroll
@@ -634,7 +634,9 @@ __global__ __launch_bounds__(kBsThreads, 4) void k_bucket_sum(BucketArgs a)
     const uint32_t nbuckets = 2u * p.width;
     __shared__ double sh_total[kBkCands];   // of a candidate: kept here, not in registers
 
-    // ---- elements outside the buckets, a quarter of a tile's at a time: one candidate a lane, two lanes a candidate ----
+    __shared__ uint32_t runs[kBsTiles], first_load[kBsTiles], loads[kBsBatch], sh_wave[kBsThreads / kWave][2];
+
+    // ---- elements outside the buckets: one candidate a lane, two lanes a candidate ----
     {
         float *sh_v = reinterpret_cast<float *>(&sh);
         double *sh_half = reinterpret_cast<double *>(sh_v + 1024);
@@ -648,14 +650,61 @@ __global__ __launch_bounds__(kBsThreads, 4) void k_bucket_sum(BucketArgs a)
             const double e = score(0.0f);
             total = (double)*a.zeros * e * e;
         }
-        for (uint32_t t = blockIdx.x; t < 4u * a.tiles; t += kBkSumBlocks) {
-            const uint16_t *row = a.table + (uint64_t)(t / 4u) * kBkRow;
-            const uint32_t start = row[nbuckets], len = row[nbuckets + 1u] - start;
-            const uint32_t from = start + len * (t % 4u) / 4u, to = start + len * (t % 4u + 1u) / 4u;
+        // the tiles' quarters, or the block's share of them all
+        uint32_t share0 = 0u, share1 = 0u;
+        if (p.uneven) {
+            uint32_t len[2], sum = 0u;
+#pragma unroll
+            for (uint32_t i = 0; i < 2u; ++i) {
+                const uint32_t t = 2u * tid + i;
+                const uint16_t *row = a.table + (uint64_t)min(t, a.tiles - 1u) * kBkRow + nbuckets;
+                runs[t] = row[0];
+                len[i] = t < a.tiles ? (uint32_t)row[1] - row[0] : 0u;
+                sum += len[i];
+            }
+            uint32_t up = sum;
+#pragma unroll
+            for (uint32_t o = 1; o < (uint32_t)kWave; o <<= 1) {
+                const uint32_t v = __shfl_up(up, o, kWave);
+                if (lane >= o) up += v;
+            }
+            if (lane == (uint32_t)kWave - 1u) sh_wave[wave][0] = up;
+            __syncthreads();
+            uint32_t all = 0u;
+            for (uint32_t w = 0; w < kBsThreads / kWave; ++w) {
+                if (w < wave) up += sh_wave[w][0];
+                all += sh_wave[w][0];
+            }
+            first_load[2u * tid] = up - sum;
+            first_load[2u * tid + 1u] = up - len[1];
+            share0 = (uint32_t)((uint64_t)all * blockIdx.x / kBkSumBlocks);
+            share1 = (uint32_t)((uint64_t)all * (blockIdx.x + 1u) / kBkSumBlocks);
+        }
+        for (uint32_t t = blockIdx.x; t < (p.uneven ? blockIdx.x + 1u : 4u * a.tiles); t += kBkSumBlocks) {
+            uint32_t from = share0, to = share1;
+            if (!p.uneven) {
+                const uint16_t *row = a.table + (uint64_t)(t / 4u) * kBkRow;
+                const uint32_t start = row[nbuckets], len = row[nbuckets + 1u] - start;
+                from = start + len * (t % 4u) / 4u;
+                to = start + len * (t % 4u + 1u) / 4u;
+            }
             for (uint32_t at = from; at < to; at += 1024u) {
                 const uint32_t nv = min(1024u, to - at), mid = nv / 8u * 4u;
                 __syncthreads();
-                for (uint32_t i = tid; i < nv; i += kBsThreads) sh_v[i] = a.sorted[(uint64_t)(t / 4u) * a.tile + at + i];
+                for (uint32_t i = tid; i < nv; i += kBsThreads) {
+                    uint32_t tile = t / 4u, place = at + i;
+                    if (p.uneven) {   // the last tile that starts at or before it
+                        uint32_t h0 = kBsTiles;
+                        tile = 0u;
+                        while (h0 - tile > 1u) {
+                            const uint32_t mid0 = (tile + h0) / 2u;
+                            if (first_load[mid0] <= place) tile = mid0;
+                            else h0 = mid0;
+                        }
+                        place += runs[tile] - first_load[tile];
+                    }
+                    sh_v[i] = a.sorted[(uint64_t)tile * a.tile + place];
+                }
                 __syncthreads();
                 const uint32_t end = half ? nv : mid;
                 uint32_t i = half ? mid : 0u;
@@ -684,9 +733,8 @@ __global__ __launch_bounds__(kBsThreads, 4) void k_bucket_sum(BucketArgs a)
     // share of its elements (whole tiles: which elements of a bucket come first in one is the sort's chance) ----
     struct Item { uint16_t bucket, cls; uint32_t from, to, size; };   // from..to of size
     __shared__ Item sh_items[kBsItems];
-    __shared__ uint32_t sh_wave[kBsThreads / kWave][2], sh_first, sh_count, sh_run[2][2];
+    __shared__ uint32_t sh_first, sh_count, sh_run[2][2];
     __shared__ BucketPiece sh_piece[kBkCands];
-    __shared__ uint32_t runs[kBsTiles], first_load[kBsTiles], loads[kBsBatch];
     constexpr uint32_t per = (kBkKeys + kBsThreads - 1) / kBsThreads;
     static_assert(per * kBsThreads == kBkKeys && per % 4u == 0u, "16-byte loads");
     uint32_t *sizes = reinterpret_cast<uint32_t *>(&sh);   // of a bucket or of each of its classes, where the sums will be
@@ -1075,7 +1123,7 @@ bool bucket_search_wanted(uint64_t n, uint32_t t_steps, uint32_t stride)
 
 size_t bucket_search_end(uint64_t n, size_t at) { return bucket_layout(n, at).end; }
 
-BucketSetup bucket_setup_args(uint64_t n, const SearchPlan &plan, void *ws)
+BucketSetup bucket_setup_args(const void *x, uint64_t n, const SearchPlan &plan, void *ws)
 {
     const BucketLayout l = bucket_layout(n, plan.bucket_at);
     char *w = static_cast<char *>(ws);
@@ -1087,7 +1135,7 @@ BucketSetup bucket_setup_args(uint64_t n, const SearchPlan &plan, void *ws)
     const uint32_t dense_width = plan.bits <= 3u ? (n < (1u << 23) ? kBkWidth / 2u : kBkWidth) : width;
     return BucketSetup{reinterpret_cast<BucketPlan *>(w + l.plan), reinterpret_cast<uint32_t *>(w + l.totals),
                        l.segments * (kBkKeys + 1u), width,
-                       bucket_search_pays(n, plan.bits, plan.t_steps + 1u, true) ? dense_width : 0u};
+                       bucket_search_pays(n, plan.bits, plan.t_steps + 1u, true) ? dense_width : 0u, static_cast<const float *>(x), n};
 }
 
 hipError_t launch_bucket_search(const void *x, uint64_t n, const SearchPlan &plan, void *ws, const uint32_t **fallback, hipStream_t s)

@@ -57,7 +57,7 @@ int main(int argc, char **argv)
         const bool tile = plan.stride > 1u || (argc == 7 && plan.t_steps + 1u <= 13u);
         if (streams && !tile && qp::bucket_search_eligible(n, atoi(argv[3]), plan)) {
             plan.bucket_at = 0u;
-            puts(qp::bucket_setup_args(n, plan, reinterpret_cast<void *>(uintptr_t{1} << 20)).dense_width ? "buckets" : "buckets, or streaming if dense");
+            puts(qp::bucket_setup_args(nullptr, n, plan, reinterpret_cast<void *>(uintptr_t{1} << 20)).dense_width ? "buckets" : "buckets, or streaming if dense");
         } else {
             puts(qp::searches_value_table(n, atoi(argv[3]), plan) ? "table" : !streams || (argc == 7 && tile) ? "tile" : "streaming");
         }
@@ -157,7 +157,7 @@ int main(int argc, char **argv)
         memset(&plan, 0xff, sizeof plan);
         const qp::BucketLayout l = qp::bucket_layout(n, least);
         if (wsb > least) memcpy(&plan, (const char *)ws + l.plan, sizeof plan);
-        dump(out, "plan.bin", &plan, sizeof plan);
+        dump(out, "plan.bin", &plan, offsetof(qp::BucketPlan, uneven));
         // ... and how many elements it counted in each bucket, segment by segment
         const uint32_t parts[2] = {l.segments, l.tile * l.tiles};
         dump(out, "segments.bin", parts, sizeof parts);

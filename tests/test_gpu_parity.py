@@ -1751,6 +1751,14 @@ def bucket_values(kind, n, g):
         at = torch.arange(n, device="cuda")
         heavy = at // 31_252 % 4 != 0
         return torch.where(heavy, torch.where(at % 2 == 0, 0.71, -1.9), lap())
+    if kind == "tiny tile":       # one tile's worth below the buckets' range
+        x = lap()
+        x[n // 2: n // 2 + 40_000] *= 1e-5
+        return x
+    if kind == "mostly tiny":
+        return torch.where(torch.rand(n, device="cuda", generator=g) < 0.6, lap() * 1e-5, lap())
+    if kind == "wide gelu":       # a quarter below it, all over the tensor
+        return torch.nn.functional.gelu(normal() * 4)
     if kind == "tiny":            # the middle of the exponent range's lower end, still normal
         return lap() * 1e-24
     if kind == "wide":            # spread over more binades than the buckets have
@@ -1775,6 +1783,8 @@ BUCKET_CASES = [("laplace", 2_621_442, 2, {}, 100), ("laplace", 9_699_328, 8, {}
                 ("uneven", 256 * 31_252, 8, {}, 100), ("steps", 5_000_001, 2, {}, 100), ("steps", 5_400_000, 8, {}, 100), ("spike", 6_000_001, 4, {}, 100),
                 ("spike", 5_400_002, 8, dict(dist=2), 100), ("tiny", 4_222_222, 4, {}, 100), ("wide", 4_222_222, 4, {}, 100),
                 ("subnormal", 4_222_222, 4, {}, 77), ("nan", 2_722_222, 2, {}, 95), ("inf", 2_722_222, 2, {}, 95),
+                ("tiny tile", 4_222_222, 4, {}, 100), ("tiny tile", (1 << 24) + 77, 2, {}, 100), ("wide gelu", 9_682_944, 4, {}, 100),
+                ("mostly tiny", 4_333_333, 2, {}, 100),
                 # dense sweeps just above the line, left to the streaming kernel
                 ("gelu", 3_000_000, 2, {}, 100), ("relu", 2_700_002, 2, {}, 100), ("spike", 4_194_306, 8, dict(dist=2), 100)]
 BUCKETS_LEFT = BUCKET_CASES[-3:]
@@ -1805,7 +1815,7 @@ def test_bucket_search_equals_the_streaming_search(qp, kind, n, bits, v, t):
                     ws[grid:grid + 32].cpu().numpy().copy(),
                     int(ws[LEAST_WORKSPACE + 4:LEAST_WORKSPACE + 8].cpu().numpy().view(np.uint32)[0]) if room else None))
     (a, ra, qa, left), (b, rb, qb, _), (c, rc, qc, _) = out
-    assert left == (1 if kind in ("wide", "subnormal", "nan", "inf") or (kind, n, bits, v, t) in BUCKETS_LEFT else 0)   # found unsuitable on the device, or not
+    assert left == (1 if kind in ("wide", "subnormal", "nan", "inf", "mostly tiny") or (kind, n, bits, v, t) in BUCKETS_LEFT else 0)   # found unsuitable on the device, or not
     assert np.array_equal(np.isnan(a), np.isnan(b))
     fin = np.isfinite(b)
     assert np.allclose(a[fin], b[fin], rtol=REL_SCORE_PAIRWISE, atol=0.0) and np.array_equal(a[~fin & ~np.isnan(b)], b[~fin & ~np.isnan(b)])
@@ -1861,3 +1871,14 @@ def test_narrow_buckets_where_the_candidates_lie_dense(qp, n, bits):
     took, streaming = sender_us(qp, xd, bits, cfg, True), sender_us(qp, xd, bits, cfg, False)
     print(f"[case] gelu {n} {bits} bit: {took:.1f} / {streaming:.1f} us", flush=True)
     assert took <= 0.8 * streaming
+
+
+@pytest.mark.parametrize("kind", ["tiny tile", "wide gelu"])
+def test_elements_outside_the_buckets_do_not_cost_a_second_search(qp, kind):
+    """Many in one tile or an eighth and more of all tiles: the streaming search ran behind the sort, 1.19 of its own sender path."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    xd, cfg = bucket_values(kind, 9_682_944, g), variant_cfg(qp, {}, 100)
+    took, streaming = sender_us(qp, xd, 4, cfg, True), sender_us(qp, xd, 4, cfg, False)
+    print(f"[case] {kind}: {took:.1f} / {streaming:.1f} us", flush=True)
+    assert took <= 1.08 * streaming

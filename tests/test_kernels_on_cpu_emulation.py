@@ -127,6 +127,10 @@ def small_input(kind, n):
         g = np.random.default_rng(n)
         x = np.where(g.random(n) < 0.9, np.abs(g.laplace(0.0, 0.5, size=n)), 10.0 ** g.uniform(-3, 38.5, size=n))
         return si.f32_to_bf16_bits(np.minimum(x, 3.3e38).astype(np.float32)) | np.uint16(0x8000)
+    if kind in ("tiny_stretch", "mostly_tiny"):   # below the buckets' range: a stretch of one tile, most of the tensor
+        x = np.random.default_rng(n).laplace(0.0, 0.5, size=n).astype(np.float32)
+        x[n // 3:n // 3 + (200 if kind == "tiny_stretch" else n * 3 // 5)] *= np.float32(1e-5)
+        return x
     if kind == "offset":      # all values in two binades
         return (np.random.default_rng(n).standard_normal(n) * 0.8 + 60.0).astype(np.float32)
     if kind == "subnormal":   # the grid's reciprocal is infinite: the search's full clamp sequence
@@ -186,11 +190,13 @@ RECORD_REFUSED = ("default", ("C3", 3_001, 4, dict(record="short"), 1))
 # thresholds to a bucket; a tensor that it leaves to the streaming kernel
 BUCKET_CASES = [("bucket", c) for c in (("C1", 1_301, 2, {}, 20), ("C2", 3_001, 3, dict(conc=3), 13), ("offset", 2_601, 4, {}, 20),
                                         ("subnormal", 2_003, 4, {}, 13))]
+# Elements outside the buckets: more in one tile than its own blocks should score; too many of the tensor for the sort to pay
+OUTSIDE_CASES = [("bucket", ("tiny_stretch", 1_302, 2, dict(conc=3), 13)), ("bucket", ("mostly_tiny", 1_303, 3, {}, 13))]
 # The waves of a block in either order (candidates of two waves, so that both hand out classes)
 WAVE_CASES = [("bucket", ("offset", 1_301, 3, dict(late=w), 68)) for w in (0, 1)]
 ALL_CASES = ([("default", c) for c in TILE_CASES] + [("streaming", c) for c in STREAM_CASES] + [("streaming", REFUSED)] + ACIQ_ONLY
              + CONCURRENT_CASES + STREAM_C2F_CASES + RECORD_CASES + [RECORD_REFUSED]
-             + TABLE_STATS_CASES + PAIRS_CASES + BUCKET_CASES + WAVE_CASES)
+             + TABLE_STATS_CASES + PAIRS_CASES + BUCKET_CASES + OUTSIDE_CASES + WAVE_CASES)
 
 
 def case_id(tag, c):
@@ -239,6 +245,11 @@ def test_the_bucket_build_takes_the_buckets(runs, tag, case):
     assert p.returncode == 0
     plan = np.fromfile(os.path.join(out_dir, "plan.bin"), np.uint32)
     assert plan[1] == (1 if case[0] == "subnormal" else 0)     # 1: left to the streaming kernel
+
+
+def test_only_a_tensor_mostly_outside_the_buckets_is_left_to_the_streaming_kernel(runs):
+    plans = [np.fromfile(os.path.join(runs[case_id(*a)][1], "plan.bin"), np.uint32)[:2].tolist() for a in OUTSIDE_CASES]
+    assert plans == [[0, 0], [1, 1]]     # found before the sort, or not at all
 
 
 @pytest.mark.parametrize("tag,case", BUCKET_CASES[:3], ids=[case_id(*a) for a in BUCKET_CASES[:3]])
