@@ -173,6 +173,7 @@ template <int DT> __global__ __launch_bounds__(kStThreads) void k_search_tile(Ti
 }
 
 constexpr int kPkThreadsPick = 256;
+template <bool CONDITIONAL>
 __global__ __launch_bounds__(kPkThreadsPick) void k_search_pick(const double *__restrict__ partials, uint32_t nblocks,
                                                                 double *__restrict__ scores, Ctl *__restrict__ ctl,
                                                                 qp_search_result_t *__restrict__ res,
@@ -180,7 +181,7 @@ __global__ __launch_bounds__(kPkThreadsPick) void k_search_pick(const double *__
                                                                 double *__restrict__ scores_by_j,
                                                                 const uint32_t *__restrict__ skip)
 {
-    if (skip && *skip) return;   // nothing was scored
+    if (CONDITIONAL && *skip) return;   // nothing was scored
     __shared__ double sh[kStMaxCands];
     __shared__ uint32_t sh_flag;
     const uint32_t tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
@@ -212,7 +213,8 @@ hipError_t launch_search_pick(const double *partials, uint32_t nblocks, uint32_t
                               const uint32_t *skip, hipStream_t s)
 {
     char *w = static_cast<char *>(ws);
-    hipLaunchKernelGGL(k_search_pick, dim3(count), dim3(kPkThreadsPick), 0, s, partials, nblocks, scores_list,
+    auto kernel = skip ? k_search_pick<true> : k_search_pick<false>;
+    hipLaunchKernelGGL(kernel, dim3(count), dim3(kPkThreadsPick), 0, s, partials, nblocks, scores_list,
                        reinterpret_cast<Ctl *>(w + kOffCtl), reinterpret_cast<qp_search_result_t *>(w + kOffResult),
                        reinterpret_cast<qp_qparams_t *>(w + kOffQParams), n, reinterpret_cast<double *>(w + kOffScores), skip);
     return hipGetLastError();
