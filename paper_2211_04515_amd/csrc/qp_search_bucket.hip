@@ -12,10 +12,12 @@
 //                   bucket starts; then it takes its share of the buckets and lists, for each, the pieces on which a
 //                   candidate's x^ and e's binade are constant, and the sums that these pieces need;
 //   k_bucket_sum    blocks gather a bucket's elements from the tiles, form its sums, and add each candidate's pieces;
-//                   elements outside the buckets' range (about 0.1 % of them) are scored one by one;
+//                   elements outside the buckets' range (0.1 to 2 % as a rule) are scored one by one;
 //   k_search_pick   adds the blocks' partial sums and takes the first minimum, as for the tile search.
-// A tensor that this does not suit (NaN or Inf, a grid that needs the full clamp sequence, so many thresholds to a bucket that
-// the pieces outgrow their lists) is found out on the device and left to the streaming kernel, which is launched behind.
+// A tensor that this does not suit is left to the streaming kernel, which is launched behind.  The set-up finds most of them (NaN or
+// Inf, a grid that needs the full clamp sequence, too many elements outside the buckets: see bucket_plan): the call then takes 4 to 10
+// us longer than without buckets.  Lists that outgrow their room are found by k_bucket_sort, whose time is then spent: 27 us at 4.3 M
+// elements, 40 at 9.7 M, 100 at 30 M.
 #include "qp_bucket.hpp"
 
 namespace qp {
@@ -544,6 +546,7 @@ constexpr uint32_t kBsBatch = kBsThreads * kBsQuads;   // loads of a batch
 constexpr uint32_t kBsItems = 128;         // most work items that a block lists at a time
 
 struct alignas(4) Float4U { float x, y, z, w; };   // a run starts at any element
+struct alignas(2) Pair16U { uint16_t x, y; };      // a bucket's start and end in a tile, one load
 
 // Sums of one work item: those that its pieces refer to, or one class's by interval between cuts.
 struct BucketSums {
@@ -840,17 +843,16 @@ __global__ __launch_bounds__(kBsThreads, 4) void k_bucket_sum(BucketArgs a)
             const float base = at.value(0);
             if (tid < a.ncand) sh_piece[tid] = a.pieces[(uint64_t)b * kBkCands + tid];   // (kept in LDS, not in registers)
             // the runs, two a lane, and where their loads come in the item's list of loads
+            Pair16U row[2];
+#pragma unroll
+            for (uint32_t i = 0; i < 2u; ++i)   // (a tile past the last has the last one's run, and no loads of it)
+                row[i] = *reinterpret_cast<const Pair16U *>(a.table + (uint64_t)min(2u * tid + i, a.tiles - 1u) * kBkRow + b);
             uint32_t nl[2], sum = 0u;
 #pragma unroll
             for (uint32_t i = 0; i < 2u; ++i) {
-                const uint32_t t = 2u * tid + i;
-                nl[i] = 0u;
-                if (t < a.tiles) {
-                    const uint16_t *row = a.table + (uint64_t)t * kBkRow + b;
-                    const uint32_t from = row[0], len = (uint32_t)row[1] - from;
-                    runs[t] = from | (len << 16);
-                    nl[i] = (len + 3u) / 4u;
-                }
+                const uint32_t t = 2u * tid + i, from = row[i].x, len = (uint32_t)row[i].y - from;
+                runs[t] = from | (len << 16);
+                nl[i] = t < a.tiles ? (len + 3u) / 4u : 0u;
                 sum += nl[i];
             }
             static_assert(kBsTiles <= 2u * kBsThreads, "two runs a lane");
