@@ -209,6 +209,7 @@ def c2_leg(qp, si, torch, x_host, args, timed_reps, side_streams):
     qdev = ws.data_ptr() + qp.qp_ws_offset(qp.QP_WS_QPARAMS)
     ev = lambda: torch.cuda.Event(enable_timing=True)
     counter = [0]
+    events = []
 
     # The six passes of a step are independent jobs (each a whole sender + receiver path at its own bitwidth), so the
     # step hands them round-robin to `--streams` HIP streams of default priority, each with a workspace of its own
@@ -223,7 +224,7 @@ def c2_leg(qp, si, torch, x_host, args, timed_reps, side_streams):
             qp.qp_compress_async(xs[i], bits, ws, packs[bits][i])
             qp.qp_unpack_dequant_dev(packs[bits][i], bits, qdev, ys[i])
             return
-        e = [ev() for _ in range(5)]
+        e = events.pop()
         e[0].record()
         qp.qp_stats_async(xs[i], ws)
         e[1].record()
@@ -286,6 +287,12 @@ def c2_leg(qp, si, torch, x_host, args, timed_reps, side_streams):
     # the same `steps` steps again with a HIP event between the stages of every pass (this costs a few
     # microseconds per pass and one extra small launch, so it is kept out of `value`)
     timers = []
+    # (an event is made when it is first recorded, which takes the host as long as a stage takes the GPU)
+    for _ in range(args.steps * len(bits_set)):
+        events.append([ev() for _ in range(5)])
+        for e in events[-1]:
+            e.record()
+    torch.cuda.synchronize()
     t0 = time.perf_counter()
     for _ in range(args.steps):
         step(timers)
@@ -298,13 +305,13 @@ def c2_leg(qp, si, torch, x_host, args, timed_reps, side_streams):
     mean = lambda v: float(sum(v) / len(v))
     search_us = mean(stage["search"])       # every kernel of the search, all six bitwidths
     by_bits = {b: mean([e[1].elapsed_time(e[2]) * 1e3 for bits, e in timers if bits == b]) for b in bits_set}
-    events = "HIP events around every search in an instrumented repetition of the timed steps"
-    roofline = bucket_entry(n, mean([by_bits[b] for b in bits_set if b <= 8]), events + ", the passes at up to 8 bit")
+    by_events = "HIP events around every search in an instrumented repetition of the timed steps"
+    roofline = bucket_entry(n, mean([by_bits[b] for b in bits_set if b <= 8]), by_events + ", the passes at up to 8 bit")
     roofline["us_per_launch_by_bitwidth"] = {str(b): by_bits[b] for b in bits_set}
     roofline_16 = None
     if 16 in by_bits:
         roofline_16 = alu_entry("k_search_mse<fp32,13> (+ k_search_setup)", n, 101, by_bits[16], TRAFFIC_RATIO["c2_search_bytes"],
-                                events + ", the passes at 16 bit")
+                                by_events + ", the passes at 16 bit")
         roofline_16["traffic_source"] = TRAFFIC_SOURCE["c2"]
 
     rot = (f"{args.kernel_reps} back-to-back launches between two HIP events, every stream rotating over at least {NBUF} distinct "

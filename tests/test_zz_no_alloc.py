@@ -1,7 +1,8 @@
 """The sender path for callers that cannot allocate (qp_compress_noalloc: the workspace is a static
 device array inside the library) against qp_compress_async with a caller-owned workspace: same packed
 stream and same winner's record, bit for bit, on calls in a row whose inputs shrink (the array keeps
-the previous call's contents), for each of the search kernels; and the payload against the oracle.
+the previous call's contents), for each of the search kernels but those of the value buckets, for which the
+array has no room; and the payload against the oracle.
 Runs last in the suite and also alone in a fresh process (the array's address is looked up on the
 first call)."""
 import ctypes as C
