@@ -17,6 +17,8 @@ constexpr uint32_t kBkCands = 128;           // most candidates of a sweep
 #ifndef QP_BUCKET_SUM_BLOCKS
 #define QP_BUCKET_SUM_BLOCKS 1024            // summing blocks: four per compute unit
 #endif
+// Senders of 9.7 M elements, t = 100, with 2^-8 / 2^-10 / 2^-12: Laplace data at 2 bit 116 / 113 / 226 us (too many binades for 256 buckets, left to the
+// streaming kernel), 8 bit 135 / 144 / 145; lognormal data at 2 bit 157 / 144 / 141; after GELU, 4 bit 143 / 143 / 145.
 #ifndef QP_BUCKET_DEPTH
 #define QP_BUCKET_DEPTH 0x1p-10              // smallest element that has a bucket, as a share of |mean| + s_E
 #endif
@@ -36,7 +38,10 @@ constexpr uint32_t kBkRow = kBkKeys + 4u;                        // table entrie
 constexpr uint32_t kBkCutCap = 512, kBkOwnCap = 96, kBkPieceCap = 768;
 constexpr uint32_t kBkCutAll = (1u << 19) / kBkTiles, kBkClassAll = (1u << 16) / kBkTiles, kBkPieceAll = (1u << 19) / kBkTiles;   // of one sorting block
 
-constexpr uint32_t kBkSample = 1024, kBkSampleOut = 384;   // elements of a sample; most of them outside the buckets
+// Elements of a sample, and most of them outside the buckets.  Those are scored one by one at about the streaming search's rate, so at
+// 9.7 M elements, where the buckets save 98 us of 208 (2 bit) or 64 (8 bit), half to a third of a tensor uses that up: a fifth outside 177 / 198
+// and 196 / 201 us.
+constexpr uint32_t kBkSample = 1024, kBkSampleOut = 384;
 struct BucketPlan {
     uint32_t unsuited;    // 1: the set-up leaves this tensor to the streaming kernel ...
     uint32_t fallback;    // ... or the sort does
@@ -134,6 +139,7 @@ __device__ inline void bucket_plan(const BucketSetup &b, const GridModel &g, con
         // b_R far below b_E (after ReLU or GELU, by 10 to 20): most candidates' thresholds lie much closer than the first one's
         const bool dense = fmax(g.s_e, g.s_r) > QP_BUCKET_DENSE * fmin(g.s_e, g.s_r);
         const uint32_t width = dense && b.dense_width ? b.dense_width : b.width;
+        // up to 16 s_E from the mean: with 8 / 16 / 32 of them Laplace data at 8 bit takes 137 / 144 / 145 us, lognormal data at 2 bit 145 / 144 / 141
         const double am = fabs(g.mean) + g.s_e, reach = 16.0 * g.s_e;
         const double lo = fmax(am * QP_BUCKET_DEPTH, fabs(g.mean) - reach), hi = fabs(g.mean) + reach;
         const uint32_t plo = __float_as_uint((float)lo), phi = __float_as_uint((float)hi);
@@ -141,7 +147,8 @@ __device__ inline void bucket_plan(const BucketSetup &b, const GridModel &g, con
         uint32_t shift = 8u;
         if (ok)
             while ((phi >> shift) - (plo >> shift) + 1u > width) ++shift;
-        // thresholds that a typical bucket holds, all candidates together
+        // thresholds that a typical bucket holds, all candidates together.  The lists have room for 512; nothing measured comes near 250 (190 the
+        // most, after a GELU of N(0, 6^2) at 8 bit and t = 127, and that by buckets is faster: 197 / 242 us)
         const double cell = (double)__uint_as_float(__float_as_uint((float)am) & 0x7f800000u) * (double)(1u << shift) * 0x1p-23;
         BucketPlan p{};
         p.unsuited = (!ok || !safe || (dense && b.dense_width == 0u) || shift > 19u || !(inv * cell <= 250.0)) ? 1u : 0u;
